@@ -242,11 +242,16 @@ int run_reduce(caramel_plan* p, const Binding& bd, const DeviceTables& dt, bool 
   a.count = r.count;
   a.world = p->host.cfg.world;
   a.bf16 = p->host.cfg.dtype == CARAMEL_BF16;
-  a.nontemporal = p->opt.nontemporal != 0;
   a.tree = p->host.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
   // by default a workgroup takes a whole tile in one go: vectors per lane = tile / workgroup size
   const bool lng = cls == kLong;
   a.block = lng ? p->opt.block : p->opt.small_block;
+  // Writing through pays for replicas that stream from HBM, and long tiles exist for those only (at
+  // least 32 MiB each): VGG-16 1469 -> 1437 us, Inception-v3 544 -> 525, 12 workers 449 -> 431.
+  // Where the last-level cache holds the data it costs (24 workers of 3 MB, small tiles: 38.5 -> 46.2
+  // us), and so it does for fused buffers, which unpack is about to read (Inception-v3's stages
+  // 359 -> 363 us).
+  a.policy = p->opt.nontemporal == 0 ? kPlain : (lng && direct ? kThrough : kStream);
   const uint32_t tile_vecs = lng ? bd.shape.long_vecs : bd.shape.small_vecs;
   a.unroll = p->opt.unroll ? p->opt.unroll : std::max(1u, tile_vecs / a.block);
   // stream-major walk: as many vectors per lane as a whole tile has rows of lanes (2, 4 or 8)
@@ -286,8 +291,8 @@ int run_copy(caramel_plan* p, const DeviceTables& dt, bool unpack, Range r, hipS
   // Measured on MI355X: with 0.9 GB of fused buffers (Inception-v3, Transformer) streaming loads and
   // stores are 3 to 5 points of peak faster; with 52 MB (ResNet-50), which the last-level cache
   // holds, 10 points slower.
-  a.nontemporal = p->opt.nontemporal != 0 &&
-                  p->host.fused_elems * p->host.elem_size() * p->host.cfg.world >= (uint64_t(256) << 20);
+  const bool large = p->host.fused_elems * p->host.elem_size() * p->host.cfg.world >= (uint64_t(256) << 20);
+  a.policy = p->opt.nontemporal != 0 && large ? kStream : kPlain;
   if (tracing())
     std::fprintf(stderr, "caramel: call %llu %s stream %p copy tiles [%u, %u)\n", (unsigned long long)p->call_no,
                  unpack ? "unpack " : "pack   ", (void*)s, r.begin, r.begin + r.count);

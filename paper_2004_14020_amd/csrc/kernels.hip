@@ -29,20 +29,29 @@ typedef CARAMEL_GLOBAL uint32_t* gu32_ptr;
 constexpr int kCopyBlock = 1024;  // pack / unpack workgroup
 constexpr int kMaxBlock = 1024;  // ring-reduce workgroups are 256, 512 or 1024 lanes
 
-template <bool NT>
-__device__ __forceinline__ u32x4 ld(gvec_ptr p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-template <bool NT>
-__device__ __forceinline__ void st(gvec_ptr p, u32x4 v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
-
 // scalar base + 32-bit lane byte offset
 __device__ __forceinline__ gvec_ptr at(gvec_ptr base, uint32_t byte_off) {
   return reinterpret_cast<gvec_ptr>(reinterpret_cast<CARAMEL_GLOBAL char*>(base) + byte_off);
+}
+
+template <int P>
+__device__ __forceinline__ u32x4 ld(gvec_ptr p) {
+  if constexpr (P != kPlain) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <int P>
+__device__ __forceinline__ void st(gvec_ptr base, uint32_t byte_off, u32x4 v) {
+  if constexpr (P == kThrough) {
+    // C++ has no way to ask for this pair on a 128-bit store; the buffer form takes the policy as an
+    // operand.  The resource is the bare base (untyped, no bound of its own).
+    constexpr int kRaw = 0x00027000, kNt = 2, kSc1 = 16;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, kRaw);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, int(byte_off), 0, kSc1 | kNt);
+  } else if constexpr (P == kStream) {
+    __builtin_nontemporal_store(v, at(base, byte_off));
+  } else {
+    *at(base, byte_off) = v;
+  }
 }
 
 __device__ __forceinline__ f32x4 bits_to_f32(u32x4 v) { return __builtin_bit_cast(f32x4, v); }
@@ -156,7 +165,7 @@ __device__ __forceinline__ float widen(uint16_t h) { return __uint_as_float(uint
 // ------------------------------------------------------------------------------------------
 // W known at compile time: all W loads of a vector (times U vectors) are issued before the
 // first add, so each lane keeps W*U 128-bit requests in flight.
-template <int W, int U, bool BF16, bool NT, bool TREE>
+template <int W, int U, bool BF16, int P, bool TREE>
 __global__ void __launch_bounds__(kMaxBlock)
 k_ring_reduce(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
               uint32_t count, float inv_w) {
@@ -179,23 +188,23 @@ k_ring_reduce(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int k = 0; k < W; ++k) x[u][k] = ld<NT>(at(p[k], (v + u * B) * 16u));
+        for (int k = 0; k < W; ++k) x[u][k] = ld<P>(at(p[k], (v + u * B) * 16u));
       __builtin_amdgcn_sched_barrier(0);  // keep all loads ahead of the arithmetic
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const u32x4 y = combine<W, BF16, TREE>(x[u], inv_w);
 #pragma unroll
-        for (int k = 0; k < W; ++k) st<NT>(at(p[k], (v + u * B) * 16u), y);
+        for (int k = 0; k < W; ++k) st<P>(p[k], (v + u * B) * 16u, y);
       }
     }
     for (; v < nvec; v += B) {
       u32x4 x[W];
 #pragma unroll
-      for (int k = 0; k < W; ++k) x[k] = ld<NT>(at(p[k], v * 16u));
+      for (int k = 0; k < W; ++k) x[k] = ld<P>(at(p[k], v * 16u));
       __builtin_amdgcn_sched_barrier(0);
       const u32x4 y = combine<W, BF16, TREE>(x, inv_w);
 #pragma unroll
-      for (int k = 0; k < W; ++k) st<NT>(at(p[k], v * 16u), y);
+      for (int k = 0; k < W; ++k) st<P>(p[k], v * 16u, y);
     }
     // a run that ends a tensor may stop inside a vector: finish it element by element
     const uint32_t rem = tl.n_elems - nvec * VE;
@@ -228,7 +237,7 @@ k_ring_reduce(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__
 // TREE: the values are added as the balanced pairwise tree of the halving-doubling order instead of
 // a chain: worker k's value is merged with the open partial sums the way a binary counter carries
 // (one level per trailing one bit of k), which needs log2(W) partial sums per vector.
-template <int W, int U, int D, bool BF16, bool NT, bool RAGGED, bool TREE = false>
+template <int W, int U, int D, bool BF16, int P, bool RAGGED, bool TREE = false>
 __device__ __forceinline__ void sm_walk(const gvec_ptr (&p)[W], uint32_t v, uint32_t B, uint32_t nvec, float inv_w) {
   static_assert(D >= 2 && D <= W, "look-ahead between 2 and W workers");
   static_assert(!TREE || (W & (W - 1)) == 0, "the tree needs a power of two");
@@ -244,12 +253,12 @@ __device__ __forceinline__ void sm_walk(const gvec_ptr (&p)[W], uint32_t v, uint
 #pragma unroll
   for (int k = 0; k < D - 1; ++k)
 #pragma unroll
-    for (int u = 0; u < U; ++u) buf[k][u] = ld<NT>(at(p[k], off(u)));
+    for (int u = 0; u < U; ++u) buf[k][u] = ld<P>(at(p[k], off(u)));
 #pragma unroll
   for (int k = 0; k < W; ++k) {
     if (k + D - 1 < W) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) buf[(k + D - 1) % D][u] = ld<NT>(at(p[k + D - 1], off(u)));
+      for (int u = 0; u < U; ++u) buf[(k + D - 1) % D][u] = ld<P>(at(p[k + D - 1], off(u)));
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -278,11 +287,11 @@ __device__ __forceinline__ void sm_walk(const gvec_ptr (&p)[W], uint32_t v, uint
 #pragma unroll
   for (int k = 0; k < W; ++k)
 #pragma unroll
-    for (int u = 0; u < SURE; ++u) st<NT>(at(p[k], off(u)), y[u]);
+    for (int u = 0; u < SURE; ++u) st<P>(p[k], off(u), y[u]);
   if constexpr (RAGGED) {
     if (last_ok) {
 #pragma unroll
-      for (int k = 0; k < W; ++k) st<NT>(at(p[k], off(U - 1)), y[U - 1]);
+      for (int k = 0; k < W; ++k) st<P>(p[k], off(U - 1), y[U - 1]);
     }
   }
 }
@@ -292,7 +301,7 @@ __device__ __forceinline__ void sm_walk(const gvec_ptr (&p)[W], uint32_t v, uint
 // with the next worker's U loads in flight while the current ones are added.  A 1024-lane
 // workgroup thus requests 1024*U*16 contiguous bytes of one replica before it moves on to the
 // next replica, which the memory system serves better than many short interleaved runs.
-template <int W, int U, bool BF16, bool NT>
+template <int W, int U, bool BF16, int P>
 __global__ void __launch_bounds__(kMaxBlock)
 k_ring_reduce_sm(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
                  uint32_t count, float inv_w) {
@@ -314,11 +323,11 @@ k_ring_reduce_sm(const ReduceTile* __restrict__ tiles, const uint64_t* __restric
       u32x4 cur[U], nxt[U];
       Chain<BF16> acc[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) cur[u] = ld<NT>(at(p[0], (v + u * B) * 16u));
+      for (int u = 0; u < U; ++u) cur[u] = ld<P>(at(p[0], (v + u * B) * 16u));
 #pragma unroll
       for (int k = 1; k < W; ++k) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) nxt[u] = ld<NT>(at(p[k], (v + u * B) * 16u));
+        for (int u = 0; u < U; ++u) nxt[u] = ld<P>(at(p[k], (v + u * B) * 16u));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -337,7 +346,7 @@ k_ring_reduce_sm(const ReduceTile* __restrict__ tiles, const uint64_t* __restric
 #pragma unroll
       for (int k = 0; k < W; ++k)
 #pragma unroll
-        for (int u = 0; u < U; ++u) st<NT>(at(p[k], (v + u * B) * 16u), y[u]);
+        for (int u = 0; u < U; ++u) st<P>(p[k], (v + u * B) * 16u, y[u]);
     }
     // what is left (fewer than U*B vectors: up to U rows of B lanes, the last row possibly
     // ragged) is walked the same way in one go
@@ -347,23 +356,23 @@ k_ring_reduce_sm(const ReduceTile* __restrict__ tiles, const uint64_t* __restric
       if (v < nvec) {
         u32x4 x[W];
 #pragma unroll
-        for (int k = 0; k < W; ++k) x[k] = ld<NT>(at(p[k], v * 16u));
+        for (int k = 0; k < W; ++k) x[k] = ld<P>(at(p[k], v * 16u));
         __builtin_amdgcn_sched_barrier(0);
         const u32x4 y = combine<W, BF16, false>(x, inv_w);
 #pragma unroll
-        for (int k = 0; k < W; ++k) st<NT>(at(p[k], v * 16u), y);
+        for (int k = 0; k < W; ++k) st<P>(p[k], v * 16u, y);
       }
     }
-    if (rows_left == 2) sm_walk<W, 2, 2, BF16, NT, true>(p, v, B, nvec, inv_w);
+    if (rows_left == 2) sm_walk<W, 2, 2, BF16, P, true>(p, v, B, nvec, inv_w);
     if constexpr (U >= 4) {
-      if (rows_left == 3) sm_walk<W, 3, 2, BF16, NT, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 4) sm_walk<W, 4, 2, BF16, NT, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 3) sm_walk<W, 3, 2, BF16, P, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 4) sm_walk<W, 4, 2, BF16, P, true>(p, v, B, nvec, inv_w);
     }
     if constexpr (U >= 8) {
-      if (rows_left == 5) sm_walk<W, 5, 2, BF16, NT, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 6) sm_walk<W, 6, 2, BF16, NT, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 7) sm_walk<W, 7, 2, BF16, NT, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 8) sm_walk<W, 8, 2, BF16, NT, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 5) sm_walk<W, 5, 2, BF16, P, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 6) sm_walk<W, 6, 2, BF16, P, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 7) sm_walk<W, 7, 2, BF16, P, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 8) sm_walk<W, 8, 2, BF16, P, true>(p, v, B, nvec, inv_w);
     }
     const uint32_t rem = tl.n_elems - nvec * VE;
     if (threadIdx.x < rem) {
@@ -389,7 +398,7 @@ k_ring_reduce_sm(const ReduceTile* __restrict__ tiles, const uint64_t* __restric
 // Stream-major kernel for the halving-doubling order (W a power of two up to 16): the same walk,
 // one replica after the other, with the values added as the balanced tree.  The tree does not
 // depend on the segment, so the workers are read in the order 0 .. W-1.
-template <int W, int U, bool BF16, bool NT>
+template <int W, int U, bool BF16, int P>
 __global__ void __launch_bounds__(kMaxBlock)
 k_ring_reduce_smt(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
                   uint32_t count, float inv_w) {
@@ -406,23 +415,23 @@ k_ring_reduce_smt(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
 #pragma unroll 1
     // (the walk with a guarded last row, although every row is whole here: the compiler keeps
     // fewer values live in that form and does not spill)
-    for (; v < whole; v += U * B) sm_walk<W, U, 2, BF16, NT, true, true>(p, v, B, nvec, inv_w);
+    for (; v < whole; v += U * B) sm_walk<W, U, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
     const uint32_t rows_left = (nvec - whole + B - 1) / B;
     if (rows_left == 1) {
       if (v < nvec) {
         u32x4 x[W];
 #pragma unroll
-        for (int k = 0; k < W; ++k) x[k] = ld<NT>(at(p[k], v * 16u));
+        for (int k = 0; k < W; ++k) x[k] = ld<P>(at(p[k], v * 16u));
         __builtin_amdgcn_sched_barrier(0);
         const u32x4 y = combine<W, BF16, true>(x, inv_w);
 #pragma unroll
-        for (int k = 0; k < W; ++k) st<NT>(at(p[k], v * 16u), y);
+        for (int k = 0; k < W; ++k) st<P>(p[k], v * 16u, y);
       }
     }
-    if (rows_left == 2) sm_walk<W, 2, 2, BF16, NT, true, true>(p, v, B, nvec, inv_w);
+    if (rows_left == 2) sm_walk<W, 2, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
     if constexpr (U >= 4) {
-      if (rows_left == 3) sm_walk<W, 3, 2, BF16, NT, true, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 4) sm_walk<W, 4, 2, BF16, NT, true, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 3) sm_walk<W, 3, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
+      if (rows_left == 4) sm_walk<W, 4, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
     }
     const uint32_t rem = tl.n_elems - nvec * VE;
     if (threadIdx.x < rem) {
@@ -450,7 +459,7 @@ k_ring_reduce_smt(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
 // added.  What is left of a tile after whole groups of U*B vectors (up to U rows of B lanes, the
 // last row possibly ragged) is walked in one go with that many vectors per lane; a lane beyond
 // the end of a ragged row reads the tile's last vector instead and stores nothing for it.
-template <bool BF16, bool NT, int U>
+template <bool BF16, int P, int U>
 __global__ void __launch_bounds__(kMaxBlock)
 k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
                   uint32_t count, uint32_t W, float inv_w) {
@@ -487,7 +496,7 @@ k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
 #pragma unroll
       for (int u = 0; u < N; ++u) {
         cur[u] = u32x4{0u, 0u, 0u, 0u};
-        if (!late[u]) cur[u] = ld<NT>(at(base, off[u]));
+        if (!late[u]) cur[u] = ld<P>(at(base, off[u]));
       }
       const uint32_t steps = SPLIT ? W + 1 : W;
       for (uint32_t k = 1; k < steps; ++k) {
@@ -498,11 +507,11 @@ k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
 #pragma unroll
           for (int u = 0; u < N; ++u) {
             nxt[u] = cur[u];
-            if (late[u]) nxt[u] = ld<NT>(at(base, off[u]));
+            if (late[u]) nxt[u] = ld<P>(at(base, off[u]));
           }
         } else {
 #pragma unroll
-          for (int u = 0; u < N; ++u) nxt[u] = ld<NT>(at(base, off[u]));
+          for (int u = 0; u < N; ++u) nxt[u] = ld<P>(at(base, off[u]));
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -539,7 +548,7 @@ k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
         base = reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off;
 #pragma unroll
         for (int u = 0; u < N; ++u)
-          if (!RAGGED || u < N - 1 || last_ok) st<NT>(at(base, off[u]), y[u]);
+          if (!RAGGED || u < N - 1 || last_ok) st<P>(base, off[u], y[u]);
       }
     };
     const uint32_t whole = nvec / (U * B) * (U * B);  // the same for all lanes
@@ -564,7 +573,7 @@ k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
             if (k0 + i < W) {
               uint32_t w = tl.first + k0 + i;
               if (w >= W) w -= W;
-              x[i] = ld<NT>(at(reinterpret_cast<gvec_ptr>(row[w]) + tl.vec_off, v * 16u));
+              x[i] = ld<P>(at(reinterpret_cast<gvec_ptr>(row[w]) + tl.vec_off, v * 16u));
             }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -575,7 +584,7 @@ k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
             }
         }
         const u32x4 y = acc.finish(inv_w);
-        for (uint32_t k = 0; k < W; ++k) st<NT>(at(reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off, v * 16u), y);
+        for (uint32_t k = 0; k < W; ++k) st<P>(reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off, v * 16u, y);
       }
       if (rows_left == 2) chain(v, std::integral_constant<int, 2>{}, std::true_type{}, std::false_type{});
       if (rows_left == 3) chain(v, std::integral_constant<int, 3>{}, std::true_type{}, std::false_type{});
@@ -612,7 +621,7 @@ k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
 // at a time: their eight vectors are added as a three-level tree, and the partial sums of the
 // blocks are merged the way a binary counter carries (block j closes as many levels as j + 1 has
 // trailing zeros), which is the same tree  ((x0+x1)+(x2+x3)) + ...  up to its root.
-template <bool BF16, bool NT>
+template <bool BF16, int P>
 __global__ void __launch_bounds__(kMaxBlock)
 k_ring_reduce_tree_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
                        uint32_t count, uint32_t W, float inv_w) {
@@ -633,7 +642,7 @@ k_ring_reduce_tree_any(const ReduceTile* __restrict__ tiles, const uint64_t* __r
           u32x4 x[kBlk];
 #pragma unroll
           for (int i = 0; i < kBlk; ++i)
-            x[i] = ld<NT>(at(reinterpret_cast<gvec_ptr>(row[j * kBlk + i]) + tl.vec_off, v * 16u));
+            x[i] = ld<P>(at(reinterpret_cast<gvec_ptr>(row[j * kBlk + i]) + tl.vec_off, v * 16u));
           __builtin_amdgcn_sched_barrier(0);
           Chain<BF16> t[kBlk];
 #pragma unroll
@@ -654,7 +663,7 @@ k_ring_reduce_tree_any(const ReduceTile* __restrict__ tiles, const uint64_t* __r
           if (uint32_t(j) + 1 == n_blocks) y = t[0].finish(inv_w);
         }
       }
-      for (uint32_t k = 0; k < W; ++k) st<NT>(at(reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off, v * 16u), y);
+      for (uint32_t k = 0; k < W; ++k) st<P>(reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off, v * 16u, y);
     }
     const uint32_t rem = tl.n_elems - nvec * VE;
     if (threadIdx.x < rem) {
@@ -701,7 +710,7 @@ k_ring_reduce_tree_any(const ReduceTile* __restrict__ tiles, const uint64_t* __r
 // grid.y = worker.  A tiny member leaves most lanes idle; measured against one wavefront per 8 KiB
 // run, which keeps every lane busy, this is 2 to 7 points of peak faster where it matters and
 // equal where the members are small.
-template <typename E, bool UNPACK, bool NT>
+template <typename E, bool UNPACK, int P>
 __global__ void __launch_bounds__(kCopyBlock)
 k_copy(const CopyTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
        uint32_t W, uint32_t fused_row) {
@@ -714,7 +723,7 @@ k_copy(const CopyTile* __restrict__ tiles, const uint64_t* __restrict__ rows, ui
   const uint32_t nvec = t.n_elems / VE;
   gvec_ptr src = UNPACK ? fp : tp;
   gvec_ptr dst = UNPACK ? tp : fp;
-  for (uint32_t v = lane; v < nvec; v += kCopyBlock) st<NT>(dst + v, ld<NT>(src + v));
+  for (uint32_t v = lane; v < nvec; v += kCopyBlock) st<P>(dst, v * 16u, ld<P>(src + v));
   // ragged end of a member, and (pack only) the +0.0 padding up to the next member
   CARAMEL_GLOBAL E* se = reinterpret_cast<CARAMEL_GLOBAL E*>(src);
   CARAMEL_GLOBAL E* de = reinterpret_cast<CARAMEL_GLOBAL E*>(dst);
@@ -724,14 +733,14 @@ k_copy(const CopyTile* __restrict__ tiles, const uint64_t* __restrict__ rows, ui
 
 template <int W, int U>
 hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-#define CARAMEL_GO(BF, NT, TR) \
-  hipLaunchKernelGGL((k_ring_reduce<W, U, BF, NT, TR>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
-#define CARAMEL_GO2(BF, NT) \
-  do { if (a.tree) CARAMEL_GO(BF, NT, true); else CARAMEL_GO(BF, NT, false); } while (0)
+#define CARAMEL_GO(BF, P, TR) \
+  hipLaunchKernelGGL((k_ring_reduce<W, U, BF, P, TR>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
+#define CARAMEL_GO2(BF, P) \
+  do { if (a.tree) CARAMEL_GO(BF, P, true); else CARAMEL_GO(BF, P, false); } while (0)
   if (a.bf16) {
-    if (a.nontemporal) CARAMEL_GO2(true, true); else CARAMEL_GO2(true, false);
+    if (a.policy != kPlain) CARAMEL_GO2(true, kStream); else CARAMEL_GO2(true, kPlain);
   } else {
-    if (a.nontemporal) CARAMEL_GO2(false, true); else CARAMEL_GO2(false, false);
+    if (a.policy != kPlain) CARAMEL_GO2(false, kStream); else CARAMEL_GO2(false, kPlain);
   }
 #undef CARAMEL_GO2
 #undef CARAMEL_GO
@@ -740,17 +749,24 @@ hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) 
 
 template <int W, int U>
 hipError_t launch_sm(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-#define CARAMEL_SM(BF, NT) \
-  hipLaunchKernelGGL((k_ring_reduce_sm<W, U, BF, NT>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
+#define CARAMEL_SM(BF, P) \
+  hipLaunchKernelGGL((k_ring_reduce_sm<W, U, BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
+#define CARAMEL_SM3(BF) \
+  do { \
+    if (a.policy == kThrough) CARAMEL_SM(BF, kThrough); \
+    else if (a.policy == kStream) CARAMEL_SM(BF, kStream); \
+    else CARAMEL_SM(BF, kPlain); \
+  } while (0)
   if constexpr (U >= 8) {
     // eight vectors per lane fit the register file for fp32 only (launch_u sends bf16 elsewhere)
     if (a.bf16) return hipErrorInvalidValue;
-    if (a.nontemporal) CARAMEL_SM(false, true); else CARAMEL_SM(false, false);
+    CARAMEL_SM3(false);
   } else if (a.bf16) {
-    if (a.nontemporal) CARAMEL_SM(true, true); else CARAMEL_SM(true, false);
+    CARAMEL_SM3(true);
   } else {
-    if (a.nontemporal) CARAMEL_SM(false, true); else CARAMEL_SM(false, false);
+    CARAMEL_SM3(false);
   }
+#undef CARAMEL_SM3
 #undef CARAMEL_SM
   return hipGetLastError();
 }
@@ -759,15 +775,22 @@ hipError_t launch_sm(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s)
 // two passes
 template <int W>
 hipError_t launch_smt(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-#define CARAMEL_SMT(U, BF, NT) \
-  hipLaunchKernelGGL((k_ring_reduce_smt<W, U, BF, NT>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
+#define CARAMEL_SMT(U, BF, P) \
+  hipLaunchKernelGGL((k_ring_reduce_smt<W, U, BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
+#define CARAMEL_SMT3(U, BF) \
+  do { \
+    if (a.policy == kThrough) CARAMEL_SMT(U, BF, kThrough); \
+    else if (a.policy == kStream) CARAMEL_SMT(U, BF, kStream); \
+    else CARAMEL_SMT(U, BF, kPlain); \
+  } while (0)
   if (a.bf16) {
-    if (a.nontemporal) CARAMEL_SMT(2, true, true); else CARAMEL_SMT(2, true, false);
+    CARAMEL_SMT3(2, true);
   } else if (a.stream_major >= 4) {
-    if (a.nontemporal) CARAMEL_SMT(4, false, true); else CARAMEL_SMT(4, false, false);
+    CARAMEL_SMT3(4, false);
   } else {
-    if (a.nontemporal) CARAMEL_SMT(2, false, true); else CARAMEL_SMT(2, false, false);
+    CARAMEL_SMT3(2, false);
   }
+#undef CARAMEL_SMT3
 #undef CARAMEL_SMT
   return hipGetLastError();
 }
@@ -809,23 +832,26 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   }
   if (a.tree && a.world != 1) {  // a tree over one worker is the chain
     if (a.world != 32 && a.world != 64) return hipErrorInvalidValue;
-#define CARAMEL_TREE(BF, NT) \
-  hipLaunchKernelGGL((k_ring_reduce_tree_any<BF, NT>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
+#define CARAMEL_TREE(BF, P) \
+  hipLaunchKernelGGL((k_ring_reduce_tree_any<BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
     if (a.bf16) {
-      if (a.nontemporal) CARAMEL_TREE(true, true); else CARAMEL_TREE(true, false);
+      if (a.policy != kPlain) CARAMEL_TREE(true, kStream); else CARAMEL_TREE(true, kPlain);
     } else {
-      if (a.nontemporal) CARAMEL_TREE(false, true); else CARAMEL_TREE(false, false);
+      if (a.policy != kPlain) CARAMEL_TREE(false, kStream); else CARAMEL_TREE(false, kPlain);
     }
 #undef CARAMEL_TREE
     return hipGetLastError();
   }
-#define CARAMEL_ANY(BF, NT) \
-  hipLaunchKernelGGL((k_ring_reduce_any<BF, NT, 4>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
-  if (a.bf16) {
-    if (a.nontemporal) CARAMEL_ANY(true, true); else CARAMEL_ANY(true, false);
-  } else {
-    if (a.nontemporal) CARAMEL_ANY(false, true); else CARAMEL_ANY(false, false);
-  }
+#define CARAMEL_ANY(BF, P) \
+  hipLaunchKernelGGL((k_ring_reduce_any<BF, P, 4>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
+#define CARAMEL_ANY2(BF) \
+  do { \
+    if (a.policy == kThrough) CARAMEL_ANY(BF, kThrough); \
+    else if (a.policy == kStream) CARAMEL_ANY(BF, kStream); \
+    else CARAMEL_ANY(BF, kPlain); \
+  } while (0)
+  if (a.bf16) CARAMEL_ANY2(true); else CARAMEL_ANY2(false);
+#undef CARAMEL_ANY2
 #undef CARAMEL_ANY
   return hipGetLastError();
 }
@@ -840,10 +866,10 @@ hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
   const dim3 grid(a.count, a.world);
 #define CARAMEL_CP(E, UN) \
   do { \
-    if (a.nontemporal) \
-      hipLaunchKernelGGL((k_copy<E, UN, true>), grid, dim3(kCopyBlock), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, a.fused_row); \
+    if (a.policy != kPlain) \
+      hipLaunchKernelGGL((k_copy<E, UN, kStream>), grid, dim3(kCopyBlock), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, a.fused_row); \
     else \
-      hipLaunchKernelGGL((k_copy<E, UN, false>), grid, dim3(kCopyBlock), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, a.fused_row); \
+      hipLaunchKernelGGL((k_copy<E, UN, kPlain>), grid, dim3(kCopyBlock), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, a.fused_row); \
   } while (0)
   if (a.bf16) {
     if (a.unpack) CARAMEL_CP(uint16_t, true); else CARAMEL_CP(uint16_t, false);
