@@ -353,8 +353,7 @@ enum {
   CARAMEL_OPT_LONG_RUN_BYTES = 11,
   /* Long tiles: non-zero selects the stream-major kernel, which walks the workers one replica at
    * a time; the value (2, 4 or 8, default 8) is the most vectors a lane keeps per worker: a tile
-   * of block * value vectors is walked in one go (8 exists for fp32 chains of at most 8 workers;
-   * otherwise 4 is used).  0 fetches all workers' values at once. */
+   * of block * value vectors is walked in one go (8 exists for fp32 chains; otherwise 4 is used).  0 fetches all workers' values at once. */
   CARAMEL_OPT_STREAM_MAJOR = 12,
   /* PER_UNIT launches over long tiles: like CARAMEL_OPT_LAUNCH_MIN_BYTES.  Default 64 MiB. */
   CARAMEL_OPT_LONG_LAUNCH_MIN_BYTES = 13,
@@ -371,13 +370,13 @@ enum {
   /* The last so many long tiles of every plan stream are cut into pieces of one vector per lane
    * (16 KiB for 1024 lanes), which a workgroup fetches from all replicas at once.  When a launch
    * runs out of tiles, the workgroups still at work finish at different times; with short pieces
-   * at the end that drain is short.  Default 128 (half a tile per compute unit); 0 switches it off.
+   * at the end that drain is short.  Default 64 (a quarter of a tile per compute unit); 0 switches it off.
    * Takes effect at the next caramel_bind. */
   CARAMEL_OPT_TAIL_TILES = 16,
-  /* 1 (default): for world sizes other than 2, 4, 8 and 16 (ring order), tiles follow aligned
-   * blocks of memory across the boundaries between ring segments: a tile that contains a
-   * boundary is summed in two parts, each in its segment's order, and a run is everything of one
-   * unit that is contiguous in a tensor.  0, and always for 2, 4, 8 and 16 workers: tiles (and
+  /* 1 (default): for world sizes other than 2, 4 and 8 (ring order), tiles follow aligned blocks of
+   * memory across the boundaries between ring segments (small tiles of 16 workers excepted): a tile
+   * that contains boundaries is summed in parts, each in its segment's order, and a run is everything
+   * of one unit that is contiguous in a tensor.  0, and always for 2, 4 and 8 workers: tiles (and
    * runs) end at segment boundaries.  Takes effect at the next caramel_bind.  Results do not
    * depend on it. */
   CARAMEL_OPT_SPLIT_TILES = 17

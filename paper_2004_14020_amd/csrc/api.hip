@@ -259,6 +259,8 @@ int run_reduce(caramel_plan* p, const Binding& bd, const DeviceTables& dt, bool 
   if (lng && p->opt.stream_major) {
     const uint32_t rows = tile_vecs / a.block;
     a.stream_major = std::min(p->opt.stream_major, rows >= 8 ? 8u : (rows >= 4 ? 4u : 2u));
+  } else if (lng && bd.shape.split_tiles && bd.shape.max_splits) {
+    a.stream_major = 1;  // the option was changed after these tables were built, and only the walk takes split tiles
   }
   a.max_grid = p->opt.max_grid;
   if (tracing())
@@ -784,15 +786,28 @@ void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& 
   //  * a replica of less than 32 MiB is done before long tiles pay off (a 1024-lane workgroup
   //    walks its tile one replica after the other): every run is cut into small tiles, whose
   //    workgroups fetch all replicas at once (the MLP configuration: 3.4 against 6.3 us);
-  //  * fp32 chains of 2, 4 or 8 workers, for which the kernel can keep eight vectors per lane in
-  //    registers, get long tiles of 128 KiB once a replica holds 64 MiB (VGG-16 +2 %); everything
-  //    else 64 KiB.
+  //  * fp32 chains keep eight vectors per lane in registers, so their long tiles can be 128 KiB,
+  //    which stream best, but are few: with less than about three rounds of the 256 workgroups
+  //    that run at a time the last round is felt.  2, 4 and 8 workers take them from 64 MiB per
+  //    replica on (VGG-16 528 MiB: 1438 -> 1396 us, ResNet-50 98 MiB: 275.3 -> 272.5); the others,
+  //    whose tiles also straddle segments and cost a step more, from 192 MiB on (16 workers, VGG-16:
+  //    2893 -> 2807, ResNet-v2-152 230 MiB: 1330 -> 1316, but Inception-v3 91 MiB: 506 -> 521; 12
+  //    workers, ResNet-50: 415 either way).  Everything else 64 KiB.
   bd.shape.tail_vecs = p->opt.block;  // one vector per lane: a piece is fetched from all replicas at once
   const caramel_config& c = p->host.cfg;
-  //  * tiles may straddle a segment boundary where the kernel for the world size sums the two
-  //    parts in their own orders (the kernel for any world size; W = 48, 4 MiB chunks: 63 -> 71 %
-  //    of peak); the kernels specialised for 2, 4, 8 and 16 workers get tiles inside one segment.
-  bd.shape.split_tiles = p->opt.split_tiles && reduce_handles_split_tiles(c.world);
+  //  * tiles may straddle segment boundaries where the kernel sums the parts in their own orders.
+  //    Every boundary costs a step of the walk and saves a partial tile.  Up to 8 workers a step is
+  //    dear and segments are long: none for 2, 4 and 8, whose walk without boundaries is unrolled
+  //    (ResNet-50, 8 workers: 272 us without, 277 with one; VGG-16 1396 / 1395), one for the others
+  //    (VGG-16, 6 workers: 1082 / 1060).  16 workers: one (Inception-v3 517 / 506, VGG-16 2795 /
+  //    2807).  From 24 workers on segments are shorter than a tile: up to four (ResNet-50 bf16, 32
+  //    workers: 607 without, 579 with one, 561 with four; Inception-v3, 48 workers: 1802, 1612, 1534;
+  //    ResNet-50, 24 workers: 869, 831, 826).
+  const bool unrolled = c.world == 2 || c.world == 4 || c.world == 8;
+  bd.shape.small_splits = reduce_handles_split_tiles(c.world, false) ? 1 : 0;
+  bd.shape.max_splits = unrolled || !reduce_handles_split_tiles(c.world, p->opt.stream_major != 0) ? 0 : (c.world >= 24 ? 4 : 1);
+  bd.shape.split_tiles = p->opt.split_tiles && c.pattern == CARAMEL_PATTERN_RING &&
+                         (bd.shape.small_splits || bd.shape.max_splits);
   uint64_t replica_bytes = 0;
   for (uint64_t e : p->host.tensor_elems) replica_bytes += e * p->host.elem_size();
   //  * halving-doubling with 32 or 64 workers has no kernel that walks the replicas one at a time
@@ -802,8 +817,8 @@ void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& 
     bd.shape.long_run_bytes = (replica_bytes < (32u << 20) || tree_any) ? ~uint64_t(0) : 16u << 10;
   if (bd.shape.long_vecs == 0) {
     const bool wide = c.dtype == CARAMEL_F32 && c.pattern != CARAMEL_PATTERN_HALVING_DOUBLING &&
-                      (c.world == 2 || c.world == 4 || c.world == 8) && p->opt.stream_major >= 8 &&
-                      p->opt.block == 1024 && replica_bytes >= (64u << 20);
+                      p->opt.stream_major >= 8 && p->opt.block == 1024 &&
+                      replica_bytes >= (uint64_t(unrolled ? 64 : 192) << 20);
     // the bf16 tree keeps two vectors per lane: tiles of one pass (a second pass of a workgroup
     // waits for the stores of the first; Transformer shapes 65.4 -> 66.5 %)
     const bool narrow = c.dtype == CARAMEL_BF16 && c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;

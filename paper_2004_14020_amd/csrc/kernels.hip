@@ -1,12 +1,12 @@
 // gfx950 kernels of the aggregation path.  Everything here is bandwidth work: 128-bit
 // coalesced loads and stores, no matrix cores.
 //
-//  k_ring_reduce   ring reduce-scatter arithmetic, 1/W scaling and all-gather (paper
+//  k_walk, k_ring_reduce, k_ring_reduce_smt, k_ring_reduce_tree_any
+//                  ring reduce-scatter arithmetic, 1/W scaling and all-gather (paper
 //                  sections 2 and 4.4: partial sums travel round the ring and are added to
 //                  at each worker; the owner's result is then copied to every worker).
-//                  A workgroup handles one tile, which lies inside one ring segment, so the
-//                  chain of workers  first, first+1, ...  is the same for all lanes and the
-//                  W base pointers live in scalar registers.
+//                  A workgroup handles one tile: long tiles one replica after the other (chains:
+//                  k_walk, trees: k_ring_reduce_smt), small ones with all replicas at once.
 //  k_copy          pack / unpack of batched parameters (section 4.2) through an offset table,
 //                  one workgroup per run of at most 16 KiB.
 #include "kernels.hpp"
@@ -90,18 +90,23 @@ struct Chain {
     a = a + o.a;
     if constexpr (BF16) b = b + o.b;
   }
-  // becomes `o` in the lanes where `c` holds (a select on the bits: no arithmetic)
-  __device__ __forceinline__ void take_if(bool c, const Chain& o) {
-    a.x = c ? o.a.x : a.x;
-    a.y = c ? o.a.y : a.y;
-    a.z = c ? o.a.z : a.z;
-    a.w = c ? o.a.w : a.w;
-    if constexpr (BF16) {
-      b.x = c ? o.b.x : b.x;
-      b.y = c ? o.b.y : b.y;
-      b.z = c ? o.b.z : b.z;
-      b.w = c ? o.b.w : b.w;
-    }
+  // the sum of no values: -0.0, which leaves every first value as it is
+  __device__ __forceinline__ void zero() {
+    a = f32x4{-0.0f, -0.0f, -0.0f, -0.0f};
+    if constexpr (BF16) b = a;
+  }
+  // add() in the lanes where `c` holds; the others add -0.0, which changes nothing
+  __device__ __forceinline__ void add_if(bool c, u32x4 x) {
+    constexpr uint32_t kNothing = BF16 ? 0x80008000u : 0x80000000u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = c ? x[i] : kNothing;
+    add(x);
+  }
+  // the sum is formed here: left to itself, the compiler moves the additions of an unrolled walk behind
+  // its last load, and every value it has loaded stays live until then
+  __device__ __forceinline__ void pin() {
+    asm volatile("" : "+v"(a));
+    if constexpr (BF16) asm volatile("" : "+v"(b));
   }
   __device__ __forceinline__ u32x4 finish(float inv_w) {
     if constexpr (BF16) {
@@ -296,105 +301,6 @@ __device__ __forceinline__ void sm_walk(const gvec_ptr (&p)[W], uint32_t v, uint
   }
 }
 
-// Stream-major variant for large tiles (chain orders only).  A lane handles U vectors, but
-// instead of fetching all W workers' values at once it walks the chain one worker at a time,
-// with the next worker's U loads in flight while the current ones are added.  A 1024-lane
-// workgroup thus requests 1024*U*16 contiguous bytes of one replica before it moves on to the
-// next replica, which the memory system serves better than many short interleaved runs.
-template <int W, int U, bool BF16, int P>
-__global__ void __launch_bounds__(kMaxBlock)
-k_ring_reduce_sm(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
-                 uint32_t count, float inv_w) {
-  constexpr uint32_t VE = BF16 ? 8 : 4;
-  for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
-    const ReduceTile tl = tiles[begin + ti];
-    gvec_ptr p[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      uint32_t w = tl.first + k;
-      if (w >= uint32_t(W)) w -= W;
-      p[k] = reinterpret_cast<gvec_ptr>(rows[size_t(tl.row) * W + w]) + tl.vec_off;
-    }
-    const uint32_t nvec = tl.n_elems / VE;
-    const uint32_t B = blockDim.x;
-    uint32_t v = threadIdx.x;
-    const uint32_t whole = nvec / (U * B) * (U * B);  // the same for all lanes
-    for (; v < whole; v += U * B) {
-      u32x4 cur[U], nxt[U];
-      Chain<BF16> acc[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) cur[u] = ld<P>(at(p[0], (v + u * B) * 16u));
-#pragma unroll
-      for (int k = 1; k < W; ++k) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) nxt[u] = ld<P>(at(p[k], (v + u * B) * 16u));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (k == 1) acc[u].start(cur[u]);
-          else acc[u].add(cur[u]);
-          cur[u] = nxt[u];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      u32x4 y[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        acc[u].add(cur[u]);
-        y[u] = acc[u].finish(inv_w);
-      }
-#pragma unroll
-      for (int k = 0; k < W; ++k)
-#pragma unroll
-        for (int u = 0; u < U; ++u) st<P>(p[k], (v + u * B) * 16u, y[u]);
-    }
-    // what is left (fewer than U*B vectors: up to U rows of B lanes, the last row possibly
-    // ragged) is walked the same way in one go
-    const uint32_t rows_left = (nvec - whole + B - 1) / B;
-    if (rows_left == 1) {
-      // at most one vector per lane: nothing to walk, fetch all workers' values at once
-      if (v < nvec) {
-        u32x4 x[W];
-#pragma unroll
-        for (int k = 0; k < W; ++k) x[k] = ld<P>(at(p[k], v * 16u));
-        __builtin_amdgcn_sched_barrier(0);
-        const u32x4 y = combine<W, BF16, false>(x, inv_w);
-#pragma unroll
-        for (int k = 0; k < W; ++k) st<P>(p[k], v * 16u, y);
-      }
-    }
-    if (rows_left == 2) sm_walk<W, 2, 2, BF16, P, true>(p, v, B, nvec, inv_w);
-    if constexpr (U >= 4) {
-      if (rows_left == 3) sm_walk<W, 3, 2, BF16, P, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 4) sm_walk<W, 4, 2, BF16, P, true>(p, v, B, nvec, inv_w);
-    }
-    if constexpr (U >= 8) {
-      if (rows_left == 5) sm_walk<W, 5, 2, BF16, P, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 6) sm_walk<W, 6, 2, BF16, P, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 7) sm_walk<W, 7, 2, BF16, P, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 8) sm_walk<W, 8, 2, BF16, P, true>(p, v, B, nvec, inv_w);
-    }
-    const uint32_t rem = tl.n_elems - nvec * VE;
-    if (threadIdx.x < rem) {
-      const uint32_t e = nvec * VE + threadIdx.x;
-      float val[W];
-      if constexpr (BF16) {
-#pragma unroll
-        for (int k = 0; k < W; ++k) val[k] = widen(reinterpret_cast<gu16_ptr>(p[k])[e]);
-        const uint16_t y = uint16_t(bf16_rne(combine_scalar<W, false>(val, inv_w)));
-#pragma unroll
-        for (int k = 0; k < W; ++k) reinterpret_cast<gu16_ptr>(p[k])[e] = y;
-      } else {
-#pragma unroll
-        for (int k = 0; k < W; ++k) val[k] = reinterpret_cast<gf32_ptr>(p[k])[e];
-        const float y = combine_scalar<W, false>(val, inv_w);
-#pragma unroll
-        for (int k = 0; k < W; ++k) reinterpret_cast<gf32_ptr>(p[k])[e] = y;
-      }
-    }
-  }
-}
-
 // Stream-major kernel for the halving-doubling order (W a power of two up to 16): the same walk,
 // one replica after the other, with the values added as the balanced tree.  The tree does not
 // depend on the segment, so the workers are read in the order 0 .. W-1.
@@ -454,162 +360,237 @@ k_ring_reduce_smt(const ReduceTile* __restrict__ tiles, const uint64_t* __restri
   }
 }
 
-// Any W: the chain is walked one worker at a time, like the stream-major kernel: the next
-// worker's base pointer (a scalar load) and its vectors are requested while the current ones are
-// added.  What is left of a tile after whole groups of U*B vectors (up to U rows of B lanes, the
-// last row possibly ragged) is walked in one go with that many vectors per lane; a lane beyond
-// the end of a ragged row reads the tile's last vector instead and stores nothing for it.
-template <bool BF16, int P, int U>
+// Chain orders, one replica after the other (long tiles of any W up to 64, and the small tiles of the
+// world sizes without a kernel of their own).
+//
+// Bound: HBM.  A 1024-lane workgroup asks for N * 16 KiB contiguous bytes of one replica, then of the
+// next, ...: it issues the next worker's N loads at once, then waits for the current worker's and adds
+// them.  The memory system serves such bursts best: an in-place update of 8 x 512 MiB (16 x 94 MiB)
+// reaches 82.5 (79.0) % of 8 TB/s with N = 8 and 79.1 (77.3) with N = 4; with each load re-issued as
+// soon as its own values were added, which keeps as many bytes in flight, 76.2 (74.0).
+//
+// The tile is a buffer resource of its own size in every replica: a lane beyond the end of a ragged
+// last row reads zeros that nothing uses and its stores are dropped, without a branch, and the loads
+// take no address registers: two sets of eight vectors and eight fp32 sums fit 128 VGPRs (four vectors
+// with bf16, whose sums take twice the room).
+constexpr uint32_t kNowhere = 0x40000000u;  // an offset beyond every tile
+constexpr int kRawBuffer = 0x00027000;      // resource word 3: untyped data
+
+// The segment boundaries inside a tile, in bytes from its start.
+struct Splits {
+  uint32_t n;
+  uint32_t at[kMaxSplits];
+  __device__ __forceinline__ explicit Splits(const ReduceTile& t, uint32_t elem_bytes) : n(0) {
+#pragma unroll
+    for (uint32_t i = 0; i < kMaxSplits; ++i) {
+      const uint32_t b = i == 0 ? t.split : t.more[i == 0 ? 0 : i - 1];
+      at[i] = b ? b * elem_bytes : ~0u;
+      n += b ? 1u : 0u;
+    }
+  }
+  // how many of them lie at or before `off`
+  __device__ __forceinline__ uint32_t before(uint32_t off) const {
+    uint32_t s = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kMaxSplits; ++i) s += off >= at[i] ? 1u : 0u;
+    return s;
+  }
+};
+
+// One tile's chain.  CW: the number of workers, 0 if known at run time only (the loop over them is
+// rolled then).
+// SPLIT (a tile across S segment boundaries, S < W; CW == 0): the workers are visited in the
+// tile's order and then the first S once more, W + S steps; a lane behind s of the boundaries, whose
+// sums start s workers later, adds the values of steps s .. s+W-1.  A lane asks for no data in the
+// steps it sits out, so nothing is fetched twice and the whole workgroup still reads one replica at a
+// time.
+template <int CW, bool BF16, int P, bool SPLIT>
+struct Walk {
+  static_assert(!SPLIT || CW == 0, "the unrolled loop has no room for the conditions");
+  static constexpr int kLoad = P == kPlain ? 0 : 2 /* nt */;
+  static constexpr int kStore = P == kPlain ? 0 : (P == kThrough ? 18 /* sc1 nt */ : 2);
+  const uint64_t* __restrict__ row;
+  uint64_t mine;       // CW == 0: the tile's address in replica `lane` (W <= 64: every wavefront holds all)
+  uint64_t start;      // bytes from a row's base to the tile
+  uint32_t workers, first, bytes;
+  const Splits& splits;
+  float inv_w;
+
+  __device__ __forceinline__ uint32_t W() const { return CW ? uint32_t(CW) : workers; }
+  __device__ __forceinline__ uint32_t steps() const { return W() + (SPLIT ? splits.n : 0u); }
+  __device__ __forceinline__ uint32_t worker(uint32_t k) const {  // k < 2 W
+    uint32_t w = first + k;
+    if (SPLIT && w >= 2 * W()) w -= W();
+    return w >= W() ? w - W() : w;
+  }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t res(uint32_t w) const {  // the tile in replica w
+    uint64_t base;
+    if constexpr (CW == 0) {
+      // from the lane that keeps it: no scalar load to wait for at every step
+      base = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(mine >> 32), int(w)))) << 32 |
+             uint32_t(__builtin_amdgcn_readlane(int(mine), int(w)));
+    } else {
+      base = row[w] + start;
+    }
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), 0, int(bytes), kRawBuffer);
+  }
+
+  // One pass over N vectors of this lane: `off` + u * `stride`, in bytes from the tile's start.
+  template <int N>
+  __device__ __forceinline__ void rows(uint32_t off, uint32_t stride) const {
+    const uint32_t n_steps = steps();
+    uint32_t lateness = 0;  // boundaries before each of the N vectors, four bits each
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) lateness |= splits.before(off + u * stride) << (4 * u);
+    }
+    auto wanted = [&](uint32_t k, int u) -> bool {  // step k adds to vector u
+      return !SPLIT || k - ((lateness >> (4 * u)) & 15u) < W();  // (unsigned: false for k < lateness)
+    };
+    Chain<BF16> acc[N];
+    u32x4 buf[2][N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) acc[u].zero();
+    auto load = [&](uint32_t k, int j) {
+      const __amdgpu_buffer_rsrc_t r = res(worker(k));
+      if constexpr (SPLIT) asm volatile("" : "+v"(lateness));  // (shifted anew: no registers for the parts)
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        buf[j][u] = __builtin_amdgcn_raw_buffer_load_b128(r, int(wanted(k, u) ? off + u * stride : kNowhere), 0, kLoad);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto add = [&](uint32_t k, int j) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        if constexpr (SPLIT) acc[u].add_if(wanted(k, u), buf[j][u]);
+        else acc[u].add(buf[j][u]);
+        acc[u].pin();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load(0, 0);
+    if constexpr (CW != 0) {
+      #pragma unroll
+      for (int k = 0; k < CW; ++k) {
+        if (k + 1 < CW) load(k + 1, (k + 1) % 2);
+        add(k, k % 2);
+      }
+    } else {
+      uint32_t k = 0;
+#pragma unroll 1
+      for (; k + 2 < n_steps; k += 2) {
+        load(k + 1, 1);
+        add(k, 0);
+        load(k + 2, 0);
+        add(k + 1, 1);
+      }
+      if (k + 1 < n_steps) load(k + 1, 1);
+      add(k, 0);
+      if (k + 1 < n_steps) add(k + 1, 1);
+    }
+    u32x4 y[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) y[u] = acc[u].finish(inv_w);
+#pragma unroll(CW ? CW : 4)
+    for (uint32_t k = 0; k < W(); ++k) {
+      const __amdgpu_buffer_rsrc_t r = res(worker(k));
+#pragma unroll
+      for (int u = 0; u < N; ++u) __builtin_amdgcn_raw_buffer_store_b128(y[u], r, int(off + u * stride), 0, kStore);
+    }
+  }
+
+  // One vector per lane: nothing to walk, the workers' values are fetched up to sixteen at a time.
+  __device__ __forceinline__ void column(uint32_t off) const {
+    constexpr int kMost = CW ? CW : 16;
+    const uint32_t n_steps = steps(), late = SPLIT ? splits.before(off) : 0;
+    Chain<BF16> acc;
+    acc.zero();
+    for (uint32_t k0 = 0; k0 < n_steps; k0 += kMost) {
+      u32x4 x[kMost];
+#pragma unroll
+      for (int i = 0; i < kMost; ++i)
+        if (CW || i == 0 || k0 + i < n_steps) {
+          const bool wanted = !SPLIT || k0 + i - late < W();
+          x[i] = __builtin_amdgcn_raw_buffer_load_b128(res(worker(k0 + i)), int(wanted ? off : kNowhere), 0, kLoad);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < kMost; ++i)
+        if (CW || i == 0 || k0 + i < n_steps) {
+          if constexpr (SPLIT) acc.add_if(k0 + i - late < W(), x[i]);
+          else acc.add(x[i]);
+        }
+    }
+    const u32x4 y = acc.finish(inv_w);
+#pragma unroll(CW ? CW : 4)
+    for (uint32_t k = 0; k < W(); ++k)
+      __builtin_amdgcn_raw_buffer_store_b128(y, res(worker(k)), int(off), 0, kStore);
+  }
+};
+
+// MAXN: most vectors per lane and pass (long tiles: 8 with fp32, 4 with bf16; small ones: 1); `cap`
+// lowers it.
+template <int CW, bool BF16, int P, int MAXN>
 __global__ void __launch_bounds__(kMaxBlock)
-k_ring_reduce_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
-                  uint32_t count, uint32_t W, float inv_w) {
+k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
+       uint32_t workers, uint32_t cap, float inv_w) {
   constexpr uint32_t VE = BF16 ? 8 : 4;
+  const uint32_t W = CW ? uint32_t(CW) : workers;
   for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
     const ReduceTile tl = tiles[begin + ti];
     const uint64_t* row = rows + size_t(tl.row) * W;
     const uint32_t nvec = tl.n_elems / VE;
     const uint32_t B = blockDim.x;
-    const uint32_t late_from = tl.split / VE;  // used for split tiles only
-    // One pass of the chain over N vectors of this lane, B apart, starting at v.
-    // SPLIT (a tile across a segment boundary, W >= 2): the workers are visited in the tile's
-    // order and then the first one once more, W + 1 steps; the lanes before the boundary add the
-    // values of steps 0 .. W-1, the late lanes (whose sums start one worker later) those of steps
-    // 1 .. W.  A lane asks for no data in the step it sits out, so nothing is fetched twice and
-    // the whole workgroup still reads one replica at a time.
-    auto chain = [&](uint32_t v, auto n_tag, auto ragged_tag, auto split_tag) {
-      constexpr int N = decltype(n_tag)::value;
-      constexpr bool RAGGED = decltype(ragged_tag)::value;
-      constexpr bool SPLIT = decltype(split_tag)::value;
-      Chain<BF16> acc[N];
-      u32x4 cur[N], nxt[N];
-      const bool last_ok = !RAGGED || v + (N - 1) * B < nvec;
-      uint32_t off[N];
-      bool late[N];
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        off[u] = (v + u * B) * 16u;
-        late[u] = SPLIT && v + u * B >= late_from;
-      }
-      if (RAGGED && !last_ok) off[N - 1] = (nvec - 1) * 16u;
-      uint32_t w = tl.first;
-      gvec_ptr base = reinterpret_cast<gvec_ptr>(row[w]) + tl.vec_off;
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        cur[u] = u32x4{0u, 0u, 0u, 0u};
-        if (!late[u]) cur[u] = ld<P>(at(base, off[u]));
-      }
-      const uint32_t steps = SPLIT ? W + 1 : W;
-      for (uint32_t k = 1; k < steps; ++k) {
-        w = (w + 1 == W) ? 0 : w + 1;
-        base = reinterpret_cast<gvec_ptr>(row[w]) + tl.vec_off;
-        if (SPLIT && k == W) {
-          // back at the first worker: only the late lanes still need its value
-#pragma unroll
-          for (int u = 0; u < N; ++u) {
-            nxt[u] = cur[u];
-            if (late[u]) nxt[u] = ld<P>(at(base, off[u]));
-          }
-        } else {
-#pragma unroll
-          for (int u = 0; u < N; ++u) nxt[u] = ld<P>(at(base, off[u]));
+    const uint64_t start = uint64_t(tl.vec_off) * 16;
+    const Splits splits(tl, 16 / VE);
+    const uint32_t lane = threadIdx.x % 64;
+    const uint64_t mine = CW == 0 || tl.split ? row[lane < W ? lane : W - 1] + start : 0;
+    const uint32_t total_rows = (nvec + B - 1) / B;
+    for (uint32_t done = 0; done < total_rows;) {
+      const uint32_t left = total_rows - done;
+      const uint32_t n = left < cap ? left : cap;  // rows of this pass
+      const uint32_t off = (done * B + threadIdx.x) * 16;
+      // a pass of n rows ends where they do
+      const uint32_t end = (done + n) * B < nvec ? (done + n) * B * 16 : nvec * 16;
+      auto go = [&](auto split_tag) {
+        constexpr bool kSplit = decltype(split_tag)::value;
+        const Walk<kSplit ? 0 : CW, BF16, P, kSplit> walk{row, mine, start, W, tl.first, end, splits, inv_w};
+        if constexpr (MAXN >= 8) {
+          if (n > 4) walk.template rows<8>(off, B * 16);
         }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-          // cur holds the values of step k - 1
-          if (k == 1) {
-            acc[u].start(cur[u]);  // (a late lane starts over at the next step)
-          } else if (SPLIT && k == 2) {
-            Chain<BF16> fresh;
-            fresh.start(cur[u]);
-            acc[u].add(cur[u]);
-            acc[u].take_if(late[u], fresh);
-          } else {
-            acc[u].add(cur[u]);
-          }
-          cur[u] = nxt[u];
+        if constexpr (MAXN >= 4) {
+          if (n > 2 && n <= 4) walk.template rows<4>(off, B * 16);
+          if (n == 2) walk.template rows<2>(off, B * 16);
         }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      u32x4 y[N];
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        if constexpr (SPLIT) {
-          Chain<BF16> more = acc[u];
-          more.add(cur[u]);
-          acc[u].take_if(late[u], more);
-        } else {
-          if (W == 1) acc[u].start(cur[u]);
-          else acc[u].add(cur[u]);
-        }
-        y[u] = acc[u].finish(inv_w);
-      }
-      for (uint32_t k = 0; k < W; ++k) {
-        base = reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off;
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-          if (!RAGGED || u < N - 1 || last_ok) st<P>(base, off[u], y[u]);
-      }
-    };
-    const uint32_t whole = nvec / (U * B) * (U * B);  // the same for all lanes
-    uint32_t v = threadIdx.x;
-    const uint32_t rows_left = (nvec - whole + B - 1) / B;
-    static_assert(U == 4, "the dispatches below list the row counts of U = 4");
-    if (tl.split) {
-      for (; v < whole; v += U * B) chain(v, std::integral_constant<int, U>{}, std::false_type{}, std::true_type{});
-      if (rows_left == 1) chain(v, std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{});
-      if (rows_left == 2) chain(v, std::integral_constant<int, 2>{}, std::true_type{}, std::true_type{});
-      if (rows_left == 3) chain(v, std::integral_constant<int, 3>{}, std::true_type{}, std::true_type{});
-      if (rows_left == 4) chain(v, std::integral_constant<int, 4>{}, std::true_type{}, std::true_type{});
-    } else {
-      for (; v < whole; v += U * B) chain(v, std::integral_constant<int, U>{}, std::false_type{}, std::false_type{});
-      if (rows_left == 1 && v < nvec) {
-        // at most one vector per lane: nothing to walk; fetch the workers' values eight at a time
-        Chain<BF16> acc;
-        for (uint32_t k0 = 0; k0 < W; k0 += 8) {
-          u32x4 x[8];
-#pragma unroll
-          for (uint32_t i = 0; i < 8; ++i)
-            if (k0 + i < W) {
-              uint32_t w = tl.first + k0 + i;
-              if (w >= W) w -= W;
-              x[i] = ld<P>(at(reinterpret_cast<gvec_ptr>(row[w]) + tl.vec_off, v * 16u));
-            }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (uint32_t i = 0; i < 8; ++i)
-            if (k0 + i < W) {
-              if (k0 + i == 0) acc.start(x[i]);
-              else acc.add(x[i]);
-            }
-        }
-        const u32x4 y = acc.finish(inv_w);
-        for (uint32_t k = 0; k < W; ++k) st<P>(reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off, v * 16u, y);
-      }
-      if (rows_left == 2) chain(v, std::integral_constant<int, 2>{}, std::true_type{}, std::false_type{});
-      if (rows_left == 3) chain(v, std::integral_constant<int, 3>{}, std::true_type{}, std::false_type{});
-      if (rows_left == 4) chain(v, std::integral_constant<int, 4>{}, std::true_type{}, std::false_type{});
+        if (n == 1) walk.column(off);
+      };
+      if (tl.split) go(std::true_type{});
+      else go(std::false_type{});
+      done += n;
     }
+    // a run that ends a tensor may stop inside a vector: finish it element by element
     const uint32_t rem = tl.n_elems - nvec * VE;
     if (threadIdx.x < rem) {
       const size_t e = size_t(tl.vec_off) * VE + nvec * VE + threadIdx.x;
-      // an element behind the boundary of a split tile starts one worker later
-      uint32_t w = tl.first + ((tl.split && nvec * VE + threadIdx.x >= tl.split) ? 1u : 0u);
-      if (w >= W) w -= W;
-      if constexpr (BF16) {
-        float acc = widen(reinterpret_cast<gu16_ptr>(row[w])[e]);
-        for (uint32_t k = 1; k < W; ++k) {
-          w = (w + 1 == W) ? 0 : w + 1;
-          acc = acc + widen(reinterpret_cast<gu16_ptr>(row[w])[e]);
+      // an element behind s boundaries of a split tile starts s workers later
+      const uint32_t first = (tl.first + splits.before((nvec * VE + threadIdx.x) * (16 / VE))) % W;
+      float acc = -0.0f;
+      for (uint32_t k0 = 0; k0 < W; k0 += 8) {
+        float x[8];
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) {
+          uint32_t w = first + (k0 + i < W ? k0 + i : 0);
+          if (w >= W) w -= W;
+          if constexpr (BF16) x[i] = widen(reinterpret_cast<gu16_ptr>(row[w])[e]);
+          else x[i] = reinterpret_cast<gf32_ptr>(row[w])[e];
         }
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) acc = k0 + i < W ? acc + x[i] : acc;
+      }
+      if constexpr (BF16) {
         const uint16_t y = uint16_t(bf16_rne(acc * inv_w));
         for (uint32_t k = 0; k < W; ++k) reinterpret_cast<gu16_ptr>(row[k])[e] = y;
       } else {
-        float acc = reinterpret_cast<gf32_ptr>(row[w])[e];
-        for (uint32_t k = 1; k < W; ++k) {
-          w = (w + 1 == W) ? 0 : w + 1;
-          acc = acc + reinterpret_cast<gf32_ptr>(row[w])[e];
-        }
         const float y = acc * inv_w;
         for (uint32_t k = 0; k < W; ++k) reinterpret_cast<gf32_ptr>(row[k])[e] = y;
       }
@@ -747,30 +728,6 @@ hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) 
   return hipGetLastError();
 }
 
-template <int W, int U>
-hipError_t launch_sm(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-#define CARAMEL_SM(BF, P) \
-  hipLaunchKernelGGL((k_ring_reduce_sm<W, U, BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
-#define CARAMEL_SM3(BF) \
-  do { \
-    if (a.policy == kThrough) CARAMEL_SM(BF, kThrough); \
-    else if (a.policy == kStream) CARAMEL_SM(BF, kStream); \
-    else CARAMEL_SM(BF, kPlain); \
-  } while (0)
-  if constexpr (U >= 8) {
-    // eight vectors per lane fit the register file for fp32 only (launch_u sends bf16 elsewhere)
-    if (a.bf16) return hipErrorInvalidValue;
-    CARAMEL_SM3(false);
-  } else if (a.bf16) {
-    CARAMEL_SM3(true);
-  } else {
-    CARAMEL_SM3(false);
-  }
-#undef CARAMEL_SM3
-#undef CARAMEL_SM
-  return hipGetLastError();
-}
-
 // fp32: four vectors per lane; bf16 (twice the partial sums per vector): two, i.e. a long tile in
 // two passes
 template <int W>
@@ -798,13 +755,6 @@ hipError_t launch_smt(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s
 template <int W>
 hipError_t launch_u(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
   if (a.stream_major && a.tree) return launch_smt<W>(a, grid, inv_w, s);
-  if (a.stream_major && !a.tree) {
-    if constexpr (W <= 8) {
-      if (a.stream_major >= 8 && !a.bf16) return launch_sm<W, 8>(a, grid, inv_w, s);
-    }
-    if (a.stream_major >= 4) return launch_sm<W, 4>(a, grid, inv_w, s);
-    return launch_sm<W, 2>(a, grid, inv_w, s);
-  }
   // W * U vectors per lane must fit the register budget of a 1024-lane workgroup
   constexpr uint32_t kMaxU = W <= 4 ? 4 : (W <= 8 ? 2 : 1);
   uint32_t u = a.unroll ? a.unroll : kMaxU;
@@ -823,6 +773,38 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   if (a.max_grid && g > a.max_grid) g = a.max_grid;
   const dim3 grid(g);
   const float inv_w = 1.0f / float(a.world);
+  const bool chain = !a.tree || a.world == 1;  // a tree over one worker is the chain
+  const bool any = !(a.world == 2 || a.world == 4 || a.world == 8 || a.world == 16);
+  if (chain && (a.stream_major || any)) {
+#define CARAMEL_WALK(CW, BF, P, MAXN) \
+  hipLaunchKernelGGL((k_walk<CW, BF, P, MAXN>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, \
+                     a.stream_major < MAXN ? (a.stream_major ? a.stream_major : 1u) : uint32_t(MAXN), inv_w)
+#define CARAMEL_WALK3(CW, BF, MAXN) \
+  do { \
+    if (a.policy == kThrough) CARAMEL_WALK(CW, BF, kThrough, MAXN); \
+    else if (a.policy == kStream) CARAMEL_WALK(CW, BF, kStream, MAXN); \
+    else CARAMEL_WALK(CW, BF, kPlain, MAXN); \
+  } while (0)
+#define CARAMEL_WALK_T(CW) \
+  do { if (a.bf16) CARAMEL_WALK3(CW, true, 4); else CARAMEL_WALK3(CW, false, 8); } while (0)
+    if (!a.stream_major) {
+      if (a.bf16) CARAMEL_WALK3(0, true, 1); else CARAMEL_WALK3(0, false, 1);
+    } else if (a.world == 2) {
+      CARAMEL_WALK_T(2);
+    } else if (a.world == 4) {
+      CARAMEL_WALK_T(4);
+    } else if (a.world == 8) {
+      CARAMEL_WALK_T(8);
+    } else if (a.world == 16) {
+      CARAMEL_WALK_T(16);
+    } else {
+      CARAMEL_WALK_T(0);
+    }
+#undef CARAMEL_WALK_T
+#undef CARAMEL_WALK3
+#undef CARAMEL_WALK
+    return hipGetLastError();
+  }
   switch (a.world) {
     case 2: return launch_u<2>(a, grid, inv_w, s);
     case 4: return launch_u<4>(a, grid, inv_w, s);
@@ -830,35 +812,21 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
     case 16: return launch_u<16>(a, grid, inv_w, s);
     default: break;
   }
-  if (a.tree && a.world != 1) {  // a tree over one worker is the chain
-    if (a.world != 32 && a.world != 64) return hipErrorInvalidValue;
+  if (a.world != 32 && a.world != 64) return hipErrorInvalidValue;
 #define CARAMEL_TREE(BF, P) \
   hipLaunchKernelGGL((k_ring_reduce_tree_any<BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
-    if (a.bf16) {
-      if (a.policy != kPlain) CARAMEL_TREE(true, kStream); else CARAMEL_TREE(true, kPlain);
-    } else {
-      if (a.policy != kPlain) CARAMEL_TREE(false, kStream); else CARAMEL_TREE(false, kPlain);
-    }
-#undef CARAMEL_TREE
-    return hipGetLastError();
+  if (a.bf16) {
+    if (a.policy != kPlain) CARAMEL_TREE(true, kStream); else CARAMEL_TREE(true, kPlain);
+  } else {
+    if (a.policy != kPlain) CARAMEL_TREE(false, kStream); else CARAMEL_TREE(false, kPlain);
   }
-#define CARAMEL_ANY(BF, P) \
-  hipLaunchKernelGGL((k_ring_reduce_any<BF, P, 4>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
-#define CARAMEL_ANY2(BF) \
-  do { \
-    if (a.policy == kThrough) CARAMEL_ANY(BF, kThrough); \
-    else if (a.policy == kStream) CARAMEL_ANY(BF, kStream); \
-    else CARAMEL_ANY(BF, kPlain); \
-  } while (0)
-  if (a.bf16) CARAMEL_ANY2(true); else CARAMEL_ANY2(false);
-#undef CARAMEL_ANY2
-#undef CARAMEL_ANY
+#undef CARAMEL_TREE
   return hipGetLastError();
 }
 
-// the kernel for any world size does; the ones specialised for 2, 4, 8 and 16 workers do not
-bool reduce_handles_split_tiles(uint32_t world) {
-  return world != 2 && world != 4 && world != 8 && world != 16;
+// the walk does; the kernel for the small tiles of 2, 4, 8 and 16 workers does not
+bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
+  return long_tiles || (world != 2 && world != 4 && world != 8 && world != 16);
 }
 
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {

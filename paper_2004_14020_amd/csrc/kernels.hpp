@@ -26,9 +26,9 @@ struct ReduceArgs {
   uint32_t unroll;    // vectors in flight per lane and worker: 1, 2 or 4 (0 = choose from W)
   uint32_t max_grid;  // 0 = one workgroup per tile
   uint32_t block;     // lanes per workgroup: 256, 512 or 1024
-  uint32_t stream_major;  // 0: a launch over small tiles, fetch all workers at once; 2, 4 or 8: walk the workers one by one with
-                          // (up to) that many vectors per lane; 8 exists for fp32 chains of at most
-                          // 8 workers, everything else gets 4
+  uint32_t stream_major;  // 0: a launch over small tiles, fetch all workers at once; else: walk the
+                          // workers one by one with (up to) that many vectors per lane; 8 exists for
+                          // fp32 chains, everything else gets 4
 };
 
 struct CopyArgs {
@@ -44,9 +44,10 @@ struct CopyArgs {
 
 // Ring reduce-scatter arithmetic + 1/W scaling + all-gather for a range of tiles.
 hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t stream);
-// Whether the kernel that launch_ring_reduce picks for this world size handles tiles that straddle
-// a segment boundary (ReduceTile::split != 0).  The tile tables must hold none otherwise.
-bool reduce_handles_split_tiles(uint32_t world);
+// Whether the kernel that launch_ring_reduce picks for the long (stream_major != 0) or small tiles of
+// this world size handles tiles that straddle segment boundaries (ReduceTile::split != 0).  The tile
+// tables must hold none otherwise.
+bool reduce_handles_split_tiles(uint32_t world, bool long_tiles);
 // Segmented gather (pack) or scatter (unpack) driven by the copy-tile table.
 hipError_t launch_copy(const CopyArgs& a, hipStream_t stream);
 

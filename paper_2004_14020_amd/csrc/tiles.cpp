@@ -18,22 +18,24 @@ struct Run {
   std::vector<Part> parts;
 };
 
-// The tile [at, at + len) of a run: first worker and split position.  Requires that the tile
-// touches at most two parts (cut_run cuts it that way).
+// The i-th boundary inside a tile.
+uint32_t& boundary(ReduceTile& t, uint32_t i) { return i == 0 ? t.split : t.more[i - 1]; }
+uint32_t boundary(const ReduceTile& t, uint32_t i) { return i == 0 ? t.split : t.more[i - 1]; }
+
+// The tile [at, at + len) of a run: first worker and boundaries (cut_run sees to it that there are
+// at most kMaxSplits of them).
 ReduceTile make_tile(const Run& r, uint64_t at, uint64_t len, uint64_t vec_elems) {
   ReduceTile t{};
   t.row = r.row;
   t.vec_off = uint32_t((r.row_elem + at) / vec_elems);
   t.n_elems = uint32_t(len);
   uint64_t part_begin = 0;
+  uint32_t inside = 0;
   for (const Part& pt : r.parts) {
-    if (at < part_begin + pt.n) {
-      t.first = pt.first;
-      const uint64_t in_part = part_begin + pt.n - at;  // elements of the tile inside this part
-      t.split = in_part < len ? uint32_t(in_part) : 0;
-      break;
-    }
-    part_begin += pt.n;
+    const uint64_t part_end = part_begin + pt.n;
+    if (part_begin <= at && at < part_end) t.first = pt.first;
+    if (part_begin > at && part_begin < at + len) boundary(t, inside++) = uint32_t(part_begin - at);
+    part_begin = part_end;
   }
   return t;
 }
@@ -41,23 +43,23 @@ ReduceTile make_tile(const Run& r, uint64_t at, uint64_t len, uint64_t vec_elems
 // Cut a run into tiles of `tile_elems`.  `phase_elems` is the position of the run's start
 // inside a tile-sized block of memory (0 if unknown or not to be used): the first tile is
 // shortened so that every later tile starts on a multiple of the tile size in memory.  A tile
-// ends early at the second part boundary it would contain (or, without split tiles, at the
-// first).  `phases` receives for every tile the position of its start inside such a block.
+// ends early at the part boundary that it would contain in excess of `max_splits`.  `phases`
+// receives for every tile the position of its start inside such a block.
 void cut_run(std::vector<ReduceTile>& out, const Run& r, uint64_t vec_elems, uint64_t tile_elems,
-             uint64_t phase_elems, bool split_tiles, uint32_t world, std::vector<uint64_t>& phases) {
+             uint64_t phase_elems, uint32_t max_splits, uint32_t world, std::vector<uint64_t>& phases) {
   std::vector<uint64_t> bounds;  // ends of the parts, relative to the run
   uint64_t acc = 0;
   for (const Part& pt : r.parts) bounds.push_back(acc += pt.n);
   uint64_t phase = phase_elems % tile_elems;
   for (uint64_t at = 0; at < r.n;) {
     uint64_t len = std::min(tile_elems - phase, r.n - at);
-    // the part ends after `at`: the tile may run past the first of them if the sums of the next
-    // part start exactly one worker later (what the kernels assume of a split tile)
+    // the parts end after `at`: the tile may run past the end of one if the sums of the next
+    // part start exactly one worker later (what the kernels assume of a boundary inside a tile)
     const auto lo = std::upper_bound(bounds.begin(), bounds.end(), at);
-    const size_t part = size_t(lo - bounds.begin());
-    const bool next_is_one_later =
-        part + 1 < r.parts.size() && r.parts[part + 1].first == (r.parts[part].first + 1) % world;
-    const size_t allowed = split_tiles && next_is_one_later ? 1 : 0;
+    size_t part = size_t(lo - bounds.begin()), allowed = 0;
+    while (allowed < max_splits && part + 1 < r.parts.size() &&
+           r.parts[part + 1].first == (r.parts[part].first + 1) % world)
+      ++allowed, ++part;
     if (size_t(bounds.end() - lo) > allowed && lo[allowed] < at + len) len = lo[allowed] - at;
     out.push_back(make_tile(r, at, len, vec_elems));
     phases.push_back(phase);
@@ -88,14 +90,14 @@ void split_tail(std::vector<ReduceTile>& tiles, size_t begin, const std::vector<
       ReduceTile q = t;
       q.vec_off = uint32_t(t.vec_off + at / vec_elems);
       q.n_elems = uint32_t(std::min<uint64_t>(len, t.n_elems - at));
-      // where the piece lies relative to the tile's segment boundary
-      if (t.split && at >= t.split) {
-        q.first = (t.first + 1) % world;
-        q.split = 0;
-      } else if (t.split && at + q.n_elems > t.split) {
-        q.split = uint32_t(t.split - at);
-      } else {
-        q.split = 0;
+      // where the piece lies relative to the tile's segment boundaries
+      q.split = 0;
+      for (uint32_t& m : q.more) m = 0;
+      uint32_t inside = 0;
+      for (uint32_t k = 0; k < kMaxSplits && boundary(t, k); ++k) {
+        const uint32_t bd = boundary(t, k);
+        if (bd <= at) q.first = (t.first + k + 1) % world;
+        else if (bd < at + q.n_elems) boundary(q, inside++) = uint32_t(bd - at);
       }
       cut.push_back(q);
     }
@@ -201,6 +203,7 @@ void build_tiles(const HostPlan& p, const TileShape& ts, TileTables& out, const 
     for (int cls = 0; cls < 2; ++cls) {
       const uint64_t tile_elems = uint64_t(cls == kLong ? ts.long_vecs : ts.small_vecs) * ve;
       const bool align = (ts.align_tiles & (cls == kSmall ? 1u : 2u)) != 0;
+      const uint32_t splits = ts.split_tiles ? std::min(cls == kSmall ? ts.small_splits : ts.max_splits, std::min(kMaxSplits, W - 1)) : 0;
       for (uint32_t s = 0; s < p.cfg.num_streams; ++s) {
         const size_t stream_begin = tiles.size();
         std::vector<uint64_t> phases;
@@ -211,7 +214,7 @@ void build_tiles(const HostPlan& p, const TileShape& ts, TileTables& out, const 
           for (const Run& r : runs) {
             if ((r.n * es >= ts.long_run_bytes) != (cls == kLong)) continue;
             cut_run(tiles, r, ve, tile_elems, align ? common_phase(r.row, r.row_elem, tile_elems) : 0,
-                    ts.split_tiles, W, phases);
+                    splits, W, phases);
             ut.elems[cls] += r.n;
           }
           ut.tiles[cls].count = uint32_t(tiles.size()) - ut.tiles[cls].begin;

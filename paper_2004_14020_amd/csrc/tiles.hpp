@@ -11,17 +11,19 @@
 namespace caramel {
 
 // One workgroup's share of the ring reduction: a piece of one row that lies inside one ring
-// segment, or straddles the boundary between two consecutive ones.  Inside a segment the chain of
+// segment, or straddles boundaries between consecutive ones.  Inside a segment the chain of
 // workers is the same for every lane; the sums of the next segment start one worker later.
+constexpr uint32_t kMaxSplits = 4;  // boundaries a tile can hold
 struct ReduceTile {
   uint32_t row;      // pointer row
   uint32_t first;    // worker whose value is read first: (segment + 1) mod W for the ring, else 0
   uint32_t vec_off;  // offset of the piece inside the row, in 16-byte vectors
   uint32_t n_elems;  // elements in the piece; only a piece that ends a tensor may be ragged
-  uint32_t split;    // 0, or the number of elements that belong to the first of two segments (a
+  uint32_t split;    // 0, or the number of elements that belong to the first of several segments (a
                      // multiple of the vector size): the sums of the elements from `split` on
                      // start at worker first + 1 (mod W)
-  uint32_t pad_[3];
+  uint32_t more[kMaxSplits - 1];  // further boundaries likewise, ascending, 0 when there are no more:
+                                  // the sums of the elements from more[i] on start at first + i + 2
 };
 
 // One workgroup's share of pack / unpack: a run of one batch member.
@@ -42,8 +44,8 @@ struct Range {
 // one unit: a whole chunk, a whole member of a batch unit reduced in place, or a batch unit's
 // region of the fused buffer.  It consists of one part per ring segment it crosses.  Runs are
 // cut into tiles along aligned blocks of memory, whatever the segment boundaries; a tile that
-// contains a boundary carries its position (`split`), and where a tile would contain two, it
-// ends at the second.  Long runs are cut into long tiles, for 1024-lane workgroups that walk the
+// contains boundaries carries their positions (`split`, `more`), and where a tile would contain more
+// than `max_splits` of them, it ends at the next.  Long runs are cut into long tiles, for 1024-lane workgroups that walk the
 // replicas one after the other; the rest into small tiles, for 256-lane workgroups that fetch
 // all replicas at once.
 struct TileShape {
@@ -55,11 +57,13 @@ struct TileShape {
   // the run is shortened so that all later ones start on multiples of the tile size in memory
   // (bit 0: small tiles, bit 1: long tiles).
   uint32_t align_tiles = 3;
-  bool split_tiles = false;  // tiles may straddle a segment boundary (set at bind if the kernel handles them)
+  bool split_tiles = false;  // tiles may straddle segment boundaries (set at bind if the kernel handles them)
+  uint32_t max_splits = 1;   // boundaries a long tile may hold then, at most kMaxSplits and world - 1
+  uint32_t small_splits = 1; // ... and a small tile
   // The last `tail_tiles` long tiles of every stream are cut into pieces of `tail_vecs` vectors:
   // when a launch runs out of tiles the workgroups still at work finish at different times, and
   // with short pieces at the end that drain is short.
-  uint32_t tail_tiles = 128;
+  uint32_t tail_tiles = 64;
   uint32_t tail_vecs = 1024;
 };
 
