@@ -805,23 +805,21 @@ void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& 
   //    ResNet-50, 24 workers: 869, 831, 826).
   const bool unrolled = c.world == 2 || c.world == 4 || c.world == 8;
   bd.shape.small_splits = reduce_handles_split_tiles(c.world, false) ? 1 : 0;
-  bd.shape.max_splits = unrolled || !reduce_handles_split_tiles(c.world, p->opt.stream_major != 0) ? 0 : (c.world >= 24 ? 4 : 1);
+  bd.shape.max_splits = !reduce_handles_split_tiles(c.world, p->opt.stream_major != 0) ? 0 : (c.world >= 24 ? 4 : 1);
   bd.shape.split_tiles = p->opt.split_tiles && c.pattern == CARAMEL_PATTERN_RING &&
                          (bd.shape.small_splits || bd.shape.max_splits);
   uint64_t replica_bytes = 0;
   for (uint64_t e : p->host.tensor_elems) replica_bytes += e * p->host.elem_size();
-  //  * halving-doubling with 32 or 64 workers has no kernel that walks the replicas one at a time
-  //    (its partial sums do not fit the registers): small tiles throughout (W = 32: 64.9 -> 69.1 %).
-  const bool tree_any = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && c.world > 16;
-  if (bd.shape.long_run_bytes == 0)
-    bd.shape.long_run_bytes = (replica_bytes < (32u << 20) || tree_any) ? ~uint64_t(0) : 16u << 10;
+  if (bd.shape.long_run_bytes == 0) bd.shape.long_run_bytes = replica_bytes < (32u << 20) ? ~uint64_t(0) : 16u << 10;
   if (bd.shape.long_vecs == 0) {
-    const bool wide = c.dtype == CARAMEL_F32 && c.pattern != CARAMEL_PATTERN_HALVING_DOUBLING &&
-                      p->opt.stream_major >= 8 && p->opt.block == 1024 &&
-                      replica_bytes >= (uint64_t(unrolled ? 64 : 192) << 20);
-    // the bf16 tree keeps two vectors per lane: tiles of one pass (a second pass of a workgroup
-    // waits for the stores of the first; Transformer shapes 65.4 -> 66.5 %)
-    const bool narrow = c.dtype == CARAMEL_BF16 && c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
+    // The tree holds eight vectors with 2 and 4 workers only (VGG-16, 4 workers: 713 -> 704 us; 8
+    // workers, with sums in LDS: 1408 -> 1430).
+    const bool tree = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
+    const bool wide = c.dtype == CARAMEL_F32 && !(tree && c.world > 4) && p->opt.stream_major >= 8 &&
+                      p->opt.block == 1024 && replica_bytes >= (uint64_t(unrolled ? 64 : 192) << 20);
+    // the bf16 tree of 32 and 64 workers keeps two vectors per lane: tiles of one pass (a second pass
+    // of a workgroup waits for the stores of the first)
+    const bool narrow = c.dtype == CARAMEL_BF16 && tree && c.world >= 32;
     bd.shape.long_vecs = wide ? 8192 : (narrow ? 2048 : 4096);
   }
   bd.rows = std::move(rows);

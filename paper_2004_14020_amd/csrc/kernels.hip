@@ -1,17 +1,18 @@
 // gfx950 kernels of the aggregation path.  Everything here is bandwidth work: 128-bit
 // coalesced loads and stores, no matrix cores.
 //
-//  k_walk, k_ring_reduce, k_ring_reduce_smt, k_ring_reduce_tree_any
+//  k_walk, k_tree_walk, k_ring_reduce, k_ring_reduce_tree_any
 //                  ring reduce-scatter arithmetic, 1/W scaling and all-gather (paper
 //                  sections 2 and 4.4: partial sums travel round the ring and are added to
 //                  at each worker; the owner's result is then copied to every worker).
 //                  A workgroup handles one tile: long tiles one replica after the other (chains:
-//                  k_walk, trees: k_ring_reduce_smt), small ones with all replicas at once.
+//                  k_walk, trees: k_tree_walk), small ones with all replicas at once.
 //  k_copy          pack / unpack of batched parameters (section 4.2) through an offset table,
 //                  one workgroup per run of at most 16 KiB.
 #include "kernels.hpp"
 
 #include <type_traits>
+#include <utility>
 
 namespace caramel {
 namespace {
@@ -233,133 +234,6 @@ k_ring_reduce(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__
   }
 }
 
-// One stream-major pass over U vectors of this lane (B apart, starting at v): the chain is walked
-// one worker at a time, with the loads of the next D - 1 workers in flight while the current
-// worker's values are added.  (D = 2 everywhere: looking further ahead for short tiles, which
-// have fewer vectors per lane, measured no faster.)
-// RAGGED: the last of the U vectors may lie at or beyond nvec; such a lane reads the tile's last
-// vector instead (no divergence among the loads) and stores nothing for it.
-// TREE: the values are added as the balanced pairwise tree of the halving-doubling order instead of
-// a chain: worker k's value is merged with the open partial sums the way a binary counter carries
-// (one level per trailing one bit of k), which needs log2(W) partial sums per vector.
-template <int W, int U, int D, bool BF16, int P, bool RAGGED, bool TREE = false>
-__device__ __forceinline__ void sm_walk(const gvec_ptr (&p)[W], uint32_t v, uint32_t B, uint32_t nvec, float inv_w) {
-  static_assert(D >= 2 && D <= W, "look-ahead between 2 and W workers");
-  static_assert(!TREE || (W & (W - 1)) == 0, "the tree needs a power of two");
-  constexpr int LEVELS = W >= 16 ? 4 : (W >= 8 ? 3 : (W >= 4 ? 2 : 1));
-  u32x4 buf[D][U];
-  Chain<BF16> acc[U];
-  Chain<BF16> lvl[TREE ? LEVELS : 1][U];
-  const bool last_ok = !RAGGED || v + (U - 1) * B < nvec;
-  auto off = [&](int u) -> uint32_t {
-    if (RAGGED && u == U - 1) return (last_ok ? v + (U - 1) * B : nvec - 1) * 16u;
-    return (v + u * B) * 16u;
-  };
-#pragma unroll
-  for (int k = 0; k < D - 1; ++k)
-#pragma unroll
-    for (int u = 0; u < U; ++u) buf[k][u] = ld<P>(at(p[k], off(u)));
-#pragma unroll
-  for (int k = 0; k < W; ++k) {
-    if (k + D - 1 < W) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) buf[(k + D - 1) % D][u] = ld<P>(at(p[k + D - 1], off(u)));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if constexpr (!TREE) {
-        if (k == 0) acc[u].start(buf[k % D][u]);
-        else acc[u].add(buf[k % D][u]);
-      } else {
-        acc[u].start(buf[k % D][u]);
-        int j = 0;
-#pragma unroll
-        for (int m = k; m & 1; m >>= 1) {
-          lvl[j][u].merge(acc[u]);  // the earlier partial sum + the later one
-          acc[u] = lvl[j][u];
-          ++j;
-        }
-        if (k + 1 < W) lvl[j][u] = acc[u];
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  u32x4 y[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) y[u] = acc[u].finish(inv_w);
-  constexpr int SURE = RAGGED ? U - 1 : U;  // vectors that are stored by every lane
-#pragma unroll
-  for (int k = 0; k < W; ++k)
-#pragma unroll
-    for (int u = 0; u < SURE; ++u) st<P>(p[k], off(u), y[u]);
-  if constexpr (RAGGED) {
-    if (last_ok) {
-#pragma unroll
-      for (int k = 0; k < W; ++k) st<P>(p[k], off(U - 1), y[U - 1]);
-    }
-  }
-}
-
-// Stream-major kernel for the halving-doubling order (W a power of two up to 16): the same walk,
-// one replica after the other, with the values added as the balanced tree.  The tree does not
-// depend on the segment, so the workers are read in the order 0 .. W-1.
-template <int W, int U, bool BF16, int P>
-__global__ void __launch_bounds__(kMaxBlock)
-k_ring_reduce_smt(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
-                  uint32_t count, float inv_w) {
-  constexpr uint32_t VE = BF16 ? 8 : 4;
-  for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
-    const ReduceTile tl = tiles[begin + ti];
-    gvec_ptr p[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) p[k] = reinterpret_cast<gvec_ptr>(rows[size_t(tl.row) * W + k]) + tl.vec_off;
-    const uint32_t nvec = tl.n_elems / VE;
-    const uint32_t B = blockDim.x;
-    const uint32_t whole = nvec / (U * B) * (U * B);  // the same for all lanes
-    uint32_t v = threadIdx.x;
-#pragma unroll 1
-    // (the walk with a guarded last row, although every row is whole here: the compiler keeps
-    // fewer values live in that form and does not spill)
-    for (; v < whole; v += U * B) sm_walk<W, U, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
-    const uint32_t rows_left = (nvec - whole + B - 1) / B;
-    if (rows_left == 1) {
-      if (v < nvec) {
-        u32x4 x[W];
-#pragma unroll
-        for (int k = 0; k < W; ++k) x[k] = ld<P>(at(p[k], v * 16u));
-        __builtin_amdgcn_sched_barrier(0);
-        const u32x4 y = combine<W, BF16, true>(x, inv_w);
-#pragma unroll
-        for (int k = 0; k < W; ++k) st<P>(p[k], v * 16u, y);
-      }
-    }
-    if (rows_left == 2) sm_walk<W, 2, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
-    if constexpr (U >= 4) {
-      if (rows_left == 3) sm_walk<W, 3, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
-      if (rows_left == 4) sm_walk<W, 4, 2, BF16, P, true, true>(p, v, B, nvec, inv_w);
-    }
-    const uint32_t rem = tl.n_elems - nvec * VE;
-    if (threadIdx.x < rem) {
-      const uint32_t e = nvec * VE + threadIdx.x;
-      float val[W];
-      if constexpr (BF16) {
-#pragma unroll
-        for (int k = 0; k < W; ++k) val[k] = widen(reinterpret_cast<gu16_ptr>(p[k])[e]);
-        const uint16_t y = uint16_t(bf16_rne(combine_scalar<W, true>(val, inv_w)));
-#pragma unroll
-        for (int k = 0; k < W; ++k) reinterpret_cast<gu16_ptr>(p[k])[e] = y;
-      } else {
-#pragma unroll
-        for (int k = 0; k < W; ++k) val[k] = reinterpret_cast<gf32_ptr>(p[k])[e];
-        const float y = combine_scalar<W, true>(val, inv_w);
-#pragma unroll
-        for (int k = 0; k < W; ++k) reinterpret_cast<gf32_ptr>(p[k])[e] = y;
-      }
-    }
-  }
-}
-
 // Chain orders, one replica after the other (long tiles of any W up to 64, and the small tiles of the
 // world sizes without a kernel of their own).
 //
@@ -535,6 +409,7 @@ __global__ void __launch_bounds__(kMaxBlock)
 k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
        uint32_t workers, uint32_t cap, float inv_w) {
   constexpr uint32_t VE = BF16 ? 8 : 4;
+  constexpr bool kSplits = CW == 0 || CW >= 16;  // (2, 4 and 8 workers: no tile holds a boundary)
   const uint32_t W = CW ? uint32_t(CW) : workers;
   for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
     const ReduceTile tl = tiles[begin + ti];
@@ -544,7 +419,7 @@ k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, 
     const uint64_t start = uint64_t(tl.vec_off) * 16;
     const Splits splits(tl, 16 / VE);
     const uint32_t lane = threadIdx.x % 64;
-    const uint64_t mine = CW == 0 || tl.split ? row[lane < W ? lane : W - 1] + start : 0;
+    const uint64_t mine = CW == 0 || (kSplits && tl.split) ? row[lane < W ? lane : W - 1] + start : 0;
     const uint32_t total_rows = (nvec + B - 1) / B;
     for (uint32_t done = 0; done < total_rows;) {
       const uint32_t left = total_rows - done;
@@ -564,8 +439,12 @@ k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, 
         }
         if (n == 1) walk.column(off);
       };
-      if (tl.split) go(std::true_type{});
-      else go(std::false_type{});
+      if constexpr (kSplits) {
+        if (tl.split) go(std::true_type{});
+        else go(std::false_type{});
+      } else {
+        go(std::false_type{});
+      }
       done += n;
     }
     // a run that ends a tensor may stop inside a vector: finish it element by element
@@ -598,90 +477,241 @@ k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, 
   }
 }
 
-// Balanced pairwise tree (halving-doubling order) for W = 32 or 64.  The workers are taken eight
-// at a time: their eight vectors are added as a three-level tree, and the partial sums of the
-// blocks are merged the way a binary counter carries (block j closes as many levels as j + 1 has
-// trailing zeros), which is the same tree  ((x0+x1)+(x2+x3)) + ...  up to its root.
+// Halving-doubling order, one vector per lane, W = 32 or 64: the workers are taken eight at a time:
+// their eight vectors are added as a three-level tree, and the partial sums of the blocks are merged
+// the way a binary counter carries (block j closes as many levels as j + 1 has trailing zeros), which
+// is the same tree  ((x0+x1)+(x2+x3)) + ...  up to its root.
+template <bool BF16, int P>
+__device__ __forceinline__ void tree_column(const uint64_t* __restrict__ row, uint32_t vec_off, uint32_t W, uint32_t v,
+                                            float inv_w) {
+  constexpr int kBlk = 8;       // workers per block
+  constexpr int kMaxBlocks = 8;  // W <= 64
+  const uint32_t n_blocks = W / kBlk;
+  Chain<BF16> part[4];  // open partial sums of 8, 16, 32 workers (and the root of 64)
+  u32x4 y = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int j = 0; j < kMaxBlocks; ++j) {
+    if (uint32_t(j) < n_blocks) {
+      u32x4 x[kBlk];
+#pragma unroll
+      for (int i = 0; i < kBlk; ++i)
+        x[i] = ld<P>(at(reinterpret_cast<gvec_ptr>(row[j * kBlk + i]) + vec_off, v * 16u));
+      __builtin_amdgcn_sched_barrier(0);
+      Chain<BF16> t[kBlk];
+#pragma unroll
+      for (int i = 0; i < kBlk; ++i) t[i].start(x[i]);
+#pragma unroll
+      for (int s = 1; s < kBlk; s *= 2)
+#pragma unroll
+        for (int i = 0; i + s < kBlk; i += 2 * s) t[i].merge(t[i + s]);
+      // carry: j + 1 = ...1000 closes one level per trailing zero
+      int lvl = 0;
+#pragma unroll
+      for (int m = j + 1; (m & 1) == 0; m >>= 1) {
+        part[lvl].merge(t[0]);
+        t[0] = part[lvl];
+        ++lvl;
+      }
+      part[lvl] = t[0];
+      if (uint32_t(j) + 1 == n_blocks) y = t[0].finish(inv_w);
+    }
+  }
+  for (uint32_t k = 0; k < W; ++k) st<P>(reinterpret_cast<gvec_ptr>(row[k]) + vec_off, v * 16u, y);
+}
+
+// The same tree on one element (the ragged end of a tensor), any power of two.
+template <bool BF16>
+__device__ __forceinline__ void tree_element(const uint64_t* __restrict__ row, size_t e, uint32_t W, float inv_w) {
+  float part[7];
+  float y = 0.f;
+  for (uint32_t k0 = 0; k0 < W; k0 += 8) {
+    float x[8];
+#pragma unroll
+    for (uint32_t i = 0; i < 8; ++i)
+      if (k0 + i < W) {
+        if constexpr (BF16) x[i] = widen(reinterpret_cast<gu16_ptr>(row[k0 + i])[e]);
+        else x[i] = reinterpret_cast<gf32_ptr>(row[k0 + i])[e];
+      }
+#pragma unroll
+    for (uint32_t i = 0; i < 8; i += 2)
+      if (k0 + i < W) {
+        y = x[i] + x[i + 1];
+        bool open = true;
+#pragma unroll
+        for (int l = 1; l < 7; ++l) {
+          const bool carry = open && (((k0 + i) >> l) & 1);
+          y = carry ? part[l] + y : y;
+          if (open && !carry) part[l] = y;
+          open = carry;
+        }
+      }
+  }
+  y *= inv_w;
+  if constexpr (BF16) {
+    const uint16_t o = uint16_t(bf16_rne(y));
+    for (uint32_t k = 0; k < W; ++k) reinterpret_cast<gu16_ptr>(row[k])[e] = o;
+  } else {
+    for (uint32_t k = 0; k < W; ++k) reinterpret_cast<gf32_ptr>(row[k])[e] = y;
+  }
+}
+
+// Small tiles of W = 32 or 64.
 template <bool BF16, int P>
 __global__ void __launch_bounds__(kMaxBlock)
 k_ring_reduce_tree_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
                        uint32_t count, uint32_t W, float inv_w) {
   constexpr uint32_t VE = BF16 ? 8 : 4;
-  constexpr int kBlk = 8;       // workers per block
-  constexpr int kMaxBlocks = 8;  // W <= 64
   for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
     const ReduceTile tl = tiles[begin + ti];
     const uint64_t* row = rows + size_t(tl.row) * W;
     const uint32_t nvec = tl.n_elems / VE;
-    const uint32_t n_blocks = W / kBlk;
-    for (uint32_t v = threadIdx.x; v < nvec; v += blockDim.x) {
-      Chain<BF16> part[4];  // open partial sums of 8, 16, 32 workers (and the root of 64)
-      u32x4 y = {0u, 0u, 0u, 0u};
+    for (uint32_t v = threadIdx.x; v < nvec; v += blockDim.x) tree_column<BF16, P>(row, tl.vec_off, W, v, inv_w);
+    const uint32_t rem = tl.n_elems - nvec * VE;
+    if (threadIdx.x < rem)
+      tree_element<BF16>(row, size_t(tl.vec_off) * VE + nvec * VE + threadIdx.x, W, inv_w);
+  }
+}
+
+// Long tiles in the halving-doubling order: the walk of k_walk, replica by replica in bursts, with the
+// values added as the balanced tree.  The tree does not depend on the segment, so the workers are read
+// in the order 0 .. W-1, two at a time: their sum is merged with the open partial sums the way a binary
+// counter carries, which takes log2(W) - 1 partial sums per vector.
+//
+// Bound: HBM, and how many vectors per lane (bytes per burst) there is room for.  A pair's two bursts
+// are issued at once, into two buffers of N vectors; a third buffer, so that the next worker's burst
+// flies while a pair is added, measured no faster (VGG-16, 8 workers fp32: 1442 us with, 1408 without;
+// ResNet-v2-152, 16 workers: 1239 / 1235).  The partial sums of the highest levels, which change least
+// often, lie in LDS where the registers do not hold them all (kLds levels, at most 128 KiB, each lane
+// its own slots, so nothing has to be waited for).  That is room for N = 4 (64 KiB per burst) with fp32
+// and, up to 16 workers, with bf16, whose sums are twice as large.  With 36 bytes per lane spilled,
+// global loads and two vectors for bf16 before: ResNet-v2-152, 16 workers 1301 -> 1235 us, Transformer
+// bf16, 8 workers 2049 -> 1724, ResNet-50, 32 workers fp32 (small tiles only) 1306 -> 1080.
+template <int W, bool BF16>
+struct TreeShape {
+  static constexpr int kLevels = W >= 64 ? 5 : (W >= 32 ? 4 : (W >= 16 ? 3 : (W >= 8 ? 2 : (W >= 4 ? 1 : 0))));
+  static constexpr int N = BF16 ? (W >= 32 ? 2 : 4) : (W <= 4 ? 8 : 4);
+  static constexpr int kLds = W >= 32 ? 2 : (BF16 && W == 16 ? 1 : 0);
+  static constexpr int kSlots = kLds * N * (BF16 ? 2 : 1);  // 16-byte slots per lane
+};
+
+// f(0), f(1), ... with each index a constant (a loop pragma gives up on 64 workers)
+template <int... I, typename F>
+__device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+template <int W, bool BF16, int P>
+__global__ void __launch_bounds__(kMaxBlock)
+k_tree_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
+            uint32_t cap, float inv_w) {
+  using S = TreeShape<W, BF16>;
+  constexpr uint32_t VE = BF16 ? 8 : 4;
+  constexpr int kLoad = P == kPlain ? 0 : 2 /* nt */;
+  constexpr int kStore = P == kPlain ? 0 : (P == kThrough ? 18 /* sc1 nt */ : 2);
+  __shared__ f32x4 high[S::kSlots ? S::kSlots * kMaxBlock : 1];
+  for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
+    const ReduceTile tl = tiles[begin + ti];
+    const uint64_t* row = rows + size_t(tl.row) * W;
+    const uint32_t nvec = tl.n_elems / VE;
+    const uint32_t B = blockDim.x;
+    const uint32_t lane = threadIdx.x % 64;
+    const uint64_t mine = row[lane < W ? lane : W - 1] + uint64_t(tl.vec_off) * 16;  // kept by lane w for replica w
+    const uint32_t total_rows = (nvec + B - 1) / B;
+    for (uint32_t done = 0; done < total_rows;) {
+      const uint32_t left = total_rows - done;
+      const uint32_t n = left < cap ? left : cap;  // rows of this pass
+      const uint32_t off = (done * B + threadIdx.x) * 16, stride = B * 16;
+      const uint32_t end = (done + n) * B < nvec ? (done + n) * B * 16 : nvec * 16;
+      auto res = [&](int w) {
+        const uint64_t base = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(mine >> 32), w))) << 32 |
+                              uint32_t(__builtin_amdgcn_readlane(int(mine), w));
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), 0, int(end), kRawBuffer);
+      };
+      auto pass = [&](auto n_tag) {
+        constexpr int N = decltype(n_tag)::value;
+        u32x4 buf[2][N];
+        Chain<BF16> low[S::kLevels ? S::kLevels : 1][N];  // (the levels that lie in LDS stay unused here)
+        u32x4 y[N];
+        auto load = [&](int k) {
+          const __amdgpu_buffer_rsrc_t r = res(k);
 #pragma unroll
-      for (int j = 0; j < kMaxBlocks; ++j) {
-        if (uint32_t(j) < n_blocks) {
-          u32x4 x[kBlk];
-#pragma unroll
-          for (int i = 0; i < kBlk; ++i)
-            x[i] = ld<P>(at(reinterpret_cast<gvec_ptr>(row[j * kBlk + i]) + tl.vec_off, v * 16u));
-          __builtin_amdgcn_sched_barrier(0);
-          Chain<BF16> t[kBlk];
-#pragma unroll
-          for (int i = 0; i < kBlk; ++i) t[i].start(x[i]);
-#pragma unroll
-          for (int s = 1; s < kBlk; s *= 2)
-#pragma unroll
-            for (int i = 0; i + s < kBlk; i += 2 * s) t[i].merge(t[i + s]);
-          // carry: j + 1 = ...1000 closes one level per trailing zero
-          int lvl = 0;
-#pragma unroll
-          for (int m = j + 1; (m & 1) == 0; m >>= 1) {
-            part[lvl].merge(t[0]);
-            t[0] = part[lvl];
-            ++lvl;
+          for (int u = 0; u < N; ++u)
+            buf[k % 2][u] = __builtin_amdgcn_raw_buffer_load_b128(r, int(off + u * stride), 0, kLoad);
+        };
+        auto slot = [&](int level, int u, int half) -> f32x4& {
+          constexpr int kHalves = BF16 ? 2 : 1;
+          return high[(((level - (S::kLevels - S::kLds)) * N + u) * kHalves + half) * B + threadIdx.x];
+        };
+        auto get = [&](int level, int u) {
+          if (level < S::kLevels - S::kLds) return low[level][u];
+          Chain<BF16> c;
+          c.a = slot(level, u, 0);
+          if constexpr (BF16) c.b = slot(level, u, 1);
+          return c;
+        };
+        auto put = [&](int level, int u, const Chain<BF16>& c) {
+          if (level < S::kLevels - S::kLds) {
+            low[level][u] = c;
+          } else {
+            slot(level, u, 0) = c.a;
+            if constexpr (BF16) slot(level, u, 1) = c.b;
           }
-          part[lvl] = t[0];
-          if (uint32_t(j) + 1 == n_blocks) y = t[0].finish(inv_w);
+        };
+        for_each_index(std::make_integer_sequence<int, W / 2>{}, [&](auto pair) {
+          constexpr int k = 2 * decltype(pair)::value + 1;
+          load(k - 1);
+          load(k);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            Chain<BF16> t;
+            t.start(buf[0][u]);
+            t.add(buf[1][u]);
+            constexpr int kClosed = __builtin_ctz(~(k >> 1));  // levels that this pair closes
+#pragma unroll
+            for (int level = 0; level < kClosed; ++level) {
+              Chain<BF16> o = get(level, u);  // the earlier partial sum + the later one
+              o.merge(t);
+              t = o;
+            }
+            t.pin();
+            if (k + 1 < W) put(kClosed, u, t);
+            else y[u] = t.finish(inv_w);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        });
+#pragma unroll(W < 16 ? W : 16)
+        for (int k = 0; k < W; ++k) {
+          const __amdgpu_buffer_rsrc_t r = res(k);
+#pragma unroll
+          for (int u = 0; u < N; ++u) __builtin_amdgcn_raw_buffer_store_b128(y[u], r, int(off + u * stride), 0, kStore);
+        }
+      };
+      if constexpr (S::N >= 8) {
+        if (n > 4) pass(std::integral_constant<int, 8>{});
+      }
+      if constexpr (S::N >= 4) {
+        if (n > 2 && n <= 4) pass(std::integral_constant<int, 4>{});
+      }
+      if (n == 2) pass(std::integral_constant<int, 2>{});
+      if (n == 1) {
+        if constexpr (W >= 32) {
+          if (off < end) tree_column<BF16, P>(row, tl.vec_off, W, off / 16, inv_w);
+        } else {
+          u32x4 x[W];
+#pragma unroll
+          for (int k = 0; k < W; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b128(res(k), int(off), 0, kLoad);
+          __builtin_amdgcn_sched_barrier(0);
+          const u32x4 y = combine<W, BF16, true>(x, inv_w);
+#pragma unroll
+          for (int k = 0; k < W; ++k) __builtin_amdgcn_raw_buffer_store_b128(y, res(k), int(off), 0, kStore);
         }
       }
-      for (uint32_t k = 0; k < W; ++k) st<P>(reinterpret_cast<gvec_ptr>(row[k]) + tl.vec_off, v * 16u, y);
+      done += n;
     }
     const uint32_t rem = tl.n_elems - nvec * VE;
-    if (threadIdx.x < rem) {
-      // ragged end of a tensor, one element per lane: the same tree on scalars
-      const size_t e = size_t(tl.vec_off) * VE + nvec * VE + threadIdx.x;
-      float part[4];
-      float y = 0.f;
-#pragma unroll
-      for (int j = 0; j < kMaxBlocks; ++j) {
-        if (uint32_t(j) < n_blocks) {
-          float t[kBlk];
-#pragma unroll
-          for (int i = 0; i < kBlk; ++i) {
-            if constexpr (BF16) t[i] = widen(reinterpret_cast<gu16_ptr>(row[j * kBlk + i])[e]);
-            else t[i] = reinterpret_cast<gf32_ptr>(row[j * kBlk + i])[e];
-          }
-#pragma unroll
-          for (int s = 1; s < kBlk; s *= 2)
-#pragma unroll
-            for (int i = 0; i + s < kBlk; i += 2 * s) t[i] = t[i] + t[i + s];
-          int lvl = 0;
-#pragma unroll
-          for (int m = j + 1; (m & 1) == 0; m >>= 1) {
-            t[0] = part[lvl] + t[0];
-            ++lvl;
-          }
-          part[lvl] = t[0];
-          if (uint32_t(j) + 1 == n_blocks) y = t[0] * inv_w;
-        }
-      }
-      if constexpr (BF16) {
-        const uint16_t o = uint16_t(bf16_rne(y));
-        for (uint32_t k = 0; k < W; ++k) reinterpret_cast<gu16_ptr>(row[k])[e] = o;
-      } else {
-        for (uint32_t k = 0; k < W; ++k) reinterpret_cast<gf32_ptr>(row[k])[e] = y;
-      }
-    }
+    if (threadIdx.x < rem)
+      tree_element<BF16>(row, size_t(tl.vec_off) * VE + nvec * VE + threadIdx.x, W, inv_w);
   }
 }
 
@@ -728,33 +758,26 @@ hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) 
   return hipGetLastError();
 }
 
-// fp32: four vectors per lane; bf16 (twice the partial sums per vector): two, i.e. a long tile in
-// two passes
 template <int W>
-hipError_t launch_smt(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-#define CARAMEL_SMT(U, BF, P) \
-  hipLaunchKernelGGL((k_ring_reduce_smt<W, U, BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
-#define CARAMEL_SMT3(U, BF) \
+hipError_t launch_tree(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
+#define CARAMEL_TREE(BF, P) \
+  hipLaunchKernelGGL((k_tree_walk<W, BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, \
+                     a.stream_major < uint32_t(TreeShape<W, BF>::N) ? a.stream_major : uint32_t(TreeShape<W, BF>::N), inv_w)
+#define CARAMEL_TREE3(BF) \
   do { \
-    if (a.policy == kThrough) CARAMEL_SMT(U, BF, kThrough); \
-    else if (a.policy == kStream) CARAMEL_SMT(U, BF, kStream); \
-    else CARAMEL_SMT(U, BF, kPlain); \
+    if (a.policy == kThrough) CARAMEL_TREE(BF, kThrough); \
+    else if (a.policy == kStream) CARAMEL_TREE(BF, kStream); \
+    else CARAMEL_TREE(BF, kPlain); \
   } while (0)
-  if (a.bf16) {
-    CARAMEL_SMT3(2, true);
-  } else if (a.stream_major >= 4) {
-    CARAMEL_SMT3(4, false);
-  } else {
-    CARAMEL_SMT3(2, false);
-  }
-#undef CARAMEL_SMT3
-#undef CARAMEL_SMT
+  if (a.bf16) CARAMEL_TREE3(true); else CARAMEL_TREE3(false);
+#undef CARAMEL_TREE3
+#undef CARAMEL_TREE
   return hipGetLastError();
 }
 
 template <int W>
 hipError_t launch_u(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-  if (a.stream_major && a.tree) return launch_smt<W>(a, grid, inv_w, s);
+  if (a.stream_major && a.tree) return launch_tree<W>(a, grid, inv_w, s);
   // W * U vectors per lane must fit the register budget of a 1024-lane workgroup
   constexpr uint32_t kMaxU = W <= 4 ? 4 : (W <= 8 ? 2 : 1);
   uint32_t u = a.unroll ? a.unroll : kMaxU;
@@ -813,6 +836,7 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
     default: break;
   }
   if (a.world != 32 && a.world != 64) return hipErrorInvalidValue;
+  if (a.stream_major) return a.world == 32 ? launch_tree<32>(a, grid, inv_w, s) : launch_tree<64>(a, grid, inv_w, s);
 #define CARAMEL_TREE(BF, P) \
   hipLaunchKernelGGL((k_ring_reduce_tree_any<BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
   if (a.bf16) {
@@ -824,9 +848,10 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// the walk does; the kernel for the small tiles of 2, 4, 8 and 16 workers does not
+// the rolled walk does; the unrolled one for 2, 4 and 8 workers and the kernel for the small tiles of
+// 2, 4, 8 and 16 do not
 bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
-  return long_tiles || (world != 2 && world != 4 && world != 8 && world != 16);
+  return world != 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
 }
 
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
