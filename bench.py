@@ -203,7 +203,7 @@ def main() -> int:
     alg_bytes = wl.algorithmic_bytes()
     gbs = alg_bytes / (ms_per_step * 1e-3) / 1e9
 
-    # Dominant kernel: k_ring_reduce_sm, the stream-major ring reduction over long tiles (in the
+    # Dominant kernel: k_walk, the ring reduction over long tiles (in the
     # default in-place mode the only other kernel is k_ring_reduce over the few short runs).
     #   achieved = algorithmic bytes of its launches (2*W*s per element they cover)
     #              / the sum of their durations, both counted by the library over the timed region
@@ -221,7 +221,7 @@ def main() -> int:
             out["achieved"] = round(per_elem * st["elements"] / (st["total_ms"] * 1e-3) / 1e9, 1)
         return out
 
-    dom_name, dom = ("k_ring_reduce_sm", lng) if lng["elements"] >= sml["elements"] else ("k_ring_reduce", sml)
+    dom_name, dom = ("k_walk", lng) if lng["elements"] >= sml["elements"] else ("k_ring_reduce", sml)
     dom_line = kernel_line(dom) or {}
     span_ms = seq["span_ms"] / max(1, seq["calls"])
     roofline = {"bound": "hbm", "kernel": dom_name, "achieved": dom_line.get("achieved"), "peak": HBM_PEAK_GBS,
