@@ -404,8 +404,12 @@ struct Walk {
 
 // MAXN: most vectors per lane and pass (long tiles: 8 with fp32, 4 with bf16; small ones: 1); `cap`
 // lowers it.
+// A walk over long tiles asks for at most four wavefronts per SIMD, one 1024-lane workgroup per compute
+// unit, which most of them need anyway (65 to 128 VGPRs).  With two workers and bf16 60 would do, and two
+// workgroups then read and write in step: 2 x 33 MiB 27.5 us, 25.8 with one, 2 x 260 MiB 174.3 / 171.0.
+// It also leaves the compiler room between the loads (8 workers bf16, 260 MiB: 714.6 / 703.2).
 template <int CW, bool BF16, int P, int MAXN>
-__global__ void __launch_bounds__(kMaxBlock)
+__global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, MAXN > 1 ? 4 : 8)))
 k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
        uint32_t workers, uint32_t cap, float inv_w) {
   constexpr uint32_t VE = BF16 ? 8 : 4;
@@ -600,8 +604,10 @@ __device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>,
   (f(std::integral_constant<int, I>{}), ...);
 }
 
+// (at most one 1024-lane workgroup per compute unit, like k_walk: 2 x 33 MiB bf16 27.6 -> 25.8 us,
+// 8 x 80 MiB fp32 225.3 -> 223.1)
 template <int W, bool BF16, int P>
-__global__ void __launch_bounds__(kMaxBlock)
+__global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_tree_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
             uint32_t cap, float inv_w) {
   using S = TreeShape<W, BF16>;
