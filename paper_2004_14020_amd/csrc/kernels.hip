@@ -41,6 +41,12 @@ __device__ __forceinline__ u32x4 ld(gvec_ptr p) {
   else return *p;
 }
 template <int P>
+__device__ __forceinline__ void st(gvec_ptr p, u32x4 v) {
+  static_assert(P != kThrough, "needs the form with a base and an offset");
+  if constexpr (P == kStream) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+template <int P>
 __device__ __forceinline__ void st(gvec_ptr base, uint32_t byte_off, u32x4 v) {
   if constexpr (P == kThrough) {
     // C++ has no way to ask for this pair on a 128-bit store; the buffer form takes the policy as an
@@ -48,10 +54,8 @@ __device__ __forceinline__ void st(gvec_ptr base, uint32_t byte_off, u32x4 v) {
     constexpr int kRaw = 0x00027000, kNt = 2, kSc1 = 16;
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, kRaw);
     __builtin_amdgcn_raw_buffer_store_b128(v, r, int(byte_off), 0, kSc1 | kNt);
-  } else if constexpr (P == kStream) {
-    __builtin_nontemporal_store(v, at(base, byte_off));
   } else {
-    *at(base, byte_off) = v;
+    st<P>(at(base, byte_off), v);
   }
 }
 
@@ -740,7 +744,9 @@ k_copy(const CopyTile* __restrict__ tiles, const uint64_t* __restrict__ rows, ui
   const uint32_t nvec = t.n_elems / VE;
   gvec_ptr src = UNPACK ? fp : tp;
   gvec_ptr dst = UNPACK ? tp : fp;
-  for (uint32_t v = lane; v < nvec; v += kCopyBlock) st<P>(dst, v * 16u, ld<P>(src + v));
+  // (source and destination of a vector share one 64-bit lane offset; a 32-bit one for the stores alone
+  // costs two registers and an addition more: small stages 0.6 % slower, 18.03 -> 18.15 us for 4 x 8 MiB)
+  for (uint32_t v = lane; v < nvec; v += kCopyBlock) st<P>(dst + v, ld<P>(src + v));
   // ragged end of a member, and (pack only) the +0.0 padding up to the next member
   CARAMEL_GLOBAL E* se = reinterpret_cast<CARAMEL_GLOBAL E*>(src);
   CARAMEL_GLOBAL E* de = reinterpret_cast<CARAMEL_GLOBAL E*>(dst);

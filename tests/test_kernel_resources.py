@@ -34,3 +34,9 @@ def test_long_walks_run_one_workgroup_per_compute_unit(kernels):
     assert len(walks) > 20
     # 1024 lanes are four wavefronts per SIMD
     assert {n: r["Occupancy [waves/SIMD]"] for n, r in walks.items() if r["Occupancy [waves/SIMD]"] != 4} == {}
+
+
+def test_copies_address_both_sides_with_one_offset(kernels):
+    copies = {n: r["VGPRs"] for n, r in kernels.items() if n.startswith("k_copy<")}
+    # a 128-bit value, a 64-bit offset, the counter and the lane
+    assert len(copies) == 8 and max(copies.values()) <= 10, copies
