@@ -417,7 +417,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
 k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
        uint32_t workers, uint32_t cap, float inv_w) {
   constexpr uint32_t VE = BF16 ? 8 : 4;
-  constexpr bool kSplits = CW == 0 || CW >= 16;  // (2, 4 and 8 workers: no tile holds a boundary)
+  constexpr bool kSplits = CW == 0 || CW >= 16;  // (1, 2, 4 and 8 workers: no tile holds a boundary)
   const uint32_t W = CW ? uint32_t(CW) : workers;
   for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
     const ReduceTile tl = tiles[begin + ti];
@@ -759,7 +759,8 @@ hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) 
 #define CARAMEL_GO(BF, P, TR) \
   hipLaunchKernelGGL((k_ring_reduce<W, U, BF, P, TR>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
 #define CARAMEL_GO2(BF, P) \
-  do { if (a.tree) CARAMEL_GO(BF, P, true); else CARAMEL_GO(BF, P, false); } while (0)
+  do { if (kTree && a.tree) CARAMEL_GO(BF, P, kTree); else CARAMEL_GO(BF, P, false); } while (0)
+  constexpr bool kTree = W > 1;  // a tree over one worker is the chain
   if (a.bf16) {
     if (a.policy != kPlain) CARAMEL_GO2(true, kStream); else CARAMEL_GO2(true, kPlain);
   } else {
@@ -789,7 +790,8 @@ hipError_t launch_tree(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t 
 
 template <int W>
 hipError_t launch_u(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-  if (a.stream_major && a.tree) return launch_tree<W>(a, grid, inv_w, s);
+  if constexpr (W > 1)
+    if (a.stream_major && a.tree) return launch_tree<W>(a, grid, inv_w, s);
   // W * U vectors per lane must fit the register budget of a 1024-lane workgroup
   constexpr uint32_t kMaxU = W <= 4 ? 4 : (W <= 8 ? 2 : 1);
   uint32_t u = a.unroll ? a.unroll : kMaxU;
@@ -808,9 +810,12 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   if (a.max_grid && g > a.max_grid) g = a.max_grid;
   const dim3 grid(g);
   const float inv_w = 1.0f / float(a.world);
-  const bool chain = !a.tree || a.world == 1;  // a tree over one worker is the chain
-  const bool any = !(a.world == 2 || a.world == 4 || a.world == 8 || a.world == 16);
-  if (chain && (a.stream_major || any)) {
+  const bool tree = a.tree && a.world > 1;  // a tree over one worker is the chain
+  // One worker is a plain scaling: small tiles take the kernel that fetches all values at once (4 MiB: 4.3
+  // us, 4.8 with the rolled walk's column; 20 MiB 8.1 / 13.3), long ones the unrolled walk (33 MiB fp32
+  // 14.6 / 17.2, 260 MiB 85.9 / 90.5; all at once 14.1 and 90.6).
+  const bool any = !(a.world == 1 || a.world == 2 || a.world == 4 || a.world == 8 || a.world == 16);
+  if (!tree && (a.stream_major || any)) {
 #define CARAMEL_WALK(CW, BF, P, MAXN) \
   hipLaunchKernelGGL((k_walk<CW, BF, P, MAXN>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, \
                      a.stream_major < MAXN ? (a.stream_major ? a.stream_major : 1u) : uint32_t(MAXN), inv_w)
@@ -824,6 +829,8 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   do { if (a.bf16) CARAMEL_WALK3(CW, true, 4); else CARAMEL_WALK3(CW, false, 8); } while (0)
     if (!a.stream_major) {
       if (a.bf16) CARAMEL_WALK3(0, true, 1); else CARAMEL_WALK3(0, false, 1);
+    } else if (a.world == 1) {
+      CARAMEL_WALK_T(1);
     } else if (a.world == 2) {
       CARAMEL_WALK_T(2);
     } else if (a.world == 4) {
@@ -841,6 +848,7 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
     return hipGetLastError();
   }
   switch (a.world) {
+    case 1: return launch_u<1>(a, grid, inv_w, s);
     case 2: return launch_u<2>(a, grid, inv_w, s);
     case 4: return launch_u<4>(a, grid, inv_w, s);
     case 8: return launch_u<8>(a, grid, inv_w, s);
@@ -861,9 +869,9 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
 }
 
 // the rolled walk does; the unrolled one for 2, 4 and 8 workers and the kernel for the small tiles of
-// 2, 4, 8 and 16 do not
+// 2, 4, 8 and 16 do not (one worker has no boundaries)
 bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
-  return world != 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
+  return world > 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
 }
 
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
