@@ -417,7 +417,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
 k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
        uint32_t workers, uint32_t cap, float inv_w) {
   constexpr uint32_t VE = BF16 ? 8 : 4;
-  constexpr bool kSplits = CW == 0 || CW >= 16;  // (1, 2, 4 and 8 workers: no tile holds a boundary)
+  constexpr bool kSplits = CW == 0 || CW >= 16;  // (up to 4 and 8 workers: no tile holds a boundary)
   const uint32_t W = CW ? uint32_t(CW) : workers;
   for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
     const ReduceTile tl = tiles[begin + ti];
@@ -754,13 +754,17 @@ k_copy(const CopyTile* __restrict__ tiles, const uint64_t* __restrict__ rows, ui
   for (uint32_t e = nvec * VE + lane; e < end; e += kCopyBlock) de[e] = (e < t.n_elems) ? se[e] : E(0);
 }
 
+// a tree over one worker is the chain
+template <int W>
+constexpr bool kTreeWorld = W > 1 && (W & (W - 1)) == 0;
+
 template <int W, int U>
 hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
 #define CARAMEL_GO(BF, P, TR) \
   hipLaunchKernelGGL((k_ring_reduce<W, U, BF, P, TR>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
 #define CARAMEL_GO2(BF, P) \
   do { if (kTree && a.tree) CARAMEL_GO(BF, P, kTree); else CARAMEL_GO(BF, P, false); } while (0)
-  constexpr bool kTree = W > 1;  // a tree over one worker is the chain
+  constexpr bool kTree = kTreeWorld<W>;
   if (a.bf16) {
     if (a.policy != kPlain) CARAMEL_GO2(true, kStream); else CARAMEL_GO2(true, kPlain);
   } else {
@@ -790,7 +794,7 @@ hipError_t launch_tree(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t 
 
 template <int W>
 hipError_t launch_u(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-  if constexpr (W > 1)
+  if constexpr (kTreeWorld<W>)
     if (a.stream_major && a.tree) return launch_tree<W>(a, grid, inv_w, s);
   // W * U vectors per lane must fit the register budget of a 1024-lane workgroup
   constexpr uint32_t kMaxU = W <= 4 ? 4 : (W <= 8 ? 2 : 1);
@@ -814,7 +818,9 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   // One worker is a plain scaling: small tiles take the kernel that fetches all values at once (4 MiB: 4.3
   // us, 4.8 with the rolled walk's column; 20 MiB 8.1 / 13.3), long ones the unrolled walk (33 MiB fp32
   // 14.6 / 17.2, 260 MiB 85.9 / 90.5; all at once 14.1 and 90.6).
-  const bool any = !(a.world == 1 || a.world == 2 || a.world == 4 || a.world == 8 || a.world == 16);
+  // Three workers likewise, without boundaries in tiles: 2 MiB fp32 4.8 us rolled, 4.0; 33 MiB 39.0 / 37.5;
+  // 130 MiB 131.9 / 131.8; but 30 MiB 33.1 / 33.5.
+  const bool any = !(a.world <= 4 || a.world == 8 || a.world == 16);
   if (!tree && (a.stream_major || any)) {
 #define CARAMEL_WALK(CW, BF, P, MAXN) \
   hipLaunchKernelGGL((k_walk<CW, BF, P, MAXN>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, \
@@ -833,6 +839,8 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
       CARAMEL_WALK_T(1);
     } else if (a.world == 2) {
       CARAMEL_WALK_T(2);
+    } else if (a.world == 3) {
+      CARAMEL_WALK_T(3);
     } else if (a.world == 4) {
       CARAMEL_WALK_T(4);
     } else if (a.world == 8) {
@@ -850,6 +858,7 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   switch (a.world) {
     case 1: return launch_u<1>(a, grid, inv_w, s);
     case 2: return launch_u<2>(a, grid, inv_w, s);
+    case 3: return launch_u<3>(a, grid, inv_w, s);
     case 4: return launch_u<4>(a, grid, inv_w, s);
     case 8: return launch_u<8>(a, grid, inv_w, s);
     case 16: return launch_u<16>(a, grid, inv_w, s);
@@ -868,10 +877,10 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// the rolled walk does; the unrolled one for 2, 4 and 8 workers and the kernel for the small tiles of
-// 2, 4, 8 and 16 do not (one worker has no boundaries)
+// the rolled walk does; the unrolled one for up to 4 and for 8 workers and the kernel for the small tiles
+// of these and of 16 do not
 bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
-  return world > 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
+  return world > 4 && world != 8 && (world != 16 || long_tiles);
 }
 
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {

@@ -5,7 +5,7 @@ import oracle
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("W", [1])
+@pytest.mark.parametrize("W", [1, 3])
 @pytest.mark.parametrize("dtype", [oracle.F32, oracle.BF16])
 def test_edges_of_tiles_with_few_workers(W, dtype):
     import paper_2004_14020_amd as cm
