@@ -373,10 +373,10 @@ enum {
    * at the end that drain is short.  Default 64 (a quarter of a tile per compute unit); 0 switches it off.
    * Takes effect at the next caramel_bind. */
   CARAMEL_OPT_TAIL_TILES = 16,
-  /* 1 (default): for world sizes other than 1 to 4 and 8 (ring order), tiles follow aligned blocks of
+  /* 1 (default): for world sizes other than 1, 2, 4 and 8 (ring order), tiles follow aligned blocks of
    * memory across the boundaries between ring segments (small tiles of 16 workers excepted): a tile
    * that contains boundaries is summed in parts, each in its segment's order, and a run is everything
-   * of one unit that is contiguous in a tensor.  0, and always for 1 to 4 and 8 workers: tiles (and
+   * of one unit that is contiguous in a tensor.  0, and always for 1, 2, 4 and 8 workers: tiles (and
    * runs) end at segment boundaries.  Takes effect at the next caramel_bind.  Results do not
    * depend on it. */
   CARAMEL_OPT_SPLIT_TILES = 17

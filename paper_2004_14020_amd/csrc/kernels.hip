@@ -417,7 +417,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
 k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin, uint32_t count,
        uint32_t workers, uint32_t cap, float inv_w) {
   constexpr uint32_t VE = BF16 ? 8 : 4;
-  constexpr bool kSplits = CW == 0 || CW >= 16;  // (up to 4 and 8 workers: no tile holds a boundary)
+  constexpr bool kSplits = CW == 0 || CW == 3 || CW >= 16;  // (1, 2, 4 and 8 workers: no tile holds a boundary)
   const uint32_t W = CW ? uint32_t(CW) : workers;
   for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
     const ReduceTile tl = tiles[begin + ti];
@@ -431,14 +431,17 @@ k_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, 
     const uint32_t total_rows = (nvec + B - 1) / B;
     for (uint32_t done = 0; done < total_rows;) {
       const uint32_t left = total_rows - done;
-      const uint32_t n = left < cap ? left : cap;  // rows of this pass
+      // (three workers: the few tiles with a boundary take two passes; eight vectors of that walk beside the
+      // unrolled one spill)
+      const uint32_t most = CW == 3 && MAXN > 4 && tl.split && cap > 4 ? 4 : cap;
+      const uint32_t n = left < most ? left : most;  // rows of this pass
       const uint32_t off = (done * B + threadIdx.x) * 16;
       // a pass of n rows ends where they do
       const uint32_t end = (done + n) * B < nvec ? (done + n) * B * 16 : nvec * 16;
       auto go = [&](auto split_tag) {
         constexpr bool kSplit = decltype(split_tag)::value;
         const Walk<kSplit ? 0 : CW, BF16, P, kSplit> walk{row, mine, start, W, tl.first, end, splits, inv_w};
-        if constexpr (MAXN >= 8) {
+        if constexpr (MAXN >= 8 && !(kSplit && CW == 3)) {
           if (n > 4) walk.template rows<8>(off, B * 16);
         }
         if constexpr (MAXN >= 4) {
@@ -754,17 +757,13 @@ k_copy(const CopyTile* __restrict__ tiles, const uint64_t* __restrict__ rows, ui
   for (uint32_t e = nvec * VE + lane; e < end; e += kCopyBlock) de[e] = (e < t.n_elems) ? se[e] : E(0);
 }
 
-// a tree over one worker is the chain
-template <int W>
-constexpr bool kTreeWorld = W > 1 && (W & (W - 1)) == 0;
-
 template <int W, int U>
 hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
 #define CARAMEL_GO(BF, P, TR) \
   hipLaunchKernelGGL((k_ring_reduce<W, U, BF, P, TR>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, inv_w)
 #define CARAMEL_GO2(BF, P) \
   do { if (kTree && a.tree) CARAMEL_GO(BF, P, kTree); else CARAMEL_GO(BF, P, false); } while (0)
-  constexpr bool kTree = kTreeWorld<W>;
+  constexpr bool kTree = W > 1;  // a tree over one worker is the chain
   if (a.bf16) {
     if (a.policy != kPlain) CARAMEL_GO2(true, kStream); else CARAMEL_GO2(true, kPlain);
   } else {
@@ -794,7 +793,7 @@ hipError_t launch_tree(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t 
 
 template <int W>
 hipError_t launch_u(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
-  if constexpr (kTreeWorld<W>)
+  if constexpr (W > 1)
     if (a.stream_major && a.tree) return launch_tree<W>(a, grid, inv_w, s);
   // W * U vectors per lane must fit the register budget of a 1024-lane workgroup
   constexpr uint32_t kMaxU = W <= 4 ? 4 : (W <= 8 ? 2 : 1);
@@ -818,9 +817,7 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   // One worker is a plain scaling: small tiles take the kernel that fetches all values at once (4 MiB: 4.3
   // us, 4.8 with the rolled walk's column; 20 MiB 8.1 / 13.3), long ones the unrolled walk (33 MiB fp32
   // 14.6 / 17.2, 260 MiB 85.9 / 90.5; all at once 14.1 and 90.6).
-  // Three workers likewise, without boundaries in tiles: 2 MiB fp32 4.8 us rolled, 4.0; 33 MiB 39.0 / 37.5;
-  // 130 MiB 131.9 / 131.8; but 30 MiB 33.1 / 33.5.
-  const bool any = !(a.world <= 4 || a.world == 8 || a.world == 16);
+  const bool any = !(a.world == 1 || a.world == 2 || a.world == 4 || a.world == 8 || a.world == 16);
   if (!tree && (a.stream_major || any)) {
 #define CARAMEL_WALK(CW, BF, P, MAXN) \
   hipLaunchKernelGGL((k_walk<CW, BF, P, MAXN>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, \
@@ -833,7 +830,11 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   } while (0)
 #define CARAMEL_WALK_T(CW) \
   do { if (a.bf16) CARAMEL_WALK3(CW, true, 4); else CARAMEL_WALK3(CW, false, 8); } while (0)
-    if (!a.stream_major) {
+    // Three workers: 2 MiB fp32 4.9 us with the rolled walk, 4.3; 3 MiB 5.5 / 4.9; 33 MiB 37.5 / 37.2; 260 MiB
+    // equal; but 30 MiB 32.8 / 33.4.
+    if (!a.stream_major && a.world == 3) {
+      if (a.bf16) CARAMEL_WALK3(3, true, 1); else CARAMEL_WALK3(3, false, 1);
+    } else if (!a.stream_major) {
       if (a.bf16) CARAMEL_WALK3(0, true, 1); else CARAMEL_WALK3(0, false, 1);
     } else if (a.world == 1) {
       CARAMEL_WALK_T(1);
@@ -858,7 +859,6 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   switch (a.world) {
     case 1: return launch_u<1>(a, grid, inv_w, s);
     case 2: return launch_u<2>(a, grid, inv_w, s);
-    case 3: return launch_u<3>(a, grid, inv_w, s);
     case 4: return launch_u<4>(a, grid, inv_w, s);
     case 8: return launch_u<8>(a, grid, inv_w, s);
     case 16: return launch_u<16>(a, grid, inv_w, s);
@@ -877,10 +877,10 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// the rolled walk does; the unrolled one for up to 4 and for 8 workers and the kernel for the small tiles
-// of these and of 16 do not
+// the rolled walk does, and that of three workers; the unrolled ones for 1, 2, 4 and 8 workers and the
+// kernel for the small tiles of these and of 16 do not
 bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
-  return world > 4 && world != 8 && (world != 16 || long_tiles);
+  return world > 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
 }
 
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
