@@ -877,12 +877,6 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// the rolled walk does, and that of three workers; the unrolled ones for 1, 2, 4 and 8 workers and the
-// kernel for the small tiles of these and of 16 do not
-bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
-  return world > 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
-}
-
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
   if (a.count == 0) return hipSuccess;
   const dim3 grid(a.count, a.world);

@@ -44,10 +44,6 @@ struct CopyArgs {
 
 // Ring reduce-scatter arithmetic + 1/W scaling + all-gather for a range of tiles.
 hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t stream);
-// Whether the kernel that launch_ring_reduce picks for the long (stream_major != 0) or small tiles of
-// this world size handles tiles that straddle segment boundaries (ReduceTile::split != 0).  The tile
-// tables must hold none otherwise.
-bool reduce_handles_split_tiles(uint32_t world, bool long_tiles);
 // Segmented gather (pack) or scatter (unpack) driven by the copy-tile table.
 hipError_t launch_copy(const CopyArgs& a, hipStream_t stream);
 

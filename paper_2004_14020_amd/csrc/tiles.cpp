@@ -120,6 +120,54 @@ void split_tail(std::vector<ReduceTile>& tiles, size_t begin, const std::vector<
 
 }  // namespace
 
+// the rolled walk does, and that of three workers; the unrolled ones for 1, 2, 4 and 8 workers and the
+// kernel for the small tiles of these and of 16 do not
+bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
+  return world > 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
+}
+
+void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, uint32_t block, TileShape& ts) {
+  const caramel_config& c = p.cfg;
+  // Shapes left to the library (option value 0) follow the size of the job, measured on MI355X:
+  //  * a replica of less than 32 MiB is done before long tiles pay off (a 1024-lane workgroup
+  //    walks its tile one replica after the other): every run is cut into small tiles, whose
+  //    workgroups fetch all replicas at once (the MLP configuration: 3.4 against 6.3 us);
+  //  * fp32 chains keep eight vectors per lane in registers, so their long tiles can be 128 KiB,
+  //    which stream best, but are few: with less than about three rounds of the 256 workgroups
+  //    that run at a time the last round is felt.  2, 4 and 8 workers take them from 64 MiB per
+  //    replica on (VGG-16 528 MiB: 1438 -> 1396 us, ResNet-50 98 MiB: 275.3 -> 272.5); the others,
+  //    whose tiles also straddle segments and cost a step more, from 192 MiB on (16 workers, VGG-16:
+  //    2893 -> 2807, ResNet-v2-152 230 MiB: 1330 -> 1316, but Inception-v3 91 MiB: 506 -> 521; 12
+  //    workers, ResNet-50: 415 either way).  Everything else 64 KiB.
+  ts.tail_vecs = block;  // one vector per lane: a piece is fetched from all replicas at once
+  //  * tiles may straddle segment boundaries where the kernel sums the parts in their own orders.
+  //    Every boundary costs a step of the walk and saves a partial tile.  Up to 8 workers a step is
+  //    dear and segments are long: none for 2, 4 and 8, whose walk without boundaries is unrolled
+  //    (ResNet-50, 8 workers: 272 us without, 277 with one; VGG-16 1396 / 1395), one for the others
+  //    (VGG-16, 6 workers: 1082 / 1060).  16 workers: one (Inception-v3 517 / 506, VGG-16 2795 /
+  //    2807).  From 24 workers on segments are shorter than a tile: up to four (ResNet-50 bf16, 32
+  //    workers: 607 without, 579 with one, 561 with four; Inception-v3, 48 workers: 1802, 1612, 1534;
+  //    ResNet-50, 24 workers: 869, 831, 826).
+  const bool unrolled = c.world == 2 || c.world == 4 || c.world == 8;
+  ts.small_splits = reduce_handles_split_tiles(c.world, false) ? 1 : 0;
+  ts.max_splits = !reduce_handles_split_tiles(c.world, stream_major != 0) ? 0 : (c.world >= 24 ? 4 : 1);
+  ts.split_tiles = split_tiles && c.pattern == CARAMEL_PATTERN_RING && (ts.small_splits || ts.max_splits);
+  uint64_t replica_bytes = 0;
+  for (uint64_t e : p.tensor_elems) replica_bytes += e * p.elem_size();
+  if (ts.long_run_bytes == 0) ts.long_run_bytes = replica_bytes < (32u << 20) ? ~uint64_t(0) : 16u << 10;
+  if (ts.long_vecs == 0) {
+    // The tree holds eight vectors with 2 and 4 workers only (VGG-16, 4 workers: 713 -> 704 us; 8
+    // workers, with sums in LDS: 1408 -> 1430).
+    const bool tree = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
+    const bool wide = c.dtype == CARAMEL_F32 && !(tree && c.world > 4) && stream_major >= 8 &&
+                      block == 1024 && replica_bytes >= (uint64_t(unrolled ? 64 : 192) << 20);
+    // the bf16 tree of 32 and 64 workers keeps two vectors per lane: tiles of one pass (a second pass
+    // of a workgroup waits for the stores of the first)
+    const bool narrow = c.dtype == CARAMEL_BF16 && tree && c.world >= 32;
+    ts.long_vecs = wide ? 8192 : (narrow ? 2048 : 4096);
+  }
+}
+
 void build_tiles(const HostPlan& p, const TileShape& ts, TileTables& out, const uint64_t* row_addr) {
   out = TileTables{};
   const uint32_t W = p.cfg.world;

@@ -88,6 +88,14 @@ struct TileTables {
   Range copy_stream[2];            // copy tiles of all batch units of a stream
 };
 
+// Whether the kernel that launch_ring_reduce picks for the long (stream_major != 0) or small tiles of
+// this world size handles tiles that straddle segment boundaries (ReduceTile::split != 0).  The tile
+// tables must hold none otherwise.
+bool reduce_handles_split_tiles(uint32_t world, bool long_tiles);
+// Fills in what the options leave to the library: tile sizes, which runs are long, where tiles may hold
+// boundaries.  `stream_major` and `block` are the options of those names, `split_tiles` likewise.
+void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, uint32_t block, TileShape& ts);
+
 // `row_addr`, if given, holds (n_tensors + 1) x W base addresses, row-major (the last row is
 // the fused workspace; zeros if there is none): needed to cut tiles on aligned blocks.
 void build_tiles(const HostPlan& p, const TileShape& ts, TileTables& out, const uint64_t* row_addr = nullptr);
