@@ -133,12 +133,15 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
   //    walks its tile one replica after the other): every run is cut into small tiles, whose
   //    workgroups fetch all replicas at once (the MLP configuration: 3.4 against 6.3 us);
   //  * fp32 chains keep eight vectors per lane in registers, so their long tiles can be 128 KiB,
-  //    which stream best, but are few: with less than about three rounds of the 256 workgroups
-  //    that run at a time the last round is felt.  2, 4 and 8 workers take them from 64 MiB per
-  //    replica on (VGG-16 528 MiB: 1438 -> 1396 us, ResNet-50 98 MiB: 275.3 -> 272.5); the others,
-  //    whose tiles also straddle segments and cost a step more, from 192 MiB on (16 workers, VGG-16:
-  //    2893 -> 2807, ResNet-v2-152 230 MiB: 1330 -> 1316, but Inception-v3 91 MiB: 506 -> 521; 12
-  //    workers, ResNet-50: 415 either way).  Everything else 64 KiB.
+  //    which stream best, but are few (256 workgroups run at a time, and the last round is felt).
+  //    2, 4 and 8 workers take them from 64 MiB per replica on, two rounds (VGG-16, 528 MiB: 1438 ->
+  //    1396 us, ResNet-50, 98 MiB: 275.3 -> 272.5).  From 5 workers on, where a tile with a boundary
+  //    costs a step more, the others take them from 192 MiB on (16 workers, VGG-16: 2893 -> 2807,
+  //    ResNet-v2-152, 230 MiB: 1330 -> 1316, but Inception-v3, 91 MiB: 506 -> 521; 12 workers, VGG-16:
+  //    2138 -> 2115, ResNet-50: 415 either way; 5 to 7, 24 and 48 workers: from 1.7 % slower, 200 MiB, to
+  //    1.7 % faster, 300 MiB).  1 and 3 workers never: VGG-16 with 3 519.8 us in 128 KiB tiles and 517.4
+  //    in 64 (536.8 / 528.9 where every replica lies at another offset), one worker, 200 MiB, 67.4 / 66.6.
+  //    Everything else 64 KiB.
   ts.tail_vecs = block;  // one vector per lane: a piece is fetched from all replicas at once
   //  * tiles may straddle segment boundaries where the kernel sums the parts in their own orders.
   //    Every boundary costs a step of the walk and saves a partial tile.  Up to 8 workers a step is
@@ -148,7 +151,6 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
   //    2807).  From 24 workers on segments are shorter than a tile: up to four (ResNet-50 bf16, 32
   //    workers: 607 without, 579 with one, 561 with four; Inception-v3, 48 workers: 1802, 1612, 1534;
   //    ResNet-50, 24 workers: 869, 831, 826).
-  const bool unrolled = c.world == 2 || c.world == 4 || c.world == 8;
   ts.small_splits = reduce_handles_split_tiles(c.world, false) ? 1 : 0;
   ts.max_splits = !reduce_handles_split_tiles(c.world, stream_major != 0) ? 0 : (c.world >= 24 ? 4 : 1);
   ts.split_tiles = split_tiles && c.pattern == CARAMEL_PATTERN_RING && (ts.small_splits || ts.max_splits);
@@ -159,8 +161,9 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
     // The tree holds eight vectors with 2 and 4 workers only (VGG-16, 4 workers: 713 -> 704 us; 8
     // workers, with sums in LDS: 1408 -> 1430).
     const bool tree = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
-    const bool wide = c.dtype == CARAMEL_F32 && !(tree && c.world > 4) && stream_major >= 8 &&
-                      block == 1024 && replica_bytes >= (uint64_t(unrolled ? 64 : 192) << 20);
+    const bool few = c.world == 2 || c.world == 4 || c.world == 8;
+    const bool wide = c.dtype == CARAMEL_F32 && !(tree && c.world > 4) && stream_major >= 8 && block == 1024 &&
+                      (few || c.world > 4) && replica_bytes >= (uint64_t(few ? 64 : 192) << 20);
     // the bf16 tree of 32 and 64 workers keeps two vectors per lane: tiles of one pass (a second pass
     // of a workgroup waits for the stores of the first)
     const bool narrow = c.dtype == CARAMEL_BF16 && tree && c.world >= 32;

@@ -1,0 +1,41 @@
+"""Which tiles a plan gets by default: the lines of the rules, on the CPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import oracle
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2004_14020_amd", "csrc")
+MIB = 1 << 20
+RING, HD, SHUFFLE = oracle.PATTERN_RING, oracle.PATTERN_HALVING_DOUBLING, oracle.PATTERN_SHUFFLE
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+
+
+@pytest.fixture(scope="module")
+def shape(tmp_path_factory):
+    """(vectors per long tile or 0 if there are none, boundaries per long tile, per small tile)"""
+    exe = str(tmp_path_factory.mktemp("shape") / "shape_check")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(ROOT, "tests", "host", "shape_check.cpp"), os.path.join(CSRC, "plan.cpp"),
+                    os.path.join(CSRC, "tiles.cpp"), "-o", exe], check=True)
+
+    def ask(world, dtype, pattern, nbytes):
+        res = subprocess.run([exe, str(world), str(dtype), str(pattern), str(nbytes)], capture_output=True, text=True,
+                             check=True)
+        return tuple(int(x) for x in res.stdout.split())
+    return ask
+
+
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 7, 8, 9, 12, 16, 24, 64])
+def test_128_kib_tiles_where_they_pay(shape, W):
+    for pattern in (RING, SHUFFLE):
+        assert shape(W, oracle.F32, pattern, 32 * MIB - 4)[0] == 0
+        for at in (32, 64, 192, 1024):
+            wide = at >= 64 if W in (2, 4, 8) else (at >= 192 and W > 4)
+            assert shape(W, oracle.F32, pattern, at * MIB)[0] == (8192 if wide else 4096), (pattern, at)
+            assert shape(W, oracle.F32, pattern, at * MIB - 4)[0] != 8192 or at > (64 if W in (2, 4, 8) else 192)
+            assert shape(W, oracle.BF16, pattern, at * MIB)[0] == 4096
