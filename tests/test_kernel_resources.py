@@ -36,6 +36,11 @@ def test_long_walks_run_one_workgroup_per_compute_unit(kernels):
     assert {n: r["Occupancy [waves/SIMD]"] for n, r in walks.items() if r["Occupancy [waves/SIMD]"] != 4} == {}
 
 
+def test_no_kernel_spills_vector_registers(kernels):
+    quantities = ("VGPRs Spill", "ScratchSize [bytes/lane]")
+    assert {n: r for n, r in kernels.items() if any(r[q] for q in quantities)} == {}
+
+
 def test_copies_address_both_sides_with_one_offset(kernels):
     copies = {n: r["VGPRs"] for n, r in kernels.items() if n.startswith("k_copy<")}
     # a 128-bit value, a 64-bit offset, the counter and the lane
