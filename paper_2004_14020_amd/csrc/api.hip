@@ -787,9 +787,9 @@ int check_pointers(const HostPlan& h, void* const* grads, void* fused_ws, std::v
   return CARAMEL_OK;
 }
 
-void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& bd) {
+void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& bd, bool few_tiles = false) {
   bd.shape = p->opt.shape;
-  choose_shape(p->host, p->opt.split_tiles, p->opt.stream_major, p->opt.block, bd.shape);
+  choose_shape(p->host, p->opt.split_tiles, p->opt.stream_major, p->opt.block, few_tiles, bd.shape);
   bd.rows = std::move(rows);
   build_tiles(p->host, bd.shape, bd.tt, bd.rows.data());
   bd.groups_stale[0] = bd.groups_stale[1] = true;
@@ -904,15 +904,20 @@ int allreduce_static(caramel_plan* p, void* const* grads, hipStream_t stream) {
   if (dev < 0 || dev >= kMaxDevices) return fail(CARAMEL_ESTATE, "device %d is beyond the %d this entry point serves", dev, kMaxDevices);
 
   std::lock_guard<std::mutex> lock(g_scratch_mu);
+  auto table_bytes = [](const Binding& b) {
+    return (b.rows.size() * sizeof(uint64_t) + 255) / 256 * 256 + b.tt.direct.size() * sizeof(ReduceTile);
+  };
   if (!p->fixed_valid || rows != p->fixed.rows) {
     fill_binding(p, std::move(rows), p->fixed);
+    if (table_bytes(p->fixed) > CARAMEL_STATIC_TABLE_BYTES)
+      fill_binding(p, std::vector<uint64_t>(p->fixed.rows), p->fixed, true);
     p->fixed_valid = true;
     p->fixed_generation = ++g_generation;
   }
   const Binding& bd = p->fixed;
   const size_t rows_bytes = (bd.rows.size() * sizeof(uint64_t) + 255) / 256 * 256;
   const size_t tile_bytes = bd.tt.direct.size() * sizeof(ReduceTile);
-  if (rows_bytes + tile_bytes > CARAMEL_STATIC_TABLE_BYTES)
+  if (table_bytes(bd) > CARAMEL_STATIC_TABLE_BYTES)
     return fail(CARAMEL_EINVAL,
                 "this plan needs %zu bytes of descriptor tables (%zu tensors x %u workers, %zu tiles); the "
                 "static array holds %u: use caramel_bind + caramel_allreduce",

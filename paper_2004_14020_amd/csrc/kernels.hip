@@ -568,7 +568,7 @@ __device__ __forceinline__ void tree_element(const uint64_t* __restrict__ row, s
   }
 }
 
-// Small tiles of W = 32 or 64.
+// W = 32 or 64: small tiles, and whatever is not for k_tree_walk.
 template <bool BF16, int P>
 __global__ void __launch_bounds__(kMaxBlock)
 k_ring_reduce_tree_any(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ rows, uint32_t begin,
@@ -596,13 +596,15 @@ k_ring_reduce_tree_any(const ReduceTile* __restrict__ tiles, const uint64_t* __r
 // ResNet-v2-152, 16 workers: 1239 / 1235).  The partial sums of the highest levels, which change least
 // often, lie in LDS where the registers do not hold them all (kLds levels, at most 128 KiB, each lane
 // its own slots, so nothing has to be waited for).  That is room for N = 4 (64 KiB per burst) with fp32
-// and, up to 16 workers, with bf16, whose sums are twice as large.  With 36 bytes per lane spilled,
+// and, up to 16 workers, with bf16, whose sums are twice as large.  Over 32 and 64 workers in bf16 there
+// would be room for two vectors, which is slower than small tiles (32 x 33 MiB 449 us, 433; 32 x 70 921 /
+// 902; 64 x 70 1843 / 1816; 64 x 100 2662 / 2691): k_ring_reduce_tree_any takes these.  With 36 bytes per lane spilled,
 // global loads and two vectors for bf16 before: ResNet-v2-152, 16 workers 1301 -> 1235 us, Transformer
 // bf16, 8 workers 2049 -> 1724, ResNet-50, 32 workers fp32 (small tiles only) 1306 -> 1080.
 template <int W, bool BF16>
 struct TreeShape {
   static constexpr int kLevels = W >= 64 ? 5 : (W >= 32 ? 4 : (W >= 16 ? 3 : (W >= 8 ? 2 : (W >= 4 ? 1 : 0))));
-  static constexpr int N = BF16 ? (W >= 32 ? 2 : 4) : (W <= 4 ? 8 : 4);
+  static constexpr int N = !BF16 && W <= 4 ? 8 : 4;
   static constexpr int kLds = W >= 32 ? 2 : (BF16 && W == 16 ? 1 : 0);
   static constexpr int kSlots = kLds * N * (BF16 ? 2 : 1);  // 16-byte slots per lane
 };
@@ -787,7 +789,12 @@ hipError_t launch_tree(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t 
     else if (a.policy == kStream) CARAMEL_TREE(BF, kStream); \
     else CARAMEL_TREE(BF, kPlain); \
   } while (0)
-  if (a.bf16) CARAMEL_TREE3(true); else CARAMEL_TREE3(false);
+  if constexpr (W <= 16)
+    if (a.bf16) {
+      CARAMEL_TREE3(true);
+      return hipGetLastError();
+    }
+  CARAMEL_TREE3(false);
 #undef CARAMEL_TREE3
 #undef CARAMEL_TREE
   return hipGetLastError();
@@ -865,7 +872,7 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
     default: break;
   }
   if (a.world != 32 && a.world != 64) return hipErrorInvalidValue;
-  if (a.stream_major) return a.world == 32 ? launch_tree<32>(a, grid, inv_w, s) : launch_tree<64>(a, grid, inv_w, s);
+  if (a.stream_major && !a.bf16) return a.world == 32 ? launch_tree<32>(a, grid, inv_w, s) : launch_tree<64>(a, grid, inv_w, s);
 #define CARAMEL_TREE(BF, P) \
   hipLaunchKernelGGL((k_ring_reduce_tree_any<BF, P>), grid, dim3(a.block), 0, s, a.tiles, a.rows, a.begin, a.count, a.world, inv_w)
   if (a.bf16) {

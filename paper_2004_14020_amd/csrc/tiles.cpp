@@ -126,7 +126,8 @@ bool reduce_handles_split_tiles(uint32_t world, bool long_tiles) {
   return world > 2 && world != 4 && world != 8 && (world != 16 || long_tiles);
 }
 
-void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, uint32_t block, TileShape& ts) {
+void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, uint32_t block, bool few_tiles,
+                  TileShape& ts) {
   const caramel_config& c = p.cfg;
   // Shapes left to the library (option value 0) follow the size of the job, measured on MI355X:
   //  * a replica of less than 32 MiB is done before long tiles pay off (a 1024-lane workgroup
@@ -156,18 +157,19 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
   ts.split_tiles = split_tiles && c.pattern == CARAMEL_PATTERN_RING && (ts.small_splits || ts.max_splits);
   uint64_t replica_bytes = 0;
   for (uint64_t e : p.tensor_elems) replica_bytes += e * p.elem_size();
-  if (ts.long_run_bytes == 0) ts.long_run_bytes = replica_bytes < (32u << 20) ? ~uint64_t(0) : 16u << 10;
+  //  * halving-doubling over 32 and 64 workers in bf16 has no walk (the partial sums leave room for too
+  //    short bursts): small tiles throughout (32 x 33 MiB 449 -> 433 us), unless there must be few
+  const bool tree = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
+  const bool no_walk = tree && c.dtype == CARAMEL_BF16 && c.world >= 32;
+  if (ts.long_run_bytes == 0)
+    ts.long_run_bytes = replica_bytes < (32u << 20) || (no_walk && !few_tiles) ? ~uint64_t(0) : 16u << 10;
   if (ts.long_vecs == 0) {
     // The tree holds eight vectors with 2 and 4 workers only (VGG-16, 4 workers: 713 -> 704 us; 8
     // workers, with sums in LDS: 1408 -> 1430).
-    const bool tree = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
     const bool few = c.world == 2 || c.world == 4 || c.world == 8;
     const bool wide = c.dtype == CARAMEL_F32 && !(tree && c.world > 4) && stream_major >= 8 && block == 1024 &&
                       (few || c.world > 4) && replica_bytes >= (uint64_t(few ? 64 : 192) << 20);
-    // the bf16 tree of 32 and 64 workers keeps two vectors per lane: tiles of one pass (a second pass
-    // of a workgroup waits for the stores of the first)
-    const bool narrow = c.dtype == CARAMEL_BF16 && tree && c.world >= 32;
-    ts.long_vecs = wide ? 8192 : (narrow ? 2048 : 4096);
+    ts.long_vecs = wide ? 8192 : (no_walk ? 2048 : 4096);
   }
 }
 

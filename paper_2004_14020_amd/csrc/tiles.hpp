@@ -93,8 +93,10 @@ struct TileTables {
 // tables must hold none otherwise.
 bool reduce_handles_split_tiles(uint32_t world, bool long_tiles);
 // Fills in what the options leave to the library: tile sizes, which runs are long, where tiles may hold
-// boundaries.  `stream_major` and `block` are the options of those names, `split_tiles` likewise.
-void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, uint32_t block, TileShape& ts);
+// boundaries.  `split_tiles`, `stream_major` and `block` are the options of those names; `few_tiles`: the
+// tables must stay small, even where that is not the fastest.
+void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, uint32_t block, bool few_tiles,
+                  TileShape& ts);
 
 // `row_addr`, if given, holds (n_tensors + 1) x W base addresses, row-major (the last row is
 // the fused workspace; zeros if there is none): needed to cut tiles on aligned blocks.

@@ -24,7 +24,7 @@ int main(int argc, char** argv) {
   std::string why;
   if (build_host_plan(cfg, &elems, 1, nullptr, 0.0, 0.0, p, why) != CARAMEL_OK) return 3;
   TileShape ts;
-  choose_shape(p, true, 8, 1024, ts);
+  choose_shape(p, true, 8, 1024, false, ts);
   const bool long_tiles = ts.long_run_bytes != ~uint64_t(0);
   std::printf("%u %u %u\n", long_tiles ? ts.long_vecs : 0, ts.split_tiles ? ts.max_splits : 0,
               ts.split_tiles ? ts.small_splits : 0);

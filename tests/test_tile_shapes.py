@@ -39,3 +39,10 @@ def test_128_kib_tiles_where_they_pay(shape, W):
             assert shape(W, oracle.F32, pattern, at * MIB)[0] == (8192 if wide else 4096), (pattern, at)
             assert shape(W, oracle.F32, pattern, at * MIB - 4)[0] != 8192 or at > (64 if W in (2, 4, 8) else 192)
             assert shape(W, oracle.BF16, pattern, at * MIB)[0] == 4096
+
+
+@pytest.mark.parametrize("W", [2, 8, 16, 32, 64])
+def test_trees_without_a_walk_get_small_tiles(shape, W):
+    for at in (32, 64, 1024):
+        assert shape(W, oracle.BF16, HD, at * MIB)[0] == (4096 if W <= 16 else 0)
+        assert shape(W, oracle.F32, HD, at * MIB)[0] == (8192 if W <= 4 and at >= 64 else 4096)

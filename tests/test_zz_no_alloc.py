@@ -70,3 +70,26 @@ def test_static_entry_point_rejects_what_does_not_fit():
     with pytest.raises(cm.CaramelError):
         plan.allreduce_static([[0] * n for _ in range(W)])
     plan.close()
+
+
+def test_static_entry_point_takes_longer_tiles_before_it_refuses():
+    """Halving-doubling over 32 workers in bf16 has small tiles by default; where the static array cannot
+    hold that many, the tables are built with long ones, and the result is the same."""
+    W, size = 32, 2
+    elems = [16] * 13800 + [(40 << 20) // size]
+    print("case: static entry point, tables that fit with long tiles only", flush=True)
+    cfg = dict(dtype=cm.BF16, pattern=cm.PATTERN_HALVING_DOUBLING, num_streams=1)
+    bound, unbound = cm.Plan(W, elems, **cfg), cm.Plan(W, elems, **cfg)
+    dev = Replicas(bound, elems, with_workspace=False, slot_align=32)
+    stream = torch.cuda.current_stream().cuda_stream
+    dev.fill_random(3)
+    bound.profile(1)
+    bound.allreduce(stream)
+    assert bound.profile_read()[cm.K_REDUCE]["elements"] == 0       # small tiles throughout
+    want = [dev.arenas[w].clone() for w in (0, 17, 31)]
+    dev.fill_random(3)
+    unbound.allreduce_static(dev.pointers(), stream)
+    for w, x in zip((0, 17, 31), want):
+        assert torch.equal(dev.arenas[w], x), f"replica {w}"
+    bound.close()
+    unbound.close()
