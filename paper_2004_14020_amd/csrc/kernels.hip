@@ -532,34 +532,38 @@ __device__ __forceinline__ void tree_column(const uint64_t* __restrict__ row, ui
   for (uint32_t k = 0; k < W; ++k) st<P>(reinterpret_cast<gvec_ptr>(row[k]) + vec_off, v * 16u, y);
 }
 
-// The same tree on one element (the ragged end of a tensor), any power of two.
+// The same tree on one element (the ragged end of a tensor).  As many loads at once as tree_column: one
+// tile in three of a small job has such an end, and a loop over the blocks that carries its partial sums
+// in memory order is felt (64 x 0.3 MiB bf16 25.4 us, 17.5; 32 x 2 MiB 30.6 / 28.5).
 template <bool BF16>
 __device__ __forceinline__ void tree_element(const uint64_t* __restrict__ row, size_t e, uint32_t W, float inv_w) {
-  float part[7];
+  constexpr int kBlk = 8, kMaxBlocks = 8;
+  const uint32_t n_blocks = W / kBlk;
+  float part[4];
   float y = 0.f;
-  for (uint32_t k0 = 0; k0 < W; k0 += 8) {
-    float x[8];
 #pragma unroll
-    for (uint32_t i = 0; i < 8; ++i)
-      if (k0 + i < W) {
-        if constexpr (BF16) x[i] = widen(reinterpret_cast<gu16_ptr>(row[k0 + i])[e]);
-        else x[i] = reinterpret_cast<gf32_ptr>(row[k0 + i])[e];
+  for (int j = 0; j < kMaxBlocks; ++j) {
+    if (uint32_t(j) < n_blocks) {
+      float t[kBlk];
+#pragma unroll
+      for (int i = 0; i < kBlk; ++i) {
+        if constexpr (BF16) t[i] = widen(reinterpret_cast<gu16_ptr>(row[j * kBlk + i])[e]);
+        else t[i] = reinterpret_cast<gf32_ptr>(row[j * kBlk + i])[e];
       }
 #pragma unroll
-    for (uint32_t i = 0; i < 8; i += 2)
-      if (k0 + i < W) {
-        y = x[i] + x[i + 1];
-        bool open = true;
+      for (int s = 1; s < kBlk; s *= 2)
 #pragma unroll
-        for (int l = 1; l < 7; ++l) {
-          const bool carry = open && (((k0 + i) >> l) & 1);
-          y = carry ? part[l] + y : y;
-          if (open && !carry) part[l] = y;
-          open = carry;
-        }
+        for (int i = 0; i + s < kBlk; i += 2 * s) t[i] = t[i] + t[i + s];
+      int lvl = 0;
+#pragma unroll
+      for (int m = j + 1; (m & 1) == 0; m >>= 1) {
+        t[0] = part[lvl] + t[0];
+        ++lvl;
       }
+      part[lvl] = t[0];
+      if (uint32_t(j) + 1 == n_blocks) y = t[0] * inv_w;
+    }
   }
-  y *= inv_w;
   if constexpr (BF16) {
     const uint16_t o = uint16_t(bf16_rne(y));
     for (uint32_t k = 0; k < W; ++k) reinterpret_cast<gu16_ptr>(row[k])[e] = o;
@@ -727,8 +731,28 @@ k_tree_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ r
       done += n;
     }
     const uint32_t rem = tl.n_elems - nvec * VE;
-    if (threadIdx.x < rem)
-      tree_element<BF16>(row, size_t(tl.vec_off) * VE + nvec * VE + threadIdx.x, W, inv_w);
+    if (threadIdx.x < rem) {
+      const size_t e = size_t(tl.vec_off) * VE + nvec * VE + threadIdx.x;
+      if constexpr (W >= 32) {
+        tree_element<BF16>(row, e, W, inv_w);
+      } else {
+        float x[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+          if constexpr (BF16) x[k] = widen(reinterpret_cast<gu16_ptr>(row[k])[e]);
+          else x[k] = reinterpret_cast<gf32_ptr>(row[k])[e];
+        }
+        const float y = combine_scalar<W, true>(x, inv_w);
+        if constexpr (BF16) {
+          const uint16_t o = uint16_t(bf16_rne(y));
+#pragma unroll
+          for (int k = 0; k < W; ++k) reinterpret_cast<gu16_ptr>(row[k])[e] = o;
+        } else {
+#pragma unroll
+          for (int k = 0; k < W; ++k) reinterpret_cast<gf32_ptr>(row[k])[e] = y;
+        }
+      }
+    }
   }
 }
 
