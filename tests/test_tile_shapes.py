@@ -23,8 +23,8 @@ def shape(tmp_path_factory):
                     os.path.join(ROOT, "tests", "host", "shape_check.cpp"), os.path.join(CSRC, "plan.cpp"),
                     os.path.join(CSRC, "tiles.cpp"), "-o", exe], check=True)
 
-    def ask(world, dtype, pattern, nbytes):
-        res = subprocess.run([exe, str(world), str(dtype), str(pattern), str(nbytes)], capture_output=True, text=True,
+    def ask(world, dtype, pattern, nbytes, block=1024):
+        res = subprocess.run([exe, *map(str, (world, dtype, pattern, nbytes, block))], capture_output=True, text=True,
                              check=True)
         return tuple(int(x) for x in res.stdout.split())
     return ask
@@ -46,3 +46,6 @@ def test_trees_without_a_walk_get_small_tiles(shape, W):
     for at in (32, 64, 1024):
         assert shape(W, oracle.BF16, HD, at * MIB)[0] == (4096 if W <= 16 else 0)
         assert shape(W, oracle.F32, HD, at * MIB)[0] == (8192 if W <= 4 and at >= 64 else 4096)
+        for block in (256, 512):
+            assert shape(W, oracle.BF16, HD, at * MIB, block)[0] == (2048 if W <= 16 else 0)
+            assert shape(W, oracle.F32, HD, at * MIB, block)[0] == 4096
