@@ -325,8 +325,11 @@ enum {
   CARAMEL_OPT_TILE_VECS = 2,
   /* Upper bound on workgroups per reduce launch (0 = one workgroup per tile). */
   CARAMEL_OPT_MAX_GRID = 3,
-  /* Non-zero (default): streaming (non-temporal) loads/stores in the reduce kernels, and in pack /
-   * unpack when the fused buffers of all workers together hold 256 MiB or more. */
+  /* Non-zero (default): streaming (non-temporal) loads/stores in the reduce kernels, with stores
+   * written through the L2 for long tiles of a reduction in place, and in pack / unpack when the
+   * fused buffers of all workers together hold 256 MiB or more.  Even then a staged reduction uses
+   * plain accesses if three quarters of the plan's elements or more are in the fused buffer.
+   * 0: plain accesses everywhere. */
   CARAMEL_OPT_NONTEMPORAL = 4,
   /* 16-byte vectors each lane keeps in flight per worker where all replicas are fetched at
    * once: 1, 2 or 4; 0 = chosen from W. */

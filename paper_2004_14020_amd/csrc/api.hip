@@ -246,18 +246,19 @@ int run_reduce(caramel_plan* p, const Binding& bd, const DeviceTables& dt, bool 
   // by default a workgroup takes a whole tile in one go: vectors per lane = tile / workgroup size
   const bool lng = cls == kLong;
   a.block = lng ? p->opt.block : p->opt.small_block;
-  // Writing through pays for replicas that stream from HBM, and long tiles exist for those only (at
-  // least 32 MiB each): VGG-16 1469 -> 1437 us, Inception-v3 544 -> 525, 12 workers 449 -> 431.
-  // Where the last-level cache holds the data it costs (24 workers of 3 MB, small tiles: 38.5 -> 46.2
-  // us), and so it does for fused buffers, which unpack is about to read (Inception-v3's stages
-  // 359 -> 363 us).
-  // A staged reduction that works mostly on fused buffers (three quarters of the elements) uses plain
-  // accesses: the replicas' fused buffers start on any granule, so lines are written in parts, which
-  // the L2 joins (Inception-v3's stages, 78 % fused: 364 -> 340 us; VGG-16's, mostly chunks: 192 -> 217).
-  uint64_t elems = 0;
-  if (!direct)
-    for (uint64_t e : p->host.tensor_elems) elems += e;
-  const bool fused = !direct && 4 * p->host.fused_elems >= 3 * elems;
+  // Writing through pays for long tiles, also where all replicas together fit the last-level cache
+  // (VGG-16 1469 -> 1437 us, Inception-v3 544 -> 525, 12 workers 449 -> 431; 2 x 33 MiB 26.2 -> 25.8, 4 x 64
+  // MiB 94.6 -> 92.4, their data not in the cache).  For small tiles it costs (24 workers of 3 MB: 38.5 ->
+  // 46.2 us), and so it does for fused buffers, which unpack is about to read (Inception-v3's stages 359
+  // -> 363 us).
+  // A staged reduction that works mostly on fused buffers uses plain accesses: the replicas' fused
+  // buffers start on any granule, so lines are written in parts, which the L2 joins.  The line lies
+  // where that comes to outweigh the chunks, which want streaming.  All three stages with plain accesses
+  // against streaming: of 90 MiB per replica, 3 to 16 workers, 7 to 13 % longer with 3 to 18 % of the
+  // elements fused, 2 to 9 % with 29 to 47 %, up to 4 % with 54 to 67 %, from 8 % shorter to 2 % longer from
+  // 78 % on (Inception-v3 bf16, 78 %: 358 -> 334 us; 16 workers fp32, all fused: 1570 / 1592); of 8 and
+  // 25 MiB up to 15 % shorter from 78 % on (3 workers fp32, 25 MiB: up to 2 % longer).
+  const bool fused = !direct && 4 * p->host.fused_elems >= 3 * p->host.replica_elems;
   a.policy = p->opt.nontemporal == 0 || fused ? kPlain : (lng && direct ? kThrough : kStream);
   const uint32_t tile_vecs = lng ? bd.shape.long_vecs : bd.shape.small_vecs;
   a.unroll = p->opt.unroll ? p->opt.unroll : std::max(1u, tile_vecs / a.block);
@@ -348,9 +349,7 @@ int join_streams(caramel_plan* p, hipStream_t user, bool pipelined) {
 bool use_pipeline(const caramel_plan* p) {
   if (p->host.cfg.num_streams != 2) return false;
   if (p->opt.launch_mode != CARAMEL_LAUNCH_AUTO) return true;
-  uint64_t elems = 0;
-  for (uint64_t e : p->host.tensor_elems) elems += e;
-  return 2 * uint64_t(p->host.cfg.world) * elems * p->host.elem_size() >= p->opt.pipeline_min_bytes;
+  return 2 * uint64_t(p->host.cfg.world) * p->host.replica_elems * p->host.elem_size() >= p->opt.pipeline_min_bytes;
 }
 
 // PER_UNIT or PER_STREAM: what the launch mode comes to for this plan.

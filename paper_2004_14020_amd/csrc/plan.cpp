@@ -161,6 +161,8 @@ int build_host_plan(const caramel_config& cfg, const uint64_t* elems, uint32_t n
   out = HostPlan{};
   out.cfg = cfg;
   out.tensor_elems.assign(elems, elems + n);
+  out.replica_elems = 0;
+  for (uint64_t e : out.tensor_elems) out.replica_elems += e;
   Queue q(cfg, out, timed, net_a, net_b);
   for (uint32_t i = 0; i < n; ++i) {
     if (timed) q.set_now(ready_time[i]);

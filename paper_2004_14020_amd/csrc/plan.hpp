@@ -13,6 +13,7 @@ namespace caramel {
 struct HostPlan {
   caramel_config cfg{};
   std::vector<uint64_t> tensor_elems;
+  uint64_t replica_elems = 0;  // their sum
   std::vector<caramel_unit> units;
   std::vector<caramel_entry> entries;
   std::vector<uint64_t> seg;  // (world + 1) offsets per unit, unit-major

@@ -155,8 +155,7 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
   ts.small_splits = reduce_handles_split_tiles(c.world, false) ? 1 : 0;
   ts.max_splits = !reduce_handles_split_tiles(c.world, stream_major != 0) ? 0 : (c.world >= 24 ? 4 : 1);
   ts.split_tiles = split_tiles && c.pattern == CARAMEL_PATTERN_RING && (ts.small_splits || ts.max_splits);
-  uint64_t replica_bytes = 0;
-  for (uint64_t e : p.tensor_elems) replica_bytes += e * p.elem_size();
+  const uint64_t replica_bytes = p.replica_elems * p.elem_size();
   //  * halving-doubling over 32 and 64 workers in bf16 has no walk (the partial sums leave room for too
   //    short bursts): small tiles throughout (32 x 33 MiB 449 -> 433 us), unless there must be few
   const bool tree = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
