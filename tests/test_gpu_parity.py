@@ -155,8 +155,8 @@ def test_segment_boundaries_at_odd_positions(W, dtype):
     elems = [100000, 4099, 70001, 16384, 262144 + 4, 50, 33333, 8192 * W, 1 << 20]
     grads = make_inputs(cfg, elems, seed=900 + W)
     ref = oracle_result(cfg, elems, grads)
-    # world sizes without a kernel of their own get tiles across the boundaries, unless switched off
-    splits = (1,) if W in (2, 4, 8, 16) else (1, 0)
+    # all but these get tiles across the boundaries, unless switched off
+    splits = (1,) if W in (2, 4, 8) else (1, 0)
     for opts in [{**o, cm.OPT_SPLIT_TILES: sp} for o in BOUNDARY_SHAPES for sp in splits]:
         for phase in (0, 1280):
             plan = lib_plan(cfg, elems, opts)
