@@ -58,11 +58,23 @@ def parse_args():
     return ap.parse_args()
 
 
-def read_traffic(name: str):
-    """HBM bytes per reduce-kernel launch from the committed counter summary, if there is one."""
+def reduce_kernel(pattern: str, world: int, bf16: bool, long_tiles: bool) -> str:
+    """The kernel that a reduction over long or small tiles runs, by the library's default rules."""
+    if pattern == "hd" and world > 1:
+        if long_tiles and not (bf16 and world >= 32):
+            return "k_tree_walk"
+        return "k_ring_reduce" if world <= 16 else "k_ring_reduce_tree_any"
+    return "k_walk" if long_tiles or world not in (1, 2, 4, 8, 16) else "k_ring_reduce"
+
+
+def read_traffic(name: str, kernel: str):
+    """HBM bytes per reduce-kernel launch from the committed counter summary, if there is one of this
+    kernel (its first line names it)."""
     path = os.path.join(ROOT, "profiles", f"ring_reduce_{name}_hbm_traffic.txt")
     try:
         with open(path) as f:
+            if f"({kernel}<" not in f.readline():
+                return None
             for line in f:
                 if line.startswith("traffic_bytes_per_launch:"):
                     return float(line.split(":", 1)[1])
@@ -203,8 +215,8 @@ def main() -> int:
     alg_bytes = wl.algorithmic_bytes()
     gbs = alg_bytes / (ms_per_step * 1e-3) / 1e9
 
-    # Dominant kernel: k_walk, the ring reduction over long tiles (in the
-    # default in-place mode the only other kernel is k_ring_reduce over the few short runs).
+    # Dominant kernel: the reduction over long tiles (in the default in-place mode the only other launch
+    # is the one over the few short runs, where these do not join it).
     #   achieved = algorithmic bytes of its launches (2*W*s per element they cover)
     #              / the sum of their durations, both counted by the library over the timed region
     es = 4 if wl.dtype == cm.F32 else 2
@@ -221,13 +233,18 @@ def main() -> int:
             out["achieved"] = round(per_elem * st["elements"] / (st["total_ms"] * 1e-3) / 1e9, 1)
         return out
 
-    dom_name, dom = ("k_walk", lng) if lng["elements"] >= sml["elements"] else ("k_ring_reduce", sml)
+    dom = lng if lng["elements"] >= sml["elements"] else sml
+    dom_name = reduce_kernel(args.pattern, wl.world, wl.dtype == cm.BF16, dom is lng)
+    # the counters were taken with the default options
+    as_profiled = args.pattern == "ring" and all(
+        v is None for v in (args.launch_mode, args.batch_path, args.tile_vecs, args.max_grid, args.nontemporal, args.unroll,
+                            args.block, args.launch_min_bytes, args.align_tiles, args.long_run_bytes))
     dom_line = kernel_line(dom) or {}
     span_ms = seq["span_ms"] / max(1, seq["calls"])
     roofline = {"bound": "hbm", "kernel": dom_name, "achieved": dom_line.get("achieved"), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s",
                 "frac": round(dom_line["achieved"] / HBM_PEAK_GBS, 4) if dom_line.get("achieved") else None,
-                "traffic": read_traffic(wl.name),
+                "traffic": read_traffic(wl.name, dom_name) if as_profiled else None,
                 "launches_per_step": dom_line.get("launches_per_step"),
                 "avg_launch_ms": dom_line.get("avg_launch_ms"), "bytes_per_launch": dom_line.get("bytes_per_launch"),
                 "share_of_step_bytes": round(dom["elements"] / max(1, lng["elements"] + sml["elements"]), 4),
