@@ -35,6 +35,14 @@ __device__ __forceinline__ gvec_ptr at(gvec_ptr base, uint32_t byte_off) {
   return reinterpret_cast<gvec_ptr>(reinterpret_cast<CARAMEL_GLOBAL char*>(base) + byte_off);
 }
 
+// The buffer accesses take the cache policy as an operand: `nt` and `sc1` bits.
+constexpr int kNt = 2, kSc1 = 16;
+template <int P>
+constexpr int kLoadBits = P == kPlain ? 0 : kNt;
+template <int P>
+constexpr int kStoreBits = P == kPlain ? 0 : (P == kThrough ? kSc1 | kNt : kNt);
+constexpr int kRawBuffer = 0x00027000;  // word 3 of a buffer resource: untyped data
+
 template <int P>
 __device__ __forceinline__ u32x4 ld(gvec_ptr p) {
   if constexpr (P != kPlain) return __builtin_nontemporal_load(p);
@@ -51,9 +59,8 @@ __device__ __forceinline__ void st(gvec_ptr base, uint32_t byte_off, u32x4 v) {
   if constexpr (P == kThrough) {
     // C++ has no way to ask for this pair on a 128-bit store; the buffer form takes the policy as an
     // operand.  The resource is the bare base (untyped, no bound of its own).
-    constexpr int kRaw = 0x00027000, kNt = 2, kSc1 = 16;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, kRaw);
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, int(byte_off), 0, kSc1 | kNt);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, kRawBuffer);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, int(byte_off), 0, kStoreBits<P>);
   } else {
     st<P>(at(base, byte_off), v);
   }
@@ -254,7 +261,6 @@ k_ring_reduce(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__
 // longer fit beside the sums (8 VGPRs and 28 SGPRs spilled), and the rolled loop is no slower
 // (ResNet-v2-152 1263 -> 1258 us, Inception-v3 512 -> 510, bf16 16 x 33 MiB 203.6 -> 202.5).
 constexpr uint32_t kNowhere = 0x40000000u;  // an offset beyond every tile
-constexpr int kRawBuffer = 0x00027000;      // resource word 3: untyped data
 
 // The segment boundaries inside a tile, in bytes from its start.
 struct Splits {
@@ -287,8 +293,6 @@ struct Splits {
 template <int CW, bool BF16, int P, bool SPLIT>
 struct Walk {
   static_assert(!SPLIT || CW == 0, "the unrolled loop has no room for the conditions");
-  static constexpr int kLoad = P == kPlain ? 0 : 2 /* nt */;
-  static constexpr int kStore = P == kPlain ? 0 : (P == kThrough ? 18 /* sc1 nt */ : 2);
   const uint64_t* __restrict__ row;
   uint64_t mine;       // CW == 0: the tile's address in replica `lane` (W <= 64: every wavefront holds all)
   uint64_t start;      // bytes from a row's base to the tile
@@ -336,7 +340,7 @@ struct Walk {
       if constexpr (SPLIT) asm volatile("" : "+v"(lateness));  // (shifted anew: no registers for the parts)
 #pragma unroll
       for (int u = 0; u < N; ++u)
-        buf[j][u] = __builtin_amdgcn_raw_buffer_load_b128(r, int(wanted(k, u) ? off + u * stride : kNowhere), 0, kLoad);
+        buf[j][u] = __builtin_amdgcn_raw_buffer_load_b128(r, int(wanted(k, u) ? off + u * stride : kNowhere), 0, kLoadBits<P>);
       __builtin_amdgcn_sched_barrier(0);
     };
     auto add = [&](uint32_t k, int j) {
@@ -375,7 +379,7 @@ struct Walk {
     for (uint32_t k = 0; k < W(); ++k) {
       const __amdgpu_buffer_rsrc_t r = res(worker(k));
 #pragma unroll
-      for (int u = 0; u < N; ++u) __builtin_amdgcn_raw_buffer_store_b128(y[u], r, int(off + u * stride), 0, kStore);
+      for (int u = 0; u < N; ++u) __builtin_amdgcn_raw_buffer_store_b128(y[u], r, int(off + u * stride), 0, kStoreBits<P>);
     }
   }
 
@@ -391,7 +395,7 @@ struct Walk {
       for (int i = 0; i < kMost; ++i)
         if (CW || i == 0 || k0 + i < n_steps) {
           const bool wanted = !SPLIT || k0 + i - late < W();
-          x[i] = __builtin_amdgcn_raw_buffer_load_b128(res(worker(k0 + i)), int(wanted ? off : kNowhere), 0, kLoad);
+          x[i] = __builtin_amdgcn_raw_buffer_load_b128(res(worker(k0 + i)), int(wanted ? off : kNowhere), 0, kLoadBits<P>);
         }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -404,7 +408,7 @@ struct Walk {
     const u32x4 y = acc.finish(inv_w);
 #pragma unroll(CW ? CW : 4)
     for (uint32_t k = 0; k < W(); ++k)
-      __builtin_amdgcn_raw_buffer_store_b128(y, res(worker(k)), int(off), 0, kStore);
+      __builtin_amdgcn_raw_buffer_store_b128(y, res(worker(k)), int(off), 0, kStoreBits<P>);
   }
 };
 
@@ -627,8 +631,6 @@ k_tree_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ r
             uint32_t cap, float inv_w) {
   using S = TreeShape<W, BF16>;
   constexpr uint32_t VE = BF16 ? 8 : 4;
-  constexpr int kLoad = P == kPlain ? 0 : 2 /* nt */;
-  constexpr int kStore = P == kPlain ? 0 : (P == kThrough ? 18 /* sc1 nt */ : 2);
   __shared__ f32x4 high[S::kSlots ? S::kSlots * kMaxBlock : 1];
   for (uint32_t ti = blockIdx.x; ti < count; ti += gridDim.x) {
     const ReduceTile tl = tiles[begin + ti];
@@ -657,7 +659,7 @@ k_tree_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ r
           const __amdgpu_buffer_rsrc_t r = res(k);
 #pragma unroll
           for (int u = 0; u < N; ++u)
-            buf[k % 2][u] = __builtin_amdgcn_raw_buffer_load_b128(r, int(off + u * stride), 0, kLoad);
+            buf[k % 2][u] = __builtin_amdgcn_raw_buffer_load_b128(r, int(off + u * stride), 0, kLoadBits<P>);
         };
         auto slot = [&](int level, int u, int half) -> f32x4& {
           constexpr int kHalves = BF16 ? 2 : 1;
@@ -705,7 +707,7 @@ k_tree_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ r
         for (int k = 0; k < W; ++k) {
           const __amdgpu_buffer_rsrc_t r = res(k);
 #pragma unroll
-          for (int u = 0; u < N; ++u) __builtin_amdgcn_raw_buffer_store_b128(y[u], r, int(off + u * stride), 0, kStore);
+          for (int u = 0; u < N; ++u) __builtin_amdgcn_raw_buffer_store_b128(y[u], r, int(off + u * stride), 0, kStoreBits<P>);
         }
       };
       if constexpr (S::N >= 8) {
@@ -721,11 +723,11 @@ k_tree_walk(const ReduceTile* __restrict__ tiles, const uint64_t* __restrict__ r
         } else {
           u32x4 x[W];
 #pragma unroll
-          for (int k = 0; k < W; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b128(res(k), int(off), 0, kLoad);
+          for (int k = 0; k < W; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b128(res(k), int(off), 0, kLoadBits<P>);
           __builtin_amdgcn_sched_barrier(0);
           const u32x4 y = combine<W, BF16, true>(x, inv_w);
 #pragma unroll
-          for (int k = 0; k < W; ++k) __builtin_amdgcn_raw_buffer_store_b128(y, res(k), int(off), 0, kStore);
+          for (int k = 0; k < W; ++k) __builtin_amdgcn_raw_buffer_store_b128(y, res(k), int(off), 0, kStoreBits<P>);
         }
       }
       done += n;

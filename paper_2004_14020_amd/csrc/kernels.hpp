@@ -28,7 +28,7 @@ struct ReduceArgs {
   uint32_t block;     // lanes per workgroup: 256, 512 or 1024
   uint32_t stream_major;  // 0: a launch over small tiles, fetch all workers at once; else: walk the
                           // workers one by one with (up to) that many vectors per lane; 8 exists for
-                          // fp32 chains, everything else gets 4
+                          // fp32 chains and fp32 trees over 2 and 4 workers, everything else gets 4
 };
 
 struct CopyArgs {

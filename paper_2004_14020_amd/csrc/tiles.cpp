@@ -149,7 +149,8 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
   //    dear and segments are long: none for 2, 4 and 8, whose walk without boundaries is unrolled
   //    (ResNet-50, 8 workers: 272 us without, 277 with one; VGG-16 1396 / 1395), one for the others
   //    (VGG-16, 6 workers: 1082 / 1060).  16 workers: one (Inception-v3 517 / 506, VGG-16 2795 /
-  //    2807).  From 24 workers on segments are shorter than a tile: up to four (ResNet-50 bf16, 32
+  //    2807).  From 24 workers on, where the segments of a unit of a few MiB are not much longer than a
+  //    tile or shorter (4 MiB over 48 workers: 85 KiB), up to four (ResNet-50 bf16, 32
   //    workers: 607 without, 579 with one, 561 with four; Inception-v3, 48 workers: 1802, 1612, 1534;
   //    ResNet-50, 24 workers: 869, 831, 826).
   ts.small_splits = reduce_handles_split_tiles(c.world, false) ? 1 : 0;
@@ -258,7 +259,8 @@ void build_tiles(const HostPlan& p, const TileShape& ts, TileTables& out, const 
     for (int cls = 0; cls < 2; ++cls) {
       const uint64_t tile_elems = uint64_t(cls == kLong ? ts.long_vecs : ts.small_vecs) * ve;
       const bool align = (ts.align_tiles & (cls == kSmall ? 1u : 2u)) != 0;
-      const uint32_t splits = ts.split_tiles ? std::min(cls == kSmall ? ts.small_splits : ts.max_splits, std::min(kMaxSplits, W - 1)) : 0;
+      const uint32_t wanted = ts.split_tiles ? (cls == kSmall ? ts.small_splits : ts.max_splits) : 0;
+      const uint32_t splits = std::min(wanted, std::min(kMaxSplits, W - 1));
       for (uint32_t s = 0; s < p.cfg.num_streams; ++s) {
         const size_t stream_begin = tiles.size();
         std::vector<uint64_t> phases;
