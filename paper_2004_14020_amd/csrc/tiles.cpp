@@ -132,7 +132,9 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
   // Shapes left to the library (option value 0) follow the size of the job, measured on MI355X:
   //  * a replica of less than 32 MiB is done before long tiles pay off (a 1024-lane workgroup
   //    walks its tile one replica after the other): every run is cut into small tiles, whose
-  //    workgroups fetch all replicas at once (the MLP configuration: 3.4 against 6.3 us);
+  //    workgroups fetch all replicas at once (small against long tiles, fp32: 2 x 16 MiB 13.6 / 14.0 us, 2 x
+  //    33 25.0 / 25.2, 4 x 24 36.6 / 37.8, 4 x 33 50.0 / 49.1, 8 x 24 76.6 / 78.3, 8 x 33 104.5 / 104.1, 8 x
+  //    48 155 / 145; 16 workers cross earlier, 8 MiB 54.0 / 69.3, 16 MiB 110 / 104);
   //  * fp32 chains keep eight vectors per lane in registers, so their long tiles can be 128 KiB,
   //    which stream best, but are few (256 workgroups run at a time, and the last round is felt).
   //    2, 4 and 8 workers take them from 64 MiB per replica on, two rounds (VGG-16, 528 MiB: 1438 ->

@@ -2,8 +2,8 @@
 """World-size sweep: one all-reduce of a single fp32 (or bf16) tensor, split into 4 MiB chunks,
 with the replicas together holding a fixed number of bytes, for a range of world sizes and the
 three aggregation patterns (paper sections 2 and 6.3: ring, halving-doubling, shuffle).
-World sizes 2, 4, 8 and 16 run kernels specialised for them, every other size the generic
-kernel; halving-doubling needs a power of two.  Prints algorithmic GB/s (2 * W * N * s bytes per
+World sizes 1 to 4 and 8 run kernels unrolled over the workers, every other size rolled ones;
+halving-doubling needs a power of two.  Prints algorithmic GB/s (2 * W * N * s bytes per
 call) and the fraction of the 8 TB/s HBM peak.
 
   python -m paper_2004_14020_amd.world_sweep [--total-mib 1024] [--bf16]
