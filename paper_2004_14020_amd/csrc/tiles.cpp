@@ -170,10 +170,10 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
     // workers, with sums in LDS: 1408 -> 1430).
     const bool few = c.world == 2 || c.world == 4 || c.world == 8;
     const bool wide = c.dtype == CARAMEL_F32 && !(tree && c.world > 4) && stream_major >= 8 && block == 1024 &&
-                      (few || c.world > 4) && replica_bytes >= (uint64_t(few ? 64 : 192) << 20);
+                      (few || few_tiles || c.world > 4) && replica_bytes >= (uint64_t(few ? 64 : 192) << 20);
     // a bf16 tree keeps four vectors per lane: workgroups of 512 lanes or fewer get tiles of 32 KiB (512
     // lanes, 8 x 60 MiB 202 -> 194 us, 2 x 60 MiB 48.9 -> 45.4)
-    const bool narrow = no_walk || (tree && c.dtype == CARAMEL_BF16 && block < 1024);
+    const bool narrow = no_walk || (tree && c.dtype == CARAMEL_BF16 && block < 1024 && !few_tiles);
     ts.long_vecs = wide ? 8192 : (narrow ? 2048 : 4096);
   }
 }

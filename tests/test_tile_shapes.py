@@ -23,8 +23,8 @@ def shape(tmp_path_factory):
                     os.path.join(ROOT, "tests", "host", "shape_check.cpp"), os.path.join(CSRC, "plan.cpp"),
                     os.path.join(CSRC, "tiles.cpp"), "-o", exe], check=True)
 
-    def ask(world, dtype, pattern, nbytes, block=1024):
-        res = subprocess.run([exe, *map(str, (world, dtype, pattern, nbytes, block))], capture_output=True, text=True,
+    def ask(world, dtype, pattern, nbytes, block=1024, few_tiles=0):
+        res = subprocess.run([exe, *map(str, (world, dtype, pattern, nbytes, block, few_tiles))], capture_output=True, text=True,
                              check=True)
         return tuple(int(x) for x in res.stdout.split())
     return ask
@@ -49,3 +49,13 @@ def test_trees_without_a_walk_get_small_tiles(shape, W):
         for block in (256, 512):
             assert shape(W, oracle.BF16, HD, at * MIB, block)[0] == (2048 if W <= 16 else 0)
             assert shape(W, oracle.F32, HD, at * MIB, block)[0] == 4096
+
+
+@pytest.mark.parametrize("W", [1, 3, 5, 8, 16, 32, 64])
+def test_few_tiles_where_the_table_space_is_limited(shape, W):
+    """The largest tiles that a kernel takes, whatever is fastest."""
+    for at in (64, 192, 1024):
+        wide = at >= (64 if W == 8 else 192)
+        assert shape(W, oracle.F32, RING, at * MIB, few_tiles=1)[0] == (8192 if wide else 4096)
+        if W in (8, 16, 32, 64):
+            assert shape(W, oracle.BF16, HD, at * MIB, 256, few_tiles=1)[0] == (4096 if W <= 16 else 2048)
