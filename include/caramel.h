@@ -323,8 +323,8 @@ enum {
    * CARAMEL_OPT_BLOCK and CARAMEL_OPT_STREAM_MAJOR have their defaults: ring and shuffle over 2, 4
    * and 8 workers and halving-doubling over 2 and 4 once a replica holds 64 MiB, ring and shuffle
    * over 5 workers or more (but 8) once it holds 192 MiB; 2048 (32 KiB) for bf16
-   * halving-doubling over 32 and 64 workers, or with CARAMEL_OPT_BLOCK below 1024; 4096 (64 KiB)
-   * otherwise. */
+   * halving-doubling over 32 and 64 workers, or with CARAMEL_OPT_BLOCK below 1024 or
+   * CARAMEL_OPT_STREAM_MAJOR below 4; 4096 (64 KiB) otherwise. */
   CARAMEL_OPT_TILE_VECS = 2,
   /* Upper bound on workgroups per reduce launch (0 = one workgroup per tile). */
   CARAMEL_OPT_MAX_GRID = 3,
@@ -354,15 +354,16 @@ enum {
   /* Bytes per replica from which a run is cut into long tiles.  Default 0 = chosen at
    * caramel_bind: 16 KiB, or, if a replica holds less than 32 MiB in all, no long tiles at all
    * (so small a job is over before the one-replica-at-a-time walk of a long tile pays off); none
-   * either for bf16 halving-doubling over 32 and 64 workers (there is no walk for it), unless the
-   * tables would not fit CARAMEL_STATIC_TABLE_BYTES.
+   * either for halving-doubling over 32 and 64 workers in bf16 (there is no walk for it), and in fp32 if
+   * CARAMEL_OPT_STREAM_MAJOR is 0 or 2, unless the tables would not fit CARAMEL_STATIC_TABLE_BYTES.
    * 1: every run is long; a huge value: every run is small. */
   CARAMEL_OPT_LONG_RUN_BYTES = 11,
   /* Long tiles: non-zero selects the stream-major kernel, which walks the workers one replica at
    * a time; the value (2, 4 or 8, default 8) is the most vectors a lane keeps per worker: a tile
    * of block * value vectors is walked in one go.  8 exists for fp32 sums in ring and shuffle order
    * and for fp32 halving-doubling over 2 and 4 workers; otherwise 4 is used.  0 fetches all
-   * workers' values at once. */
+   * workers' values at once.  Ring and shuffle over other numbers of workers than 1, 2, 4, 8 and 16
+   * are always walked, four vectors per lane at least. */
   CARAMEL_OPT_STREAM_MAJOR = 12,
   /* PER_UNIT launches over long tiles: like CARAMEL_OPT_LAUNCH_MIN_BYTES.  Default 64 MiB. */
   CARAMEL_OPT_LONG_LAUNCH_MIN_BYTES = 13,

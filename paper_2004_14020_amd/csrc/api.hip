@@ -270,6 +270,11 @@ int run_reduce(caramel_plan* p, const Binding& bd, const DeviceTables& dt, bool 
   } else if (lng && bd.shape.split_tiles && bd.shape.max_splits) {
     a.stream_major = 1;  // the option was changed after these tables were built, and only the walk takes split tiles
   }
+  // world sizes without a kernel that fetches all values at once always walk, four vectors per lane at
+  // least (3 x 50 MiB 55.9 us, 62 with two or one; 32 x 50 MiB bf16 588 / 690)
+  const uint32_t W = a.world;
+  const bool at_once = W == 1 || W == 2 || W == 4 || W == 8 || W == 16;
+  if (lng && !at_once && (!a.tree || a.stream_major)) a.stream_major = std::max(a.stream_major, 4u);
   a.max_grid = p->opt.max_grid;
   if (tracing())
     std::fprintf(stderr,

@@ -160,9 +160,11 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
   ts.split_tiles = split_tiles && c.pattern == CARAMEL_PATTERN_RING && (ts.small_splits || ts.max_splits);
   const uint64_t replica_bytes = p.replica_elems * p.elem_size();
   //  * halving-doubling over 32 and 64 workers in bf16 has no walk (the partial sums leave room for too
-  //    short bursts): small tiles throughout (32 x 33 MiB 449 -> 433 us), unless there must be few
+  //    short bursts): small tiles throughout (32 x 33 MiB 449 -> 433 us), unless there must be few; and
+  //    so in fp32 if the option leaves the walk no more than two vectors (32 x 50 MiB 685 -> 664)
   const bool tree = c.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
-  const bool no_walk = tree && c.dtype == CARAMEL_BF16 && c.world >= 32;
+  const bool bf16_tree = tree && c.dtype == CARAMEL_BF16;
+  const bool no_walk = tree && c.world >= 32 && (bf16_tree || stream_major < 4);
   if (ts.long_run_bytes == 0)
     ts.long_run_bytes = replica_bytes < (32u << 20) || (no_walk && !few_tiles) ? ~uint64_t(0) : 16u << 10;
   if (ts.long_vecs == 0) {
@@ -172,8 +174,8 @@ void choose_shape(const HostPlan& p, bool split_tiles, uint32_t stream_major, ui
     const bool wide = c.dtype == CARAMEL_F32 && !(tree && c.world > 4) && stream_major >= 8 && block == 1024 &&
                       (few || few_tiles || c.world > 4) && replica_bytes >= (uint64_t(few ? 64 : 192) << 20);
     // a bf16 tree keeps four vectors per lane: workgroups of 512 lanes or fewer get tiles of 32 KiB (512
-    // lanes, 8 x 60 MiB 202 -> 194 us, 2 x 60 MiB 48.9 -> 45.4)
-    const bool narrow = no_walk || (tree && c.dtype == CARAMEL_BF16 && block < 1024 && !few_tiles);
+    // lanes, 8 x 60 MiB 202 -> 194 us, 2 x 60 MiB 48.9 -> 45.4), and so do shorter walks
+    const bool narrow = bf16_tree && (c.world >= 32 || ((block < 1024 || stream_major < 4) && !few_tiles));
     ts.long_vecs = wide ? 8192 : (narrow ? 2048 : 4096);
   }
 }

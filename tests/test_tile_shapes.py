@@ -23,8 +23,8 @@ def shape(tmp_path_factory):
                     os.path.join(ROOT, "tests", "host", "shape_check.cpp"), os.path.join(CSRC, "plan.cpp"),
                     os.path.join(CSRC, "tiles.cpp"), "-o", exe], check=True)
 
-    def ask(world, dtype, pattern, nbytes, block=1024, few_tiles=0):
-        res = subprocess.run([exe, *map(str, (world, dtype, pattern, nbytes, block, few_tiles))], capture_output=True, text=True,
+    def ask(world, dtype, pattern, nbytes, block=1024, few_tiles=0, stream_major=8):
+        res = subprocess.run([exe, *map(str, (world, dtype, pattern, nbytes, block, few_tiles, stream_major))], capture_output=True, text=True,
                              check=True)
         return tuple(int(x) for x in res.stdout.split())
     return ask
@@ -49,6 +49,10 @@ def test_trees_without_a_walk_get_small_tiles(shape, W):
         for block in (256, 512):
             assert shape(W, oracle.BF16, HD, at * MIB, block)[0] == (2048 if W <= 16 else 0)
             assert shape(W, oracle.F32, HD, at * MIB, block)[0] == 4096
+        for vectors in (0, 2, 4):      # walks switched off, or shortened
+            short = vectors < 4
+            assert shape(W, oracle.BF16, HD, at * MIB, stream_major=vectors)[0] == (0 if W > 16 else 2048 if short else 4096)
+            assert shape(W, oracle.F32, HD, at * MIB, stream_major=vectors)[0] == (0 if W > 16 and short else 4096)
 
 
 @pytest.mark.parametrize("W", [1, 3, 5, 8, 16, 32, 64])
