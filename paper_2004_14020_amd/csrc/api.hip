@@ -18,6 +18,7 @@
 #include "kernels.hpp"
 #include "plan.hpp"
 #include "schedule.hpp"
+#include "slices.hpp"
 #include "tiles.hpp"
 
 using namespace caramel;
@@ -74,6 +75,16 @@ struct Options {
   uint64_t pipeline_min_bytes = ~uint64_t(0);  // AUTO never pipelines unless told to
   uint64_t merge_small_bytes = 1u << 20;       // one launch per stream: small tiles up to this total join the long ones
   bool split_tiles = true;                     // tiles across segment boundaries where the kernel handles them
+
+  // nothing that shapes tiles or their kernels has been asked for
+  bool tiles_left_to_library() const {
+    const Options d;
+    return shape.long_vecs == d.shape.long_vecs && shape.small_vecs == d.shape.small_vecs &&
+           shape.long_run_bytes == d.shape.long_run_bytes && shape.align_tiles == d.shape.align_tiles &&
+           shape.tail_tiles == d.shape.tail_tiles && max_grid == d.max_grid && nontemporal == d.nontemporal &&
+           unroll == d.unroll && block == d.block && small_block == d.small_block &&
+           stream_major == d.stream_major && split_tiles == d.split_tiles;
+  }
 };
 
 // Fork/join events order work between streams of the same device; no timing, and no system-scope
@@ -136,6 +147,9 @@ struct caramel_plan {
   ReduceTile* d_staged = nullptr;
   ReduceTile* d_direct = nullptr;
   CopyTile* d_copy = nullptr;
+  SliceArgs slices{};  // groups = 0: the plan is bound without slices
+  uint64_t* d_slice_addr = nullptr;
+  uint32_t* d_slice_bytes = nullptr;
   hipStream_t streams[2] = {nullptr, nullptr};
   hipEvent_t ev_fork = nullptr;
   hipEvent_t ev_join[2] = {nullptr, nullptr};
@@ -162,6 +176,11 @@ void release_device(caramel_plan* p) {
   if (p->d_staged) (void)hipFree(p->d_staged);
   if (p->d_direct) (void)hipFree(p->d_direct);
   if (p->d_copy) (void)hipFree(p->d_copy);
+  if (p->d_slice_addr) (void)hipFree(p->d_slice_addr);
+  if (p->d_slice_bytes) (void)hipFree(p->d_slice_bytes);
+  p->d_slice_addr = nullptr;
+  p->d_slice_bytes = nullptr;
+  p->slices = SliceArgs{};
   p->d_rows = nullptr;
   p->d_staged = p->d_direct = nullptr;
   p->d_copy = nullptr;
@@ -289,6 +308,23 @@ int run_reduce(caramel_plan* p, const Binding& bd, const DeviceTables& dt, bool 
   }
   Timed timer(p, lng ? CARAMEL_K_REDUCE : CARAMEL_K_REDUCE_SMALL, s, g.elems);
   HIP_TRY(launch_ring_reduce(a, s));
+  return CARAMEL_OK;
+}
+
+// Reduction in place of a job that was cut into slices at bind: one launch on the caller's stream.  An
+// option that asks for tiles, or for the pipeline, takes the tiles instead.
+bool use_slices(const caramel_plan* p, bool direct, bool pipelined) {
+  return p->slices.groups && direct && !pipelined && p->opt.launch_mode == CARAMEL_LAUNCH_AUTO &&
+         p->opt.tiles_left_to_library();
+}
+
+int run_slices(caramel_plan* p, hipStream_t s) {
+  const SliceArgs& a = p->slices;
+  if (tracing())
+    std::fprintf(stderr, "caramel: call %llu reduce  stream %p %u workgroups of %u lanes, %u slices per wavefront\n",
+                 (unsigned long long)p->call_no, (void*)s, a.groups, a.lanes, a.vecs);
+  Timed timer(p, CARAMEL_K_REDUCE_SMALL, s, p->host.replica_elems);
+  HIP_TRY(launch_slices(a, s));
   return CARAMEL_OK;
 }
 
@@ -457,7 +493,9 @@ int pipeline(caramel_plan* p, hipStream_t user, bool with_copies, bool direct) {
     for (uint32_t s = 0; s < n_lanes; ++s) seq[s].reset(new Timed(p, CARAMEL_K_SEQUENCE, lane[s]));
   if (copies)
     for (uint32_t s = 0; s < n_lanes && !rc; ++s) rc = run_copy(p, dt, false, copy_of[s], lane[s]);
-  if (!rc)
+  if (use_slices(p, direct, pipelined))
+    rc = run_slices(p, lane[0]);
+  else if (!rc)
     for (const LaunchGroup& g : launch_groups(p, p->bind, direct, pipelined)) {
       rc = run_reduce(p, p->bind, dt, direct, g, lane[g.lane]);
       if (rc) break;
@@ -799,6 +837,20 @@ void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& 
   bd.groups_stale[0] = bd.groups_stale[1] = true;
 }
 
+int bind_slices(caramel_plan* p) {
+  const HostPlan& h = p->host;
+  const uint64_t* rows = p->bind.rows.data();
+  if (!may_have_slices(h)) return CARAMEL_OK;
+  SliceTable t;
+  build_slices(h, choose_slices(h, count_slices(h, rows)), rows, t);
+  if (!t.groups) return CARAMEL_OK;
+  int rc = upload(t.addr, &p->d_slice_addr);
+  if (!rc) rc = upload(t.bytes, &p->d_slice_bytes);
+  if (!rc)
+    p->slices = SliceArgs{p->d_slice_addr, p->d_slice_bytes, t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16};
+  return rc;
+}
+
 int bind_plan(caramel_plan* p, void* const* grads, void* fused_ws) {
   if (!p || !grads) return fail(CARAMEL_EINVAL, "NULL argument");
   const HostPlan& h = p->host;
@@ -821,6 +873,7 @@ int bind_plan(caramel_plan* p, void* const* grads, void* fused_ws) {
   if (!rc) rc = upload(p->bind.tt.direct, &p->d_direct);
   if (!rc && fused_ws) rc = upload(p->bind.tt.staged, &p->d_staged);
   if (!rc && fused_ws) rc = upload(p->bind.tt.copy, &p->d_copy);
+  if (!rc && p->opt.tiles_left_to_library()) rc = bind_slices(p);
   if (rc) {
     release_device(p);
     return rc;

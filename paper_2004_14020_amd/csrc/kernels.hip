@@ -69,12 +69,15 @@ __device__ __forceinline__ void st(gvec_ptr base, uint32_t byte_off, u32x4 v) {
 __device__ __forceinline__ f32x4 bits_to_f32(u32x4 v) { return __builtin_bit_cast(f32x4, v); }
 __device__ __forceinline__ u32x4 f32_to_bits(f32x4 v) { return __builtin_bit_cast(u32x4, v); }
 
-// fp32 -> bf16, round to nearest, ties to even; NaN stays a (quiet) NaN.
-__device__ __forceinline__ uint32_t bf16_rne(float f) {
-  const uint32_t b = __float_as_uint(f);
-  const uint32_t r = (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
-  return (f != f) ? ((b >> 16) | 0x40u) : r;
+// fp32 -> bf16, round to nearest, ties to even; NaN stays a (quiet) NaN.  Two values to a conversion
+// instruction (it equals the integer arithmetic  (b + 0x7FFF + (b >> 16 & 1)) >> 16,  NaN: b >> 16 | 0x40,
+// on all 2^32 bit patterns, in both halves), where that arithmetic takes six instructions a value.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
+__device__ __forceinline__ uint32_t bf16_rne(float f) { return bf16_pair(f, f) & 0xFFFFu; }
 
 // Running ring sum of one 16-byte vector.  F32: four lanes.  BF16: eight values, kept as the
 // even-indexed (low halves) and odd-indexed (high halves) quartets, widened exactly.
@@ -124,10 +127,10 @@ struct Chain {
     if constexpr (BF16) {
       const f32x4 ya = a * inv_w, yb = b * inv_w;
       u32x4 r;
-      r.x = bf16_rne(ya.x) | (bf16_rne(yb.x) << 16);
-      r.y = bf16_rne(ya.y) | (bf16_rne(yb.y) << 16);
-      r.z = bf16_rne(ya.z) | (bf16_rne(yb.z) << 16);
-      r.w = bf16_rne(ya.w) | (bf16_rne(yb.w) << 16);
+      r.x = bf16_pair(ya.x, yb.x);
+      r.y = bf16_pair(ya.y, yb.y);
+      r.z = bf16_pair(ya.z, yb.z);
+      r.w = bf16_pair(ya.w, yb.w);
       return r;
     } else {
       return f32_to_bits(a * inv_w);
@@ -787,6 +790,133 @@ k_copy(const CopyTile* __restrict__ tiles, const uint64_t* __restrict__ rows, ui
   for (uint32_t e = nvec * VE + lane; e < end; e += kCopyBlock) de[e] = (e < t.n_elems) ? se[e] : E(0);
 }
 
+// ------------------------------------------------------------------------------------------
+// Chain orders over slices (ReduceTile's counterpart for small jobs: SliceTable).
+//
+// The tables are read through the constant address space: scalar loads, also between stores.
+typedef const __attribute__((address_space(4))) uint64_t* const_u64_ptr;
+typedef const __attribute__((address_space(4))) uint32_t* const_u32_ptr;
+
+// One wavefront's slices: where they lie, how long they are, and how their results go out.
+template <bool BF16, int N>
+struct Slices {
+  const_u64_ptr addr;
+  const_u32_ptr bytes;
+  uint32_t W, off;  // off: this lane's vector
+  uint32_t len[N], odd;
+  __device__ __forceinline__ Slices(const uint64_t* a, const uint32_t* b, uint32_t workers) : W(workers) {
+    const uint32_t wave = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) / 64);
+    addr = (const_u64_ptr)a + size_t(wave) * W * N;
+    bytes = (const_u32_ptr)b + size_t(wave) * (N + 1);
+    off = threadIdx.x % 64 * 16;
+#pragma unroll
+    for (int u = 0; u < N; ++u) len[u] = bytes[u];
+    odd = BF16 ? bytes[N] : 0u;
+  }
+  // A slice is a buffer of its own length: lanes and dwords beyond it read zeros and store nothing.
+  static __device__ __forceinline__ __amdgpu_buffer_rsrc_t res(uint64_t a, uint32_t n) {
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(a), 0, int(n), kRawBuffer);
+  }
+  // CW: the number of workers, 0 if known at run time only
+  template <int CW>
+  __device__ __forceinline__ void put(const u32x4 (&y)[N]) {
+    if constexpr (BF16) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) len[u] -= 4 * (odd >> u & 1u);  // whole dwords
+    }
+#pragma unroll(CW ? CW : 2)
+    for (uint32_t k = 0; k < W; ++k)
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        __builtin_amdgcn_raw_buffer_store_b128(y[u], res(addr[k * N + u], len[u]), int(off), 0, kStoreBits<kThrough>);
+    if (BF16 && odd) {  // half a dword is left of some slice
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        if ((odd >> u & 1u) && off == (len[u] & ~15u)) {
+          const uint32_t q = (len[u] & 15u) / 4;
+          const uint32_t v = q == 0 ? y[u].x : (q == 1 ? y[u].y : (q == 2 ? y[u].z : y[u].w));
+#pragma unroll(CW ? CW : 4)
+          for (uint32_t k = 0; k < W; ++k) *reinterpret_cast<gu16_ptr>(addr[k * N + u] + len[u]) = uint16_t(v);
+        }
+    }
+  }
+};
+
+template <bool BF16, int N, int LANES>
+__global__ void __launch_bounds__(LANES) __attribute__((amdgpu_waves_per_eu(LANES / 256, LANES / 256)))
+k_slices(const uint64_t* addr_table, const uint32_t* bytes_table, uint32_t W, float inv_w) {
+  Slices<BF16, N> sl(addr_table, bytes_table, W);
+  uint64_t a[N];  // the slices in the next worker, looked up a step ahead
+  auto look = [&](uint32_t k) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) a[u] = sl.addr[k * N + u];
+  };
+  Chain<BF16> acc[N];
+  u32x4 buf[2][N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) acc[u].zero();
+  auto load = [&](uint32_t k, int j) {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      buf[j][u] = __builtin_amdgcn_raw_buffer_load_b128(sl.res(a[u], sl.len[u]), int(sl.off), 0, kLoadBits<kThrough>);
+    __builtin_amdgcn_sched_barrier(0);
+    look(k + 1 < W ? k + 1 : 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto add = [&](int j) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      acc[u].add(buf[j][u]);
+      acc[u].pin();
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  look(0);
+  load(0, 0);
+  uint32_t k = 0;
+#pragma unroll 1
+  for (; k + 2 < W; k += 2) {
+    load(k + 1, 1);
+    add(0);
+    load(k + 2, 0);
+    add(1);
+  }
+  if (k + 1 < W) load(k + 1, 1);
+  add(0);
+  if (k + 1 < W) add(1);
+  u32x4 y[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) y[u] = acc[u].finish(inv_w);
+  sl.template put<0>(y);
+}
+
+// One slice per wavefront.  CW: the number of workers, 0 if known at run time only.  The values of up to
+// kAhead workers are fetched at once.
+template <bool BF16, int CW>
+__global__ void __launch_bounds__(256)
+k_slice(const uint64_t* addr_table, const uint32_t* bytes_table, uint32_t workers, float inv_w) {
+  const uint32_t W = CW ? uint32_t(CW) : workers;
+  Slices<BF16, 1> sl(addr_table, bytes_table, W);
+  constexpr int kAhead = CW ? CW : 8;
+  Chain<BF16> acc;
+  acc.zero();
+#pragma unroll 1
+  for (uint32_t k0 = 0; k0 < W; k0 += kAhead) {
+    u32x4 x[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const bool in = (CW && CW % kAhead == 0) || k0 + i < W;
+      x[i] = __builtin_amdgcn_raw_buffer_load_b128(sl.res(sl.addr[k0 + i], in ? sl.len[0] : 0u), int(sl.off), 0, kLoadBits<kThrough>);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if ((CW && CW % kAhead == 0) || k0 + i < W) acc.add(x[i]);
+  }
+  const u32x4 y[1] = {acc.finish(inv_w)};
+  sl.template put<CW>(y);
+}
+
 template <int W, int U>
 hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
 #define CARAMEL_GO(BF, P, TR) \
@@ -908,6 +1038,34 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
   }
 #undef CARAMEL_TREE
   return hipGetLastError();
+}
+
+hipError_t launch_slices(const SliceArgs& a, hipStream_t s) {
+  const float inv_w = 1.0f / float(a.world);
+  const dim3 grid(a.groups), lanes(a.lanes);
+#define CARAMEL_SLICES(BF, N, L) \
+  if (a.bf16 == BF && a.vecs == N && a.lanes == L) { \
+    hipLaunchKernelGGL((k_slices<BF, N, L>), grid, lanes, 0, s, a.addr, a.bytes, a.world, inv_w); \
+    return hipGetLastError(); \
+  }
+#define CARAMEL_SLICE(CW) \
+  if (a.vecs == 1 && a.lanes == 256 && (CW == 0 || a.world == CW)) { \
+    if (a.bf16) hipLaunchKernelGGL((k_slice<true, CW>), grid, lanes, 0, s, a.addr, a.bytes, a.world, inv_w); \
+    else hipLaunchKernelGGL((k_slice<false, CW>), grid, lanes, 0, s, a.addr, a.bytes, a.world, inv_w); \
+    return hipGetLastError(); \
+  }
+  CARAMEL_SLICE(2) CARAMEL_SLICE(3) CARAMEL_SLICE(4) CARAMEL_SLICE(8) CARAMEL_SLICE(16) CARAMEL_SLICE(0)
+  CARAMEL_SLICES(false, 4, 256) CARAMEL_SLICES(false, 6, 256) CARAMEL_SLICES(false, 8, 256) CARAMEL_SLICES(false, 10, 256)
+  CARAMEL_SLICES(false, 12, 256) CARAMEL_SLICES(false, 14, 256) CARAMEL_SLICES(false, 16, 256) CARAMEL_SLICES(false, 18, 256)
+  CARAMEL_SLICES(false, 20, 256)
+  CARAMEL_SLICES(true, 4, 256) CARAMEL_SLICES(true, 6, 256) CARAMEL_SLICES(true, 8, 256) CARAMEL_SLICES(true, 10, 256)
+  CARAMEL_SLICES(true, 12, 256) CARAMEL_SLICES(true, 14, 256) CARAMEL_SLICES(true, 16, 256)
+  CARAMEL_SLICES(false, 14, 512) CARAMEL_SLICES(false, 16, 512) CARAMEL_SLICES(false, 18, 512) CARAMEL_SLICES(false, 20, 512)
+  CARAMEL_SLICES(false, 5, 1024) CARAMEL_SLICES(false, 6, 1024) CARAMEL_SLICES(false, 7, 1024) CARAMEL_SLICES(false, 8, 1024)
+  CARAMEL_SLICES(true, 4, 1024) CARAMEL_SLICES(true, 5, 1024) CARAMEL_SLICES(true, 6, 1024)
+#undef CARAMEL_SLICE
+#undef CARAMEL_SLICES
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {

@@ -31,6 +31,15 @@ struct ReduceArgs {
                           // fp32 chains and fp32 trees over 2 and 4 workers, everything else gets 4
 };
 
+struct SliceArgs {
+  const uint64_t* addr;   // device (SliceTable)
+  const uint32_t* bytes;  // device
+  uint32_t groups;        // workgroups
+  uint32_t lanes, vecs;   // SliceShape
+  uint32_t world;
+  bool bf16;
+};
+
 struct CopyArgs {
   const CopyTile* tiles;  // device
   const uint64_t* rows;   // device
@@ -44,6 +53,8 @@ struct CopyArgs {
 
 // Ring reduce-scatter arithmetic + 1/W scaling + all-gather for a range of tiles.
 hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t stream);
+// The same, in chain orders, for a job that was cut into slices.
+hipError_t launch_slices(const SliceArgs& a, hipStream_t stream);
 // Segmented gather (pack) or scatter (unpack) driven by the copy-tile table.
 hipError_t launch_copy(const CopyArgs& a, hipStream_t stream);
 

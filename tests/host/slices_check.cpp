@@ -1,0 +1,126 @@
+// Host-only check of the slice tables, built with AddressSanitizer and UBSan: slices cover every element
+// of every tensor exactly once and nothing else, each stays inside its tensor and inside one aligned block
+// of kSliceBytes in the replicas that share a position, and every element is added in the order of workers that
+// the tile tables (the general path) give it.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <random>
+#include <string>
+#include <vector>
+
+#include "plan.hpp"
+#include "slices.hpp"
+#include "tiles.hpp"
+
+using namespace caramel;
+
+#define CHECK(c)                                                \
+  do {                                                          \
+    if (!(c)) {                                                 \
+      std::printf("FAIL %s:%d  %s\n", __FILE__, __LINE__, #c);  \
+      std::exit(1);                                             \
+    }                                                           \
+  } while (0)
+
+static std::map<std::string, int> shapes;
+
+static void check(const HostPlan& p, const SliceShape& shape, const std::vector<uint64_t>& rows, bool alike) {
+  const uint32_t W = p.cfg.world, V = shape.vecs, waves = shape.lanes / 64;
+  const uint64_t es = p.elem_size();
+  // the general path: first worker of every element
+  TileShape ts;
+  ts.long_vecs = 4096;
+  ts.long_run_bytes = ~uint64_t(0);
+  TileTables tt;
+  build_tiles(p, ts, tt, rows.data());
+  std::vector<std::vector<uint8_t>> first(p.tensor_elems.size()), seen(p.tensor_elems.size());
+  for (size_t t = 0; t < first.size(); ++t) first[t].assign(p.tensor_elems[t], 255), seen[t].assign(p.tensor_elems[t], 0);
+  for (const ReduceTile& t : tt.direct)
+    for (uint32_t k = 0; k < t.n_elems; ++k) first[t.row][t.vec_off * (16 / es) + k] = uint8_t(t.first);
+
+  SliceTable st;
+  build_slices(p, shape, rows.data(), st);
+  CHECK(st.lanes == shape.lanes && st.vecs == V && shape.share <= waves * V);
+  CHECK(st.addr.size() == size_t(st.groups) * waves * V * W + 16 && st.bytes.size() == size_t(st.groups) * waves * (V + 1));
+  std::map<uint64_t, size_t> at;  // worker 0's tensors by address
+  for (size_t t = 0; t < first.size(); ++t) at[rows[t * W]] = t;
+  uint64_t slices = 0;
+  for (size_t wave = 0; wave < size_t(st.groups) * waves; ++wave) {
+    const uint32_t odd = st.bytes[wave * (V + 1) + V];
+    CHECK(odd >> V == 0);
+    for (uint32_t u = 0; u < V; ++u) {
+      const uint32_t bytes = st.bytes[wave * (V + 1) + u], whole = bytes - 2 * (odd >> u & 1);
+      CHECK(bytes % 4 == 0 && bytes <= kSliceBytes && (bytes || !(odd >> u & 1)));
+      auto address = [&](uint32_t k) { return st.addr[(wave * W + k) * V + u]; };
+      if (!bytes) {
+        for (uint32_t k = 0; k < W; ++k) CHECK(address(k) == 0);
+        continue;
+      }
+      ++slices;
+      // which step reads worker 0, hence which tensor and place
+      size_t tensor = first.size();
+      uint64_t off = 0;
+      uint32_t step = W;
+      for (uint32_t k = 0; k < W && step == W; ++k) {
+        auto it = at.upper_bound(address(k));
+        if (it == at.begin()) continue;
+        --it;
+        const uint64_t d = address(k) - it->first;
+        if (d < p.tensor_elems[it->second] * es) tensor = it->second, off = d, step = k;
+      }
+      CHECK(step < W && off % 16 == 0 && off + whole <= p.tensor_elems[tensor] * es);
+      const uint32_t f = (W - step) % W;
+      for (uint32_t k = 0; k < W; ++k) CHECK(address(k) == rows[tensor * W + (f + k) % W] + off);
+      if (alike) CHECK(address(0) / kSliceBytes == (address(0) + whole - 1) / kSliceBytes);
+      for (uint64_t e = off / es; e < (off + whole) / es; ++e) {
+        CHECK(!seen[tensor][e] && first[tensor][e] == f);
+        seen[tensor][e] = 1;
+      }
+    }
+  }
+  CHECK(slices == count_slices(p, rows.data()));
+  for (const auto& s : seen)
+    for (uint8_t x : s) CHECK(x == 1);
+}
+
+int main() {
+  std::mt19937_64 rng(11);
+  auto pick = [&](std::initializer_list<uint64_t> xs) { return *(xs.begin() + rng() % xs.size()); };
+  for (int it = 0; it < 260; ++it) {
+    caramel_config cfg{};
+    cfg.world = uint32_t(pick({1, 2, 3, 4, 8, 12, 16, 33, 64}));
+    cfg.dtype = uint32_t(rng() % 2);
+    cfg.align_bytes = uint32_t(pick({16, 16, 64, 256}));
+    cfg.batch_threshold_bytes = pick({0, 1024, 65536, 1 << 20});
+    cfg.split_mode = uint32_t(pick({CARAMEL_SPLIT_NONE, CARAMEL_SPLIT_FIXED, CARAMEL_SPLIT_ADAPTIVE}));
+    cfg.split_bytes = pick({4096, 102400, 1 << 20});
+    cfg.max_depth = 8;
+    cfg.num_streams = uint32_t(pick({1, 2}));
+    cfg.pattern = uint32_t(pick({CARAMEL_PATTERN_RING, CARAMEL_PATTERN_RING, CARAMEL_PATTERN_SHUFFLE}));
+    const bool large = it % 13 == 0;  // enough slices for every shape
+    std::vector<uint64_t> elems(1 + rng() % (large ? 3 : 40));
+    for (uint64_t& e : elems) e = large ? 700001 + rng() % 2500000 : pick({1, 2, 3, 17, 100, 257, 1000, 4099, 16384, 70001});
+    HostPlan p;
+    std::string why;
+    CHECK(build_host_plan(cfg, elems.data(), uint32_t(elems.size()), nullptr, 0.0, 0.0, p, why) == CARAMEL_OK);
+    const bool alike = rng() % 2;
+    std::vector<uint64_t> rows((elems.size() + 1) * cfg.world, 0);
+    for (size_t t = 0; t < elems.size(); ++t) {
+      const uint64_t common = rng() % 4096;
+      for (uint32_t w = 0; w < cfg.world; ++w)
+        rows[t * cfg.world + w] = (uint64_t(w + 1) << 40) + (uint64_t(t) << 32) + (alike ? common : rng() % 4096) * cfg.align_bytes;
+    }
+    const SliceShape own = choose_slices(p, count_slices(p, rows.data()));
+    if (own.vecs) {
+      CHECK(own.share && own.share <= own.lanes / 64 * own.vecs);
+      ++shapes[std::to_string(own.lanes) + (own.vecs == 1 ? " x 1" : " x n")];
+      check(p, own, rows, alike);
+    }
+    const uint32_t lanes = uint32_t(pick({256, 512, 1024})), vecs = uint32_t(pick({1, 4, 5, 20}));
+    check(p, SliceShape{lanes, vecs, uint32_t(1 + rng() % (lanes / 64 * vecs))}, rows, alike);
+  }
+  CHECK(shapes["256 x 1"] && shapes["256 x n"]);
+  std::printf("slices_check ok\n");
+  return 0;
+}
