@@ -143,13 +143,9 @@ struct caramel_plan {
   bool has_ws = false;
   int device = -1;  // the device that was current at bind: tables, stream and events live there
   Binding bind;
-  uint64_t* d_rows = nullptr;
-  ReduceTile* d_staged = nullptr;
-  ReduceTile* d_direct = nullptr;
-  CopyTile* d_copy = nullptr;
+  unsigned char* d_tables = nullptr;  // all of them
+  DeviceTables dt;
   SliceArgs slices{};  // groups = 0: the plan is bound without slices
-  uint64_t* d_slice_addr = nullptr;
-  uint32_t* d_slice_bytes = nullptr;
   hipStream_t streams[2] = {nullptr, nullptr};
   hipEvent_t ev_fork = nullptr;
   hipEvent_t ev_join[2] = {nullptr, nullptr};
@@ -166,24 +162,16 @@ struct caramel_plan {
   std::vector<std::pair<uint64_t, hipEvent_t>> call_base;
   caramel_kernel_stat stats[CARAMEL_K_COUNT] = {};
 
-  DeviceTables tables() const { return DeviceTables{d_rows, d_staged, d_direct, d_copy}; }
+  DeviceTables tables() const { return dt; }
 };
 
 namespace {
 
 void release_device(caramel_plan* p) {
-  if (p->d_rows) (void)hipFree(p->d_rows);
-  if (p->d_staged) (void)hipFree(p->d_staged);
-  if (p->d_direct) (void)hipFree(p->d_direct);
-  if (p->d_copy) (void)hipFree(p->d_copy);
-  if (p->d_slice_addr) (void)hipFree(p->d_slice_addr);
-  if (p->d_slice_bytes) (void)hipFree(p->d_slice_bytes);
-  p->d_slice_addr = nullptr;
-  p->d_slice_bytes = nullptr;
+  if (p->d_tables) (void)hipFree(p->d_tables);
+  p->d_tables = nullptr;
+  p->dt = DeviceTables{};
   p->slices = SliceArgs{};
-  p->d_rows = nullptr;
-  p->d_staged = p->d_direct = nullptr;
-  p->d_copy = nullptr;
   p->bound = false;
 }
 
@@ -199,14 +187,17 @@ void drop_events(caramel_plan* p) {
   p->spare.clear();
 }
 
-template <typename T>
-int upload(const std::vector<T>& v, T** dst) {
-  *dst = nullptr;
-  if (v.empty()) return CARAMEL_OK;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(dst), v.size() * sizeof(T)));
-  HIP_TRY(hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
-  return CARAMEL_OK;
-}
+// The tables of a binding on their way to the device: one allocation and one copy for all of them.
+struct Upload {
+  std::vector<unsigned char> host;
+  template <typename T>
+  size_t add(const std::vector<T>& v) {
+    const size_t at = (host.size() + 255) / 256 * 256;
+    host.resize(at + v.size() * sizeof(T));
+    if (!v.empty()) std::memcpy(host.data() + at, v.data(), v.size() * sizeof(T));
+    return at;
+  }
+};
 
 hipEvent_t take_event(caramel_plan* p) {
   if (!p->spare.empty()) {
@@ -837,18 +828,30 @@ void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& 
   bd.groups_stale[0] = bd.groups_stale[1] = true;
 }
 
-int bind_slices(caramel_plan* p) {
+int upload_tables(caramel_plan* p, bool staged) {
   const HostPlan& h = p->host;
-  const uint64_t* rows = p->bind.rows.data();
-  if (!may_have_slices(h)) return CARAMEL_OK;
+  const Binding& bd = p->bind;
+  const std::vector<ReduceTile> none;
   SliceTable t;
-  build_slices(h, choose_slices(h, count_slices(h, rows)), rows, t);
-  if (!t.groups) return CARAMEL_OK;
-  int rc = upload(t.addr, &p->d_slice_addr);
-  if (!rc) rc = upload(t.bytes, &p->d_slice_bytes);
-  if (!rc)
-    p->slices = SliceArgs{p->d_slice_addr, p->d_slice_bytes, t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16};
-  return rc;
+  SliceShape shape;
+  if (p->opt.tiles_left_to_library() && may_have_slices(h)) {
+    shape = choose_slices(h, count_slices(h, bd.rows.data()));
+    build_slices(h, shape, bd.rows.data(), t);
+  }
+  Upload up;
+  const size_t at = up.add(t.at), bytes = up.add(t.bytes), rows = up.add(bd.rows), direct = up.add(bd.tt.direct);
+  const size_t on_fused = up.add(staged ? bd.tt.staged : none), copy = staged ? up.add(bd.tt.copy) : 0;
+  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&p->d_tables), up.host.size()));
+  unsigned char* d = p->d_tables;
+  HIP_TRY(hipMemcpy(d, up.host.data(), up.host.size(), hipMemcpyHostToDevice));
+  p->dt.rows = reinterpret_cast<const uint64_t*>(d + rows);
+  p->dt.direct = reinterpret_cast<const ReduceTile*>(d + direct);
+  p->dt.staged = reinterpret_cast<const ReduceTile*>(d + on_fused);
+  p->dt.copy = reinterpret_cast<const CopyTile*>(d + copy);
+  p->slices = SliceArgs{reinterpret_cast<const uint32_t*>(d + at), reinterpret_cast<const uint32_t*>(d + bytes), t.base,
+                        t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16,
+                        shape.through ? kThrough : kStream};
+  return CARAMEL_OK;
 }
 
 int bind_plan(caramel_plan* p, void* const* grads, void* fused_ws) {
@@ -869,11 +872,7 @@ int bind_plan(caramel_plan* p, void* const* grads, void* fused_ws) {
   p->device = dev;
 
   fill_binding(p, std::move(rows), p->bind);
-  int rc = upload(p->bind.rows, &p->d_rows);
-  if (!rc) rc = upload(p->bind.tt.direct, &p->d_direct);
-  if (!rc && fused_ws) rc = upload(p->bind.tt.staged, &p->d_staged);
-  if (!rc && fused_ws) rc = upload(p->bind.tt.copy, &p->d_copy);
-  if (!rc && p->opt.tiles_left_to_library()) rc = bind_slices(p);
+  const int rc = upload_tables(p, fused_ws != nullptr);
   if (rc) {
     release_device(p);
     return rc;

@@ -32,12 +32,14 @@ struct ReduceArgs {
 };
 
 struct SliceArgs {
-  const uint64_t* addr;   // device (SliceTable)
+  const uint32_t* at;     // device (SliceTable)
   const uint32_t* bytes;  // device
+  uint64_t base;
   uint32_t groups;        // workgroups
   uint32_t lanes, vecs;   // SliceShape
   uint32_t world;
   bool bf16;
+  Policy policy;          // kStream or kThrough
 };
 
 struct CopyArgs {

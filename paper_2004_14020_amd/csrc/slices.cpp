@@ -5,14 +5,22 @@
 namespace caramel {
 namespace {
 
-// Calls f(row, first worker, byte offset in the row, bytes) for every slice, in unit order.  Slices end on
-// multiples of kSliceBytes in memory, in most replicas if they lie differently.
+// A piece of a row inside one ring segment.
+struct Piece {
+  uint32_t row, first;  // `first`: worker that is added first
+  uint64_t at, end;     // bytes from the start of the row
+  uint64_t phase;       // position of the row's start inside an aligned block of kSliceBytes: the same in
+                        // every replica, or that of most
+  uint64_t slices() const { return (end + phase + kSliceBytes - 1) / kSliceBytes - (at + phase) / kSliceBytes; }
+};
+
+// Calls f(piece) for every piece of every unit, in unit order.
 template <typename F>
-void for_each_slice(const HostPlan& p, const uint64_t* row_addr, F&& f) {
+void for_each_piece(const HostPlan& p, const uint64_t* row_addr, F&& f) {
   const uint32_t W = p.cfg.world;
   const uint64_t es = p.elem_size();
   uint32_t phase_row = ~0u;
-  uint64_t phase = 0;  // position of row `phase_row` inside a block of kSliceBytes
+  uint64_t phase = 0;
   auto common_phase = [&](uint32_t row) {
     if (row == phase_row) return phase;
     const uint64_t* a = row_addr + size_t(row) * W;
@@ -27,12 +35,7 @@ void for_each_slice(const HostPlan& p, const uint64_t* row_addr, F&& f) {
     return phase;
   };
   auto cut = [&](uint32_t row, uint64_t row_elem, uint64_t n, uint32_t first) {
-    const uint64_t ph = common_phase(row), end = (row_elem + n) * es;
-    for (uint64_t at = row_elem * es; at < end;) {
-      const uint64_t len = std::min(kSliceBytes - (ph + at) % kSliceBytes, end - at);
-      f(row, first, at, uint32_t(len));
-      at += len;
-    }
+    f(Piece{row, first, row_elem * es, (row_elem + n) * es, common_phase(row)});
   };
   for (uint32_t ui = 0; ui < p.units.size(); ++ui) {
     const caramel_unit& u = p.units[ui];
@@ -65,7 +68,7 @@ bool may_have_slices(const HostPlan& p) {
 
 uint64_t count_slices(const HostPlan& p, const uint64_t* row_addr) {
   uint64_t n = 0;
-  for_each_slice(p, row_addr, [&](uint32_t, uint32_t, uint64_t, uint32_t) { ++n; });
+  for_each_piece(p, row_addr, [&](const Piece& c) { n += c.slices(); });
   return n;
 }
 
@@ -83,28 +86,35 @@ uint64_t count_slices(const HostPlan& p, const uint64_t* row_addr) {
 //  * Above one round of 256 lanes, fp32: from 16 workers on one round of 512 lanes (24 workers 26 MiB 247 / 238, 32
 //    workers 31 MiB 414 / 375); 8 to 15 workers 1024 lanes in equal shares (8 workers 31 MiB 100 / 90, 12 workers
 //    144 / 136), but where that comes to seven vectors per lane again 512 lanes (12 workers 27 MiB 122.5 / 125.4,
-//    with 512 lanes 122).  Up to 7 workers, and with bf16 but for 9 to 24 workers, one vector per lane
+//    with 512 lanes 122).  Up to 7 workers, and with bf16 but for 9 to 24 workers from 20 MiB on, one vector per lane
 //    in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; 8 workers bf16 98 / 92, 1024
 //    lanes 96; 12 workers bf16 143 / 139, one vector 142.5).  One worker has tiles there (26 MiB 11.5 / 13.0).
+//  * Stores: what one round writes is left to the last-level cache, where it fits (8 workers 4 MiB 12.6 written
+//    through, 11.6; 2 workers 12 MiB 9.2 / 8.8; called one at a time 8 x 15 MB 56.0 / 53.0; 32 workers 12 MiB, 384
+//    MiB in all, 142 / 144).  Longer jobs write while others read, and are better off through (4 workers 30
+//    MiB 43.8 / 44.9, 8 workers 87.4 / 90.1).
 SliceShape choose_slices(const HostPlan& p, uint64_t n) {
   const uint32_t W = p.cfg.world;
+  const uint64_t replica_bytes = p.replica_elems * p.elem_size();
   // (the table of a job of very many tiny tensors would outgrow them)
   if (!may_have_slices(p) || n == 0 || n * W > (1u << 23)) return {};
   const bool bf16 = p.cfg.dtype == CARAMEL_BF16;
   const uint32_t most = bf16 ? 16 : 20;  // vectors per lane that fit the registers
   auto even = [](uint64_t v, uint32_t lo, uint32_t hi) { return std::clamp(uint32_t((v + 1) / 2 * 2), lo, hi); };
-  SliceShape s{256, 1, 4};
+  SliceShape s{256, 1, 4, W * replica_bytes > (uint64_t(256) << 20)};
   if (n <= (W <= 4 ? 3328u : 2304u)) return s;
   if (n <= uint64_t(4) * most * kComputeUnits) {
     s.vecs = even((n + 849) / 850, 4, most);
     s.share = 4 * s.vecs;
-  } else if (W == 1) {
-    return {};
-  } else if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
+    return s;
+  }
+  if (W == 1) return {};
+  s.through = true;
+  if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
     s.lanes = 512;
     s.vecs = even((n + 1549) / 1550, 14, most);
     s.share = 8 * s.vecs;
-  } else if (bf16 ? W > 8 && W <= 24 : W >= 8) {
+  } else if (bf16 ? W > 8 && W <= 24 && n > 20480 : W >= 8) {
     const uint64_t full = 16 * (bf16 ? 6 : 8) * kComputeUnits, rounds = (n + full - 1) / full;
     s.lanes = 1024;
     s.share = uint32_t((n + rounds * kComputeUnits - 1) / (rounds * kComputeUnits));
@@ -118,21 +128,36 @@ void build_slices(const HostPlan& p, const SliceShape& shape, const uint64_t* ro
   if (!shape.vecs) return;
   const uint32_t W = p.cfg.world, V = shape.vecs, waves = shape.lanes / 64;
   const uint64_t n = count_slices(p, row_addr);
+  uint64_t lo = ~uint64_t(0), hi = 0;
+  for (size_t t = 0; t < p.tensor_elems.size(); ++t)
+    for (uint32_t w = 0; w < W; ++w) {
+      const uint64_t a = row_addr[t * W + w];
+      lo = std::min(lo, a);
+      hi = std::max(hi, a + p.tensor_elems[t] * p.elem_size());
+    }
+  if ((hi - lo) >> 36) return;
+  out.base = lo;
   out.lanes = shape.lanes;
   out.vecs = V;
   out.groups = uint32_t((n + shape.share - 1) / shape.share);
-  // (sixteen more addresses: the kernel for one slice per wavefront looks eight workers up at a time)
-  out.addr.assign(size_t(out.groups) * waves * V * W + 16, 0);
+  // (sixteen more: the kernel for one slice per wavefront looks eight workers up at a time)
+  out.at.assign(size_t(out.groups) * waves * V * W + 16, 0);
   out.bytes.assign(size_t(out.groups) * waves * (V + 1), 0);
   uint64_t i = 0;
-  for_each_slice(p, row_addr, [&](uint32_t row, uint32_t first, uint64_t at, uint32_t len) {
-    const uint32_t r = uint32_t(i % shape.share), u = r / waves;
-    const size_t wave = size_t(i / shape.share) * waves + r % waves;
-    out.bytes[wave * (V + 1) + u] = (len + 3) & ~3u;
-    if (len & 3u) out.bytes[wave * (V + 1) + V] |= 1u << u;
-    for (uint32_t k = 0; k < W; ++k)
-      out.addr[(wave * W + k) * V + u] = row_addr[size_t(row) * W + (first + k) % W] + at;
-    ++i;
+  std::vector<uint64_t> base(W);
+  for_each_piece(p, row_addr, [&](const Piece& c) {
+    for (uint32_t k = 0; k < W; ++k) base[k] = row_addr[size_t(c.row) * W + (c.first + k) % W] - lo;
+    for (uint64_t at = c.at, len; at < c.end; at += len, ++i) {
+      // slices end on multiples of kSliceBytes in memory
+      len = std::min(kSliceBytes - (c.phase + at) % kSliceBytes, c.end - at);
+      const uint32_t r = uint32_t(i % shape.share), u = r / waves;
+      const size_t wave = size_t(i / shape.share) * waves + r % waves;
+      uint32_t* b = &out.bytes[wave * (V + 1)];
+      b[u] = uint32_t(len + 3) & ~3u;
+      if (len & 3u) b[V] |= 1u << u;
+      uint32_t* a = &out.at[wave * W * V + u];
+      for (uint32_t k = 0; k < W; ++k) a[size_t(k) * V] = uint32_t((base[k] + at) / 16);
+    }
   });
 }
 

@@ -42,7 +42,7 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
   SliceTable st;
   build_slices(p, shape, rows.data(), st);
   CHECK(st.lanes == shape.lanes && st.vecs == V && shape.share <= waves * V);
-  CHECK(st.addr.size() == size_t(st.groups) * waves * V * W + 16 && st.bytes.size() == size_t(st.groups) * waves * (V + 1));
+  CHECK(st.at.size() == size_t(st.groups) * waves * V * W + 16 && st.bytes.size() == size_t(st.groups) * waves * (V + 1));
   std::map<uint64_t, size_t> at;  // worker 0's tensors by address
   for (size_t t = 0; t < first.size(); ++t) at[rows[t * W]] = t;
   uint64_t slices = 0;
@@ -52,9 +52,9 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
     for (uint32_t u = 0; u < V; ++u) {
       const uint32_t bytes = st.bytes[wave * (V + 1) + u], whole = bytes - 2 * (odd >> u & 1);
       CHECK(bytes % 4 == 0 && bytes <= kSliceBytes && (bytes || !(odd >> u & 1)));
-      auto address = [&](uint32_t k) { return st.addr[(wave * W + k) * V + u]; };
+      auto address = [&](uint32_t k) { return st.base + uint64_t(st.at[(wave * W + k) * V + u]) * 16; };
       if (!bytes) {
-        for (uint32_t k = 0; k < W; ++k) CHECK(address(k) == 0);
+        for (uint32_t k = 0; k < W; ++k) CHECK(address(k) == st.base);
         continue;
       }
       ++slices;
@@ -100,7 +100,7 @@ int main() {
     cfg.pattern = uint32_t(pick({CARAMEL_PATTERN_RING, CARAMEL_PATTERN_RING, CARAMEL_PATTERN_SHUFFLE}));
     const bool large = it % 13 == 0;  // enough slices for every shape
     std::vector<uint64_t> elems(1 + rng() % (large ? 3 : 40));
-    for (uint64_t& e : elems) e = large ? 700001 + rng() % 2500000 : pick({1, 2, 3, 17, 100, 257, 1000, 4099, 16384, 70001});
+    for (uint64_t& e : elems) e = large ? 700001 + rng() % 2000000 : pick({1, 2, 3, 17, 100, 257, 1000, 4099, 16384, 70001});
     HostPlan p;
     std::string why;
     CHECK(build_host_plan(cfg, elems.data(), uint32_t(elems.size()), nullptr, 0.0, 0.0, p, why) == CARAMEL_OK);
@@ -109,7 +109,14 @@ int main() {
     for (size_t t = 0; t < elems.size(); ++t) {
       const uint64_t common = rng() % 4096;
       for (uint32_t w = 0; w < cfg.world; ++w)
-        rows[t * cfg.world + w] = (uint64_t(w + 1) << 40) + (uint64_t(t) << 32) + (alike ? common : rng() % 4096) * cfg.align_bytes;
+        rows[t * cfg.world + w] = (uint64_t(1) << 46) + (uint64_t(w) << 29) + (uint64_t(t) << (large ? 24 : 21)) + (alike ? common : rng() % 4096) * cfg.align_bytes;
+    }
+    if (it % 20 == 1 && rows.size() > 2 * cfg.world) {  // out of the table's reach
+      std::vector<uint64_t> far = rows;
+      far[0] += uint64_t(1) << 37;
+      SliceTable st;
+      build_slices(p, SliceShape{256, 1, 4}, far.data(), st);
+      CHECK(st.groups == 0 && st.at.empty());
     }
     const SliceShape own = choose_slices(p, count_slices(p, rows.data()));
     if (own.vecs) {
