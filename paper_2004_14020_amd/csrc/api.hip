@@ -850,7 +850,8 @@ int upload_tables(caramel_plan* p, bool staged) {
   p->dt.copy = reinterpret_cast<const CopyTile*>(d + copy);
   p->slices = SliceArgs{reinterpret_cast<const uint32_t*>(d + at), reinterpret_cast<const uint32_t*>(d + bytes), t.base,
                         t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16,
-                        shape.through ? kThrough : kStream};
+                        shape.through ? kThrough : kStream,
+                        h.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && h.cfg.world > 1};
   return CARAMEL_OK;
 }
 

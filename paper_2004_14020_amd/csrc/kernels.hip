@@ -818,6 +818,13 @@ struct Slices {
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t res(uint32_t place, uint32_t n) const {
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(address(place)), 0, int(n), kRawBuffer);
   }
+  // One word of every line of the places: the steps' lookups miss the caches together and not one by one
+  // (first call on new buffers: 8 workers, 16 MiB 64.6 -> 61.3 us, 16 workers 113 -> 107; repeated ones the
+  // same).  To be consumed after the last step.
+  __device__ __forceinline__ uint32_t touch() const {
+    const uint32_t line = threadIdx.x % 64 * 32;
+    return reinterpret_cast<gu32_ptr>(reinterpret_cast<uint64_t>(at))[line < W * N ? line : 0];
+  }
   // CW: the number of workers, 0 if known at run time only
   template <int CW>
   __device__ __forceinline__ void put(const u32x4 (&y)[N]) {
@@ -873,10 +880,7 @@ k_slices(const uint32_t* places, const uint32_t* lengths, uint64_t base, uint32_
     __builtin_amdgcn_sched_barrier(0);
   };
   look(0);
-  // one word of every line that the later steps will look up: they miss the caches together and not one by one
-  // (first call on new buffers: 8 workers, 16 MiB 64.6 -> 61.3 us, 16 workers 113 -> 107; repeated ones the same)
-  const uint32_t line = threadIdx.x % 64 * 32;
-  const uint32_t touched = reinterpret_cast<gu32_ptr>(reinterpret_cast<uint64_t>(sl.at))[line < W * N ? line : 0];
+  const uint32_t touched = sl.touch();
   load(0, 0);
   uint32_t k = 0;
 #pragma unroll 1
@@ -921,6 +925,139 @@ k_slice(const uint32_t* places, const uint32_t* lengths, uint64_t base, uint32_t
   }
   const u32x4 y[1] = {acc.finish(inv_w)};
   sl.template put<CW>(y);
+}
+
+// Halving-doubling over slices: the workers in the order 0 .. W-1, their sums as the balanced tree
+// (as in k_tree_walk).  One round of 256-lane workgroups, like k_slices: one wavefront per SIMD, so 512 registers
+// hold four buffers and the open partial sums of every level.  The next pair of workers is on its way while a pair is
+// added.  Eight workers to a turn of the loop; the sums of the turns are merged by its number's trailing ones.
+// Bound: HBM, and the latencies of W / 2 pairs.
+template <bool BF16, int P, int W, int N>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+k_tree_slices(const uint32_t* places, const uint32_t* lengths, uint64_t base, float inv_w) {
+  constexpr int kTurn = W < 8 ? W : 8, kTurns = W / kTurn, kPairs = kTurn / 2;
+  Slices<BF16, P, N> sl(places, lengths, base, W);
+  uint32_t a[N];
+  auto look = [&](uint32_t k) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) a[u] = sl.at[k * N + u];
+  };
+  u32x4 buf[4][N], y[N];
+  auto load = [&](uint32_t k, int j) {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      buf[j][u] = __builtin_amdgcn_raw_buffer_load_b128(sl.res(a[u], sl.len[u]), int(sl.off), 0, kLoadBits<P>);
+    __builtin_amdgcn_sched_barrier(0);
+    look(k + 1 < uint32_t(W) ? k + 1 : 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  look(0);
+  const uint32_t touched = sl.touch();
+  load(0, 0);
+  load(1, 1);
+  Chain<BF16> low[2][N], high[3][N];  // open sums of 2 and 4 workers; of 8, 16 and 32
+#pragma unroll 1
+  for (uint32_t turn = 0; turn < uint32_t(kTurns); ++turn) {
+#pragma unroll
+    for (int p = 0; p < kPairs; ++p) {
+      if (p + 1 < kPairs || turn + 1 < uint32_t(kTurns)) {
+        load(turn * kTurn + 2 * p + 2, (2 * p + 2) % 4);
+        load(turn * kTurn + 2 * p + 3, (2 * p + 3) % 4);
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        Chain<BF16> t;
+        t.start(buf[2 * p % 4][u]);
+        t.add(buf[(2 * p + 1) % 4][u]);
+        if (p % 2 == 1) {
+          low[0][u].merge(t);
+          t = low[0][u];
+        }
+        if (p % 4 == 3) {
+          low[1][u].merge(t);
+          t = low[1][u];
+        }
+        t.pin();
+        low[p % 4 == 1 && kPairs > 2 ? 1 : 0][u] = t;  // the last pair of a turn leaves the turn's sum in low[0]
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    auto close = [&](int level) {  // the earlier sum + the later one
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        high[level][u].merge(low[0][u]);
+        low[0][u] = high[level][u];
+        low[0][u].pin();
+      }
+    };
+    auto keep = [&](int level) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) high[level][u] = low[0][u];
+    };
+    if constexpr (kTurns > 1) {
+      if (!(turn & 1)) {
+        keep(0);
+      } else {
+        close(0);
+        if constexpr (kTurns > 2) {
+          if (!(turn & 2)) {
+            keep(1);
+          } else {
+            close(1);
+            if constexpr (kTurns > 4) {
+              if (!(turn & 4)) keep(2);
+              else close(2);
+            }
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) y[u] = low[0][u].finish(inv_w);
+  asm volatile("" ::"v"(touched));
+  sl.template put<0>(y);
+}
+
+// One slice per wavefront, all values at once (eight workers' at a time over 32 and 64).
+template <bool BF16, int P, int W>
+__global__ void __launch_bounds__(256)
+k_tree_slice(const uint32_t* places, const uint32_t* lengths, uint64_t base, float inv_w) {
+  Slices<BF16, P, 1> sl(places, lengths, base, W);
+  auto fetch = [&](int k) { return __builtin_amdgcn_raw_buffer_load_b128(sl.res(sl.at[k], sl.len[0]), int(sl.off), 0, kLoadBits<P>); };
+  u32x4 y[1];
+  if constexpr (W <= 16) {
+    u32x4 x[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) x[k] = fetch(k);
+    __builtin_amdgcn_sched_barrier(0);
+    y[0] = combine<W, BF16, true>(x, inv_w);
+  } else {
+    Chain<BF16> part[4];
+    for_each_index(std::make_integer_sequence<int, W / 8>{}, [&](auto block) {
+      constexpr int j = decltype(block)::value;
+      u32x4 x[8];
+      Chain<BF16> t[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = fetch(8 * j + i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t[i].start(x[i]);
+#pragma unroll
+      for (int s = 1; s < 8; s *= 2)
+#pragma unroll
+        for (int i = 0; i + s < 8; i += 2 * s) t[i].merge(t[i + s]);
+      constexpr int kClosed = __builtin_ctz(~j);
+#pragma unroll
+      for (int level = 0; level < kClosed; ++level) {
+        part[level].merge(t[0]);
+        t[0] = part[level];
+      }
+      if constexpr (j + 1 < W / 8) part[kClosed] = t[0];
+      else y[0] = t[0].finish(inv_w);
+    });
+  }
+  sl.template put<W <= 16 ? W : 0>(y);
 }
 
 template <int W, int U>
@@ -1063,6 +1200,40 @@ hipError_t launch_slices(const SliceArgs& a, hipStream_t s) {
     if (a.policy == kThrough) CARAMEL_SLICE2(kThrough, CW); else CARAMEL_SLICE2(kStream, CW); \
     return hipGetLastError(); \
   }
+#define CARAMEL_TREE_ROUND(W, BF, N) \
+  if (a.tree && a.world == W && a.bf16 == BF && a.vecs == N && a.lanes == 256 && a.policy == kStream) { \
+    hipLaunchKernelGGL((k_tree_slices<BF, kStream, W, N>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w); \
+    return hipGetLastError(); \
+  }
+#define CARAMEL_TREE_SLICE2(W, P) \
+  if (a.bf16) hipLaunchKernelGGL((k_tree_slice<true, P, W>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w); \
+  else hipLaunchKernelGGL((k_tree_slice<false, P, W>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w)
+#define CARAMEL_TREE_SLICE(W) \
+  if (a.tree && a.world == W && a.vecs == 1 && a.lanes == 256) { \
+    if (a.policy == kThrough) CARAMEL_TREE_SLICE2(W, kThrough); else CARAMEL_TREE_SLICE2(W, kStream); \
+    return hipGetLastError(); \
+  }
+#define CARAMEL_TREE_ROUNDS(W, BF) CARAMEL_TREE_ROUND(W, BF, 2) CARAMEL_TREE_ROUND(W, BF, 4) CARAMEL_TREE_ROUND(W, BF, 6) CARAMEL_TREE_ROUND(W, BF, 8)
+  if (a.tree) {
+    CARAMEL_TREE_SLICE(2) CARAMEL_TREE_SLICE(4) CARAMEL_TREE_SLICE(8) CARAMEL_TREE_SLICE(16) CARAMEL_TREE_SLICE(32)
+    CARAMEL_TREE_SLICE(64)
+    CARAMEL_TREE_ROUNDS(2, false) CARAMEL_TREE_ROUND(2, false, 12) CARAMEL_TREE_ROUND(2, false, 16) CARAMEL_TREE_ROUND(2, false, 20)
+    CARAMEL_TREE_ROUNDS(4, false) CARAMEL_TREE_ROUND(4, false, 12) CARAMEL_TREE_ROUND(4, false, 16) CARAMEL_TREE_ROUND(4, false, 20)
+    CARAMEL_TREE_ROUNDS(8, false) CARAMEL_TREE_ROUND(8, false, 12) CARAMEL_TREE_ROUND(8, false, 16) CARAMEL_TREE_ROUND(8, false, 18)
+    CARAMEL_TREE_ROUNDS(16, false) CARAMEL_TREE_ROUND(16, false, 12) CARAMEL_TREE_ROUND(16, false, 14)
+    CARAMEL_TREE_ROUNDS(32, false) CARAMEL_TREE_ROUND(32, false, 12) CARAMEL_TREE_ROUND(32, false, 14)
+    CARAMEL_TREE_ROUNDS(64, false) CARAMEL_TREE_ROUND(64, false, 12)
+    CARAMEL_TREE_ROUNDS(2, true) CARAMEL_TREE_ROUND(2, true, 12) CARAMEL_TREE_ROUND(2, true, 16)
+    CARAMEL_TREE_ROUNDS(4, true) CARAMEL_TREE_ROUND(4, true, 12) CARAMEL_TREE_ROUND(4, true, 16)
+    CARAMEL_TREE_ROUNDS(8, true) CARAMEL_TREE_ROUND(8, true, 12) CARAMEL_TREE_ROUND(8, true, 14)
+    CARAMEL_TREE_ROUNDS(16, true) CARAMEL_TREE_ROUND(16, true, 10)
+    CARAMEL_TREE_ROUNDS(32, true) CARAMEL_TREE_ROUNDS(64, true)
+    return hipErrorInvalidValue;
+  }
+#undef CARAMEL_TREE_ROUND
+#undef CARAMEL_TREE_ROUNDS
+#undef CARAMEL_TREE_SLICE
+#undef CARAMEL_TREE_SLICE2
   CARAMEL_SLICE(2) CARAMEL_SLICE(3) CARAMEL_SLICE(4) CARAMEL_SLICE(8) CARAMEL_SLICE(16) CARAMEL_SLICE(0)
   CARAMEL_ROUND(false, 4) CARAMEL_ROUND(false, 6) CARAMEL_ROUND(false, 8) CARAMEL_ROUND(false, 10) CARAMEL_ROUND(false, 12)
   CARAMEL_ROUND(false, 14) CARAMEL_ROUND(false, 16) CARAMEL_ROUND(false, 18) CARAMEL_ROUND(false, 20)

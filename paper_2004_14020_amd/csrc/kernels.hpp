@@ -40,6 +40,7 @@ struct SliceArgs {
   uint32_t world;
   bool bf16;
   Policy policy;          // kStream or kThrough
+  bool tree;
 };
 
 struct CopyArgs {
@@ -55,7 +56,7 @@ struct CopyArgs {
 
 // Ring reduce-scatter arithmetic + 1/W scaling + all-gather for a range of tiles.
 hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t stream);
-// The same, in chain orders, for a job that was cut into slices.
+// The same for a job that was cut into slices.
 hipError_t launch_slices(const SliceArgs& a, hipStream_t stream);
 // Segmented gather (pack) or scatter (unpack) driven by the copy-tile table.
 hipError_t launch_copy(const CopyArgs& a, hipStream_t stream);

@@ -42,7 +42,7 @@ void for_each_piece(const HostPlan& p, const uint64_t* row_addr, F&& f) {
     const uint64_t* seg = p.segments(ui);
     const caramel_entry* ent = &p.entries[u.first_entry];
     // [lo, hi) in unit positions, starting at element `row_elem` of `row`.  Ring: the sums of segment c
-    // start at worker c + 1; shuffle adds from worker 0 everywhere.
+    // start at worker c + 1; the other patterns read from worker 0 everywhere.
     auto add = [&](uint32_t row, uint64_t row_elem, uint64_t lo, uint64_t hi) {
       if (p.cfg.pattern != CARAMEL_PATTERN_RING) return cut(row, row_elem, hi - lo, 0);
       for (uint32_t c = 0; c < W; ++c) {
@@ -62,8 +62,7 @@ void for_each_piece(const HostPlan& p, const uint64_t* row_addr, F&& f) {
 }  // namespace
 
 bool may_have_slices(const HostPlan& p) {
-  return !(p.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && p.cfg.world > 1) &&
-         p.replica_elems * p.elem_size() < (uint64_t(32) << 20);
+  return p.replica_elems * p.elem_size() < (uint64_t(32) << 20);
 }
 
 uint64_t count_slices(const HostPlan& p, const uint64_t* row_addr) {
@@ -75,44 +74,56 @@ uint64_t count_slices(const HostPlan& p, const uint64_t* row_addr) {
 // Measured on MI355X, microseconds, tiles / slices, data not in the last-level cache where they fit no more.
 //  * One round: if all slices fit the registers of 256 workgroups at a time, every compute unit reads its whole
 //    share, worker by worker, and then writes it, all of them at the same time: reads and writes hardly
-//    mix at the memory.  Workgroups of 256 lanes hold 20 vectors per lane in fp32, 16 in bf16 (8 workers fp32:
-//    4 MiB per replica 14.6 / 12.2, 12 MiB 38.9 / 34.6, 16 MiB 52.3 / 46.3; 16 workers 16 MiB 109 / 94; 2 workers
-//    16 MiB 14.0 / 12.0; 8 workers bf16 12 MiB 39.4 / 36.4).  The fewer, longer stretches of memory win over
-//    the last compute units: vectors are dealt out so that about 210 of them have work (12 MiB: 34.6 over 195, 35.2
-//    over 223; with all in 256 lanes x 12, which takes two rounds, 43.6).
-//  * Below some 2300 slices workgroups of one vector per lane, whose values all workers send at once, are
-//    over sooner (8 workers 2 MiB 8.4 / 7.1, four vectors 7.5; 3 MiB 11.6 / 9.8, one vector 11.1); up to 4
-//    workers there are fewer steps to wait for (4 workers bf16 2.7 MiB 5.7, one vector 5.6, four 5.8).
-//  * Above one round of 256 lanes, fp32: from 16 workers on one round of 512 lanes (24 workers 26 MiB 247 / 238, 32
-//    workers 31 MiB 414 / 375); 8 to 15 workers 1024 lanes in equal shares (8 workers 31 MiB 100 / 90, 12 workers
-//    144 / 136), but where that comes to seven vectors per lane again 512 lanes (12 workers 27 MiB 122.5 / 125.4,
-//    with 512 lanes 122).  Up to 7 workers, and with bf16 but for 9 to 24 workers from 20 MiB on, one vector per lane
-//    in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; 8 workers bf16 98 / 92, 1024
-//    lanes 96; 12 workers bf16 143 / 139, one vector 142.5).  One worker has tiles there (26 MiB 11.5 / 13.0).
+//    mix at the memory (8 workers fp32 4 MiB per replica 14.6 / 11.6, 12 MiB 38.9 / 34.2, 16 MiB 51.2 / 47.1; 16
+//    workers 16 MiB 107 / 96; 2 workers 16 MiB 14.0 / 11.7; 8 workers bf16 12 MiB 41.2 / 34.6; halving-doubling, 8
+//    workers 13.5 MiB 46.0 / 36.8, 64 workers 3 MiB 85 / 70).  From some 8 MiB on the fewer, longer stretches of
+//    memory win over the last compute units: vectors are dealt out so that about 210 of them have work (12 MiB:
+//    34.6 over 195, 35.2 over 223; with all in 256 lanes x 12, which takes two rounds, 43.6); below, the work is
+//    spread over as many as there are (4 workers 3.3 MiB 5.7 over 215, 6.1 over 143).
+//  * Below some 2000 slices workgroups of one vector per lane, whose values all workers send at once, are
+//    over sooner (8 workers 1.2 MiB 6.0, two vectors 6.1, four 6.6; 2.1 MiB 8.2, four 7.5).  Up to 4 workers there
+//    are fewer steps to wait for (4 workers 2.2 MiB 5.2, four vectors 5.3; 2.7 MiB 5.5 / 5.3).  Trees, which take
+//    the workers by pairs, have two vectors from 1000 slices on (16 workers 1.5 MiB 11.4, two vectors 9.7).
 //  * Stores: what one round writes is left to the last-level cache, where it fits (8 workers 4 MiB 12.6 written
 //    through, 11.6; 2 workers 12 MiB 9.2 / 8.8; called one at a time 8 x 15 MB 56.0 / 53.0; 32 workers 12 MiB, 384
 //    MiB in all, 142 / 144).  Longer jobs write while others read, and are better off through (4 workers 30
 //    MiB 43.8 / 44.9, 8 workers 87.4 / 90.1).
+//  * Above one round of 256 lanes, fp32 chains: from 16 workers on one round of 512 lanes (24 workers 26 MiB 247 /
+//    238, 32 workers 31 MiB 414 / 375); 8 to 15 workers 1024 lanes in equal shares (8 workers 31 MiB 100 / 90, 12
+//    workers 144 / 136), but where that comes to seven vectors per lane again 512 lanes (12 workers 27 MiB
+//    122.5 / 125.4, with 512 lanes 122).  Up to 7 workers, and with bf16 but for 9 to 24 workers from 20 MiB on, one
+//    vector per lane in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; 8 workers bf16
+//    98 / 92, 1024 lanes 96; 12 workers bf16 143 / 139, one vector 142.5), and so for trees (8 workers 25 MiB 79.9 /
+//    75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 / 13.0), and so has
+//    halving-doubling over 64 in fp32 (16 MiB 440 / 447).
 SliceShape choose_slices(const HostPlan& p, uint64_t n) {
   const uint32_t W = p.cfg.world;
   const uint64_t replica_bytes = p.replica_elems * p.elem_size();
   // (the table of a job of very many tiny tensors would outgrow them)
   if (!may_have_slices(p) || n == 0 || n * W > (1u << 23)) return {};
   const bool bf16 = p.cfg.dtype == CARAMEL_BF16;
-  const uint32_t most = bf16 ? 16 : 20;  // vectors per lane that fit the registers
-  auto even = [](uint64_t v, uint32_t lo, uint32_t hi) { return std::clamp(uint32_t((v + 1) / 2 * 2), lo, hi); };
+  const bool tree = p.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && W > 1;
+  // vectors per lane that fit the registers: two buffers and the sum, or four buffers and a sum for every level
+  const uint32_t most = !tree ? (bf16 ? 16 : 20)
+                              : (bf16 ? (W <= 4 ? 16 : (W == 8 ? 14 : (W == 16 ? 10 : 8)))
+                                      : (W <= 4 ? 20 : (W == 8 ? 18 : (W <= 32 ? 14 : 12))));
+  auto up = [](uint64_t v, uint32_t step) { return uint32_t((v + step - 1) / step * step); };
   SliceShape s{256, 1, 4, W * replica_bytes > (uint64_t(256) << 20)};
-  if (n <= (W <= 4 ? 3328u : 2304u)) return s;
+  if (n <= (tree ? 1024u : (W <= 4 ? 2560u : 2048u))) return s;
   if (n <= uint64_t(4) * most * kComputeUnits) {
-    s.vecs = even((n + 849) / 850, 4, most);
+    const uint64_t each = n <= 8192 ? 4 * kComputeUnits : 850;
+    s.vecs = std::min(most, up((n + each - 1) / each, tree && n > 8192 ? 4 : 2));
+    if (!tree) s.vecs = std::max(s.vecs, 4u);
+    if (tree) s.through = false;
     s.share = 4 * s.vecs;
     return s;
   }
-  if (W == 1) return {};
+  if (W == 1 || (tree && W == 64 && !bf16)) return {};
   s.through = true;
+  if (tree) return s;
   if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
     s.lanes = 512;
-    s.vecs = even((n + 1549) / 1550, 14, most);
+    s.vecs = std::clamp(up((n + 1549) / 1550, 2), 14u, most);
     s.share = 8 * s.vecs;
   } else if (bf16 ? W > 8 && W <= 24 && n > 20480 : W >= 8) {
     const uint64_t full = 16 * (bf16 ? 6 : 8) * kComputeUnits, rounds = (n + full - 1) / full;

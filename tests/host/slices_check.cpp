@@ -97,7 +97,8 @@ int main() {
     cfg.split_bytes = pick({4096, 102400, 1 << 20});
     cfg.max_depth = 8;
     cfg.num_streams = uint32_t(pick({1, 2}));
-    cfg.pattern = uint32_t(pick({CARAMEL_PATTERN_RING, CARAMEL_PATTERN_RING, CARAMEL_PATTERN_SHUFFLE}));
+    cfg.pattern = uint32_t(pick({CARAMEL_PATTERN_RING, CARAMEL_PATTERN_RING, CARAMEL_PATTERN_SHUFFLE, CARAMEL_PATTERN_HALVING_DOUBLING}));
+    if (cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && (cfg.world & (cfg.world - 1))) cfg.world = 16;
     const bool large = it % 13 == 0;  // enough slices for every shape
     std::vector<uint64_t> elems(1 + rng() % (large ? 3 : 40));
     for (uint64_t& e : elems) e = large ? 700001 + rng() % 2000000 : pick({1, 2, 3, 17, 100, 257, 1000, 4099, 16384, 70001});

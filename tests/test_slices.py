@@ -35,7 +35,9 @@ def test_ends_of_slices(W, dtype):
     from paper_2004_14020_amd.device import Replicas
     ve = 4 if dtype == oracle.F32 else 8
     elems = list(range(1, 2 * ve + 1)) + [64 * ve - 1, 64 * ve, 64 * ve + 1, 1000 * ve + 3, W * 512 * ve + 5]
-    for pattern in (oracle.PATTERN_RING, oracle.PATTERN_SHUFFLE):
+    for pattern in (oracle.PATTERN_RING, oracle.PATTERN_SHUFFLE, oracle.PATTERN_HALVING_DOUBLING):
+        if pattern == oracle.PATTERN_HALVING_DOUBLING and W & (W - 1):
+            continue
         print(f"case: ends of slices W={W} dtype={dtype} pattern={pattern}", flush=True)
         cfg = oracle.Config(W, dtype, 4096, oracle.SPLIT_NONE, 1, 0, 16, 1, pattern)
         grads = make_inputs(cfg, elems, seed=50 + W)
@@ -64,20 +66,26 @@ def test_ends_of_slices(W, dtype):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("W,dtype", [(1, 0), (2, 1), (3, 0), (4, 1), (8, 0), (8, 1), (12, 0), (12, 1), (16, 0), (24, 1), (32, 0)])
-def test_every_shape_gives_the_bits_of_the_tiles(W, dtype):
+@pytest.mark.parametrize("pattern,W,dtype", [("ring", 1, 0), ("ring", 2, 1), ("ring", 3, 0), ("ring", 4, 1), ("ring", 8, 0),
+                                             ("ring", 8, 1), ("ring", 12, 0), ("ring", 12, 1), ("ring", 16, 0), ("ring", 24, 1),
+                                             ("ring", 32, 0)] + [("hd", W, d) for W in (2, 4, 8, 16, 32, 64) for d in (0, 1)])
+def test_every_shape_gives_the_bits_of_the_tiles(pattern, W, dtype):
     """Around the lines between the shapes: the smallest and largest number of vectors per lane, one and
     several rounds, a last workgroup that is nearly empty."""
     import torch
     import paper_2004_14020_amd as cm
     from paper_2004_14020_amd.device import Replicas
     size = 4 if dtype == cm.F32 else 2
-    for kib in (1, 2303, 2305, 3329, 3401, 10000, 16381, 16390, 20477, 20490, 24577, 28673, 32767):
-        if kib * W > 400000:
+    sizes = (1, 2040, 2070, 2570, 3401, 10000, 16381, 16390, 20477, 20490, 24577, 28673, 32767)
+    if pattern == "hd":  # every number of vectors per lane
+        sizes = (1, 1010, 1030, 2070, 4100, 6150, 8200, 9300, 11000, 13800, 17300, 20400, 20490, 32767)
+    for kib in sizes:
+        if kib * W > 530000:
             continue
-        print(f"case: slices against tiles W={W} dtype={dtype} {kib} KiB", flush=True)
+        print(f"case: slices against tiles {pattern} W={W} dtype={dtype} {kib} KiB", flush=True)
         elems = [kib * KIB // size - 300 if kib > 1 else 100, 37, 256, 1]
-        plan = cm.Plan(W, elems, dtype=dtype, batch_threshold_bytes=4096, split_mode=cm.SPLIT_FIXED, split_bytes=1000 * KIB)
+        plan = cm.Plan(W, elems, dtype=dtype, batch_threshold_bytes=4096, split_mode=cm.SPLIT_FIXED, split_bytes=1000 * KIB,
+                       pattern=cm.PATTERN_RING if pattern == "ring" else cm.PATTERN_HALVING_DOUBLING)
         dev = Replicas(plan, elems, with_workspace=False, large_align=256)
         dev.fill_random(kib)
         before = [a.clone() for a in dev.arenas]
