@@ -143,7 +143,8 @@ struct caramel_plan {
   bool has_ws = false;
   int device = -1;  // the device that was current at bind: tables, stream and events live there
   Binding bind;
-  unsigned char* d_tables = nullptr;  // all of them
+  void* d_tables[6] = {};  // what release_device() frees
+  uint32_t n_tables = 0;
   DeviceTables dt;
   SliceArgs slices{};  // groups = 0: the plan is bound without slices
   hipStream_t streams[2] = {nullptr, nullptr};
@@ -168,8 +169,7 @@ struct caramel_plan {
 namespace {
 
 void release_device(caramel_plan* p) {
-  if (p->d_tables) (void)hipFree(p->d_tables);
-  p->d_tables = nullptr;
+  for (; p->n_tables; --p->n_tables) (void)hipFree(p->d_tables[p->n_tables - 1]);
   p->dt = DeviceTables{};
   p->slices = SliceArgs{};
   p->bound = false;
@@ -187,17 +187,17 @@ void drop_events(caramel_plan* p) {
   p->spare.clear();
 }
 
-// The tables of a binding on their way to the device: one allocation and one copy for all of them.
-struct Upload {
-  std::vector<unsigned char> host;
-  template <typename T>
-  size_t add(const std::vector<T>& v) {
-    const size_t at = (host.size() + 255) / 256 * 256;
-    host.resize(at + v.size() * sizeof(T));
-    if (!v.empty()) std::memcpy(host.data() + at, v.data(), v.size() * sizeof(T));
-    return at;
-  }
-};
+template <typename T>
+int upload(caramel_plan* p, const std::vector<T>& v, const T** dst) {
+  *dst = nullptr;
+  if (v.empty()) return CARAMEL_OK;
+  void* d = nullptr;
+  HIP_TRY(hipMalloc(&d, v.size() * sizeof(T)));
+  p->d_tables[p->n_tables++] = d;
+  HIP_TRY(hipMemcpy(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+  *dst = static_cast<const T*>(d);
+  return CARAMEL_OK;
+}
 
 hipEvent_t take_event(caramel_plan* p) {
   if (!p->spare.empty()) {
@@ -831,28 +831,22 @@ void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& 
 int upload_tables(caramel_plan* p, bool staged) {
   const HostPlan& h = p->host;
   const Binding& bd = p->bind;
-  const std::vector<ReduceTile> none;
   SliceTable t;
   SliceShape shape;
   if (p->opt.tiles_left_to_library() && may_have_slices(h)) {
     shape = choose_slices(h, count_slices(h, bd.rows.data()));
     build_slices(h, shape, bd.rows.data(), t);
   }
-  Upload up;
-  const size_t at = up.add(t.at), bytes = up.add(t.bytes), rows = up.add(bd.rows), direct = up.add(bd.tt.direct);
-  const size_t on_fused = up.add(staged ? bd.tt.staged : none), copy = staged ? up.add(bd.tt.copy) : 0;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&p->d_tables), up.host.size()));
-  unsigned char* d = p->d_tables;
-  HIP_TRY(hipMemcpy(d, up.host.data(), up.host.size(), hipMemcpyHostToDevice));
-  p->dt.rows = reinterpret_cast<const uint64_t*>(d + rows);
-  p->dt.direct = reinterpret_cast<const ReduceTile*>(d + direct);
-  p->dt.staged = reinterpret_cast<const ReduceTile*>(d + on_fused);
-  p->dt.copy = reinterpret_cast<const CopyTile*>(d + copy);
-  p->slices = SliceArgs{reinterpret_cast<const uint32_t*>(d + at), reinterpret_cast<const uint32_t*>(d + bytes), t.base,
-                        t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16,
+  p->slices = SliceArgs{nullptr, nullptr, t.base, t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16,
                         shape.through ? kThrough : kStream,
                         h.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && h.cfg.world > 1};
-  return CARAMEL_OK;
+  int rc = upload(p, t.at, &p->slices.at);
+  if (!rc) rc = upload(p, t.bytes, &p->slices.bytes);
+  if (!rc) rc = upload(p, bd.rows, &p->dt.rows);
+  if (!rc) rc = upload(p, bd.tt.direct, &p->dt.direct);
+  if (!rc && staged) rc = upload(p, bd.tt.staged, &p->dt.staged);
+  if (!rc && staged) rc = upload(p, bd.tt.copy, &p->dt.copy);
+  return rc;
 }
 
 int bind_plan(caramel_plan* p, void* const* grads, void* fused_ws) {

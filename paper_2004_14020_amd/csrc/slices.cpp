@@ -61,8 +61,17 @@ void for_each_piece(const HostPlan& p, const uint64_t* row_addr, F&& f) {
 
 }  // namespace
 
+// Up to 32 MiB per replica slices are the better cut but for the shapes that choose_slices leaves out.  Few workers
+// have them longer: their walks over long tiles are short, and a tile that is left over at the end, or at a segment
+// boundary, weighs as much as elsewhere (us, tiles / slices, fp32 ring unless said otherwise: 2 workers 90 MiB 69.5 / 61.0,
+// 110 MiB 80.2 / 75.0, bf16 75.0 / 73.8, but 190 MiB 125.4 / 126.6; 4 workers 42 MiB 61.3 / 59.5, bf16 56 MiB 81.0 / 83.4; 6
+// workers 48 MiB 106.2 / 101.5, 65 MiB 137.6 / 141.0; 8 workers 33 MiB 109 / 103, 37 MiB 118.5 / 112.1, but 12 large
+// tensors of 38 MiB 116.8 / 119.8, shuffle 108.9 / 116.3; 12 workers 37 MiB 166.5 / 167.6; halving-doubling over 4 42 MiB 63.1 / 60.4, over 8 33 MiB 96.4 / 98.9).
 bool may_have_slices(const HostPlan& p) {
-  return p.replica_elems * p.elem_size() < (uint64_t(32) << 20);
+  const uint32_t W = p.cfg.world;
+  const bool tree = p.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
+  const uint64_t mib = W == 2 ? 112 : (W > 2 && W <= (tree ? 4u : 6u) ? 48 : (!tree && (W == 7 || W == 8) ? 36 : 32));
+  return p.replica_elems * p.elem_size() < mib << 20;
 }
 
 uint64_t count_slices(const HostPlan& p, const uint64_t* row_addr) {
@@ -120,7 +129,7 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n) {
   }
   if (W == 1 || (tree && W == 64 && !bf16)) return {};
   s.through = true;
-  if (tree) return s;
+  if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
   if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
     s.lanes = 512;
     s.vecs = std::clamp(up((n + 1549) / 1550, 2), 14u, most);
