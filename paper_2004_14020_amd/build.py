@@ -25,9 +25,14 @@ def hipcc() -> str:
 DEVICE_FEATURE = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 HOST_PASS_NOTE = "'-packed-fp32-ops' is not a recognized feature for this target (ignoring feature)"
 
+# Kernel arguments come in scalar registers, so that a wavefront's first lookup need not wait for theirs: what
+# small jobs consist of is a chain of such waits (8 workers, 1 MiB 5.27 -> 4.96 us, 4 MiB 11.59 -> 11.41, 32 workers,
+# 0.25 MiB 7.60 -> 7.35; large jobs the same).
+PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=8"]
+
 
 def flags() -> list:
-    return ["-std=c++17", "-O3", "--offload-arch=gfx950", "-ffp-contract=off", "-fno-fast-math", *DEVICE_FEATURE,
+    return ["-std=c++17", "-O3", "--offload-arch=gfx950", "-ffp-contract=off", "-fno-fast-math", *DEVICE_FEATURE, *PRELOAD,
             "-Wall", "-Wno-unused-command-line-argument",
             "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc")]
 
