@@ -303,7 +303,12 @@ int caramel_allreduce_static(caramel_plan* plan, void* const* grads, void* strea
  * CARAMEL_OPT_LONG_RUN_BYTES are cut into long tiles (CARAMEL_OPT_TILE_VECS), which 1024-lane
  * workgroups walk one replica after the other; shorter runs into small tiles
  * (CARAMEL_OPT_SMALL_TILE_VECS), for which 256-lane workgroups fetch all replicas at once.
- * Long and small tiles go out in separate launches. */
+ * Long and small tiles go out in separate launches.
+ * While the options below that shape tiles and their kernels have their defaults (2 to 6, 9 to 12, 14, 16, 17) and
+ * the launch mode is AUTO without the pipeline, small jobs that are reduced in place are cut into 1 KiB slices
+ * instead and go out in one launch: less than 32 MiB per replica, 112 with 2 workers, 48 with 3 to 6, 36 with 7
+ * and 8 (halving-doubling: 112 with 2, 48 with 4), but for a few shapes for which tiles are faster.  Their
+ * table is built at caramel_bind; an option that asks for tiles takes effect all the same. */
 enum {
   /* How units map to kernel launches.  PER_UNIT: consecutive units of a plan stream share a
    * launch until it covers CARAMEL_OPT_LAUNCH_MIN_BYTES / CARAMEL_OPT_LONG_LAUNCH_MIN_BYTES

@@ -103,8 +103,9 @@ uint64_t count_slices(const HostPlan& p, const uint64_t* row_addr) {
 //    122.5 / 125.4, with 512 lanes 122).  Up to 7 workers, and with bf16 but for 9 to 24 workers from 20 MiB on, one
 //    vector per lane in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; 8 workers bf16
 //    98 / 92, 1024 lanes 96; 12 workers bf16 143 / 139, one vector 142.5), and so for trees (8 workers 25 MiB 79.9 /
-//    75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 / 13.0), and so has
-//    halving-doubling over 64 in fp32 (16 MiB 440 / 447).
+//    75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 / 13.0), and so have
+//    halving-doubling over 64 in fp32 (16 MiB 440 / 447) and 9 to 15 workers in bf16 where a second round of 1024 lanes
+//    would be nearly empty (12 workers 24 MiB 108 / 111).
 SliceShape choose_slices(const HostPlan& p, uint64_t n) {
   const uint32_t W = p.cfg.world;
   const uint64_t replica_bytes = p.replica_elems * p.elem_size();
@@ -127,7 +128,7 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n) {
     s.share = 4 * s.vecs;
     return s;
   }
-  if (W == 1 || (tree && W == 64 && !bf16)) return {};
+  if (W == 1 || (tree && W == 64 && !bf16) || (bf16 && W > 8 && W < 16 && n > 24576 && n <= 28672)) return {};
   s.through = true;
   if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
   if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
