@@ -242,9 +242,10 @@ def main() -> int:
         v is None for v in (args.launch_mode, args.batch_path, args.tile_vecs, args.max_grid, args.nontemporal, args.unroll,
                             args.block, args.launch_min_bytes, args.align_tiles, args.long_run_bytes))
     as_profiled = args.pattern == "ring" and as_default
-    # with the default options a job of less than 32 MiB per replica is cut into slices, which count as small tiles
+    # with the default options small jobs, and those of few workers that have no long tiles, are cut into slices,
+    # which count as small tiles
     dom_name = reduce_kernel(args.pattern, wl.world, wl.dtype == cm.BF16, dom is lng,
-                             as_default and dom is sml and sum(wl.elems()) * es < (32 << 20))
+                             as_default and dom is sml and (sum(wl.elems()) * es < (32 << 20) or wl.world <= 8))
     dom_line = kernel_line(dom) or {}
     span_ms = seq["span_ms"] / max(1, seq["calls"])
     roofline = {"bound": "hbm", "kernel": dom_name, "achieved": dom_line.get("achieved"), "peak": HBM_PEAK_GBS,

@@ -409,7 +409,7 @@ enum {
   CARAMEL_K_REDUCE = 1,       /* reduce launches over long tiles (the stream-major kernel) */
   CARAMEL_K_UNPACK = 2,
   CARAMEL_K_SEQUENCE = 3,
-  CARAMEL_K_REDUCE_SMALL = 4, /* reduce launches over small tiles */
+  CARAMEL_K_REDUCE_SMALL = 4, /* reduce launches over small tiles, or over slices */
   CARAMEL_K_COUNT = 5
 };
 

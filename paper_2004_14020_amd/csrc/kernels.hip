@@ -826,7 +826,8 @@ struct Slices {
     for (int u = 0; u < N; ++u) len[u] = bytes[u];
     odd = BF16 ? bytes[N] : 0u;
   }
-  // A slice is a buffer of its own length: lanes and dwords beyond it read zeros and store nothing.
+  // A slice is a buffer of its own length: lanes and dwords beyond it read zeros and store nothing.  (The dword of an
+  // odd last bf16 value is read whole; the two bytes behind the value, in the same aligned dword, go nowhere.)
   __device__ __forceinline__ uint64_t address(uint32_t place) const { return base + (uint64_t(place) << 4); }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t res(uint32_t place, uint32_t n) const {
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(address(place)), 0, int(n), kRawBuffer);
