@@ -143,7 +143,7 @@ struct caramel_plan {
   bool has_ws = false;
   int device = -1;  // the device that was current at bind: tables, stream and events live there
   Binding bind;
-  void* d_tables[6] = {};  // what release_device() frees
+  void* d_tables[4] = {};  // what release_device() frees
   uint32_t n_tables = 0;
   DeviceTables dt;
   SliceArgs slices{};  // groups = 0: the plan is bound without slices
@@ -828,21 +828,53 @@ void fill_binding(const caramel_plan* p, std::vector<uint64_t>&& rows, Binding& 
   bd.groups_stale[0] = bd.groups_stale[1] = true;
 }
 
+// Tables of a job in slices: one allocation and one copy for what the host has, and the GPU writes the slices' tables.
+int upload_with_slices(caramel_plan* p, const SliceTable& t, const std::vector<SlicePiece>& pieces, bool staged) {
+  const Binding& bd = p->bind;
+  std::vector<unsigned char> host;
+  auto add = [&](const auto& v) {
+    const size_t off = (host.size() + 255) / 256 * 256;
+    host.resize(off + v.size() * sizeof v[0]);
+    if (!v.empty()) std::memcpy(&host[off], v.data(), v.size() * sizeof v[0]);
+    return off;
+  };
+  const size_t o_pieces = add(pieces), o_rows = add(bd.rows), o_direct = add(bd.tt.direct);
+  const size_t o_staged = staged ? add(bd.tt.staged) : 0, o_copy = staged ? add(bd.tt.copy) : 0;
+  const size_t o_at = (host.size() + 255) / 256 * 256, o_bytes = o_at + (t.at_words() * sizeof(uint32_t) + 255) / 256 * 256;
+  void* q = nullptr;
+  HIP_TRY(hipMalloc(&q, o_bytes + t.bytes_words() * sizeof(uint32_t)));
+  p->d_tables[p->n_tables++] = q;
+  unsigned char* const d = static_cast<unsigned char*>(q);
+  HIP_TRY(hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice));
+  p->dt.rows = reinterpret_cast<const uint64_t*>(d + o_rows);
+  p->dt.direct = reinterpret_cast<const ReduceTile*>(d + o_direct);
+  if (staged) p->dt.staged = reinterpret_cast<const ReduceTile*>(d + o_staged);
+  if (staged) p->dt.copy = reinterpret_cast<const CopyTile*>(d + o_copy);
+  uint32_t* const at = reinterpret_cast<uint32_t*>(d + o_at);
+  uint32_t* const bytes = reinterpret_cast<uint32_t*>(d + o_bytes);
+  HIP_TRY(launch_slice_table(t, reinterpret_cast<const SlicePiece*>(d + o_pieces), p->dt.rows, at, bytes, nullptr));
+  HIP_TRY(hipStreamSynchronize(nullptr));  // calls may come on any stream
+  p->slices.at = at;
+  p->slices.bytes = bytes;
+  return CARAMEL_OK;
+}
+
 int upload_tables(caramel_plan* p, bool staged) {
   const HostPlan& h = p->host;
   const Binding& bd = p->bind;
-  SliceTable t;
-  SliceShape shape;
   if (p->opt.tiles_left_to_library() && may_have_slices(h)) {
-    shape = choose_slices(h, count_slices(h, bd.rows.data()));
-    build_slices(h, shape, bd.rows.data(), t);
+    std::vector<SlicePiece> pieces;
+    const uint64_t n = slice_pieces(h, bd.rows.data(), pieces);
+    const SliceShape shape = choose_slices(h, n);
+    const SliceTable t = slice_table(h, shape, n, pieces.size(), bd.rows.data());
+    if (t.groups) {
+      p->slices = SliceArgs{nullptr, nullptr, t.base, t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16,
+                            shape.through ? kThrough : kStream,
+                            h.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && h.cfg.world > 1};
+      return upload_with_slices(p, t, pieces, staged);
+    }
   }
-  p->slices = SliceArgs{nullptr, nullptr, t.base, t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16,
-                        shape.through ? kThrough : kStream,
-                        h.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && h.cfg.world > 1};
-  int rc = upload(p, t.at, &p->slices.at);
-  if (!rc) rc = upload(p, t.bytes, &p->slices.bytes);
-  if (!rc) rc = upload(p, bd.rows, &p->dt.rows);
+  int rc = upload(p, bd.rows, &p->dt.rows);
   if (!rc) rc = upload(p, bd.tt.direct, &p->dt.direct);
   if (!rc && staged) rc = upload(p, bd.tt.staged, &p->dt.staged);
   if (!rc && staged) rc = upload(p, bd.tt.copy, &p->dt.copy);

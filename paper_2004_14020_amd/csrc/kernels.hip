@@ -10,6 +10,7 @@
 //  k_slices, k_slice, k_tree_slices, k_tree_slice
 //                  the same arithmetic for small jobs, whose work is cut into 1 KiB slices: a wavefront
 //                  takes several of them, of whatever tensors and segments, from a table of addresses.
+//  k_slice_table   writes that table, once per bind.
 //  k_copy          pack / unpack of batched parameters (section 4.2) through an offset table,
 //                  one workgroup per run of at most 16 KiB.
 #include "kernels.hpp"
@@ -1077,6 +1078,36 @@ k_tree_slice(const uint32_t* places, const uint32_t* lengths, uint64_t base, flo
   sl.template put<W <= 16 ? W : 0>(y);
 }
 
+// The table of a job's slices, once per bind: a lane works one slice out for up to kTableSteps workers (place_slice),
+// a workgroup as many whole wavefronts' slices as it has lanes for.  Bound: latency, a binary search of log2(pieces)
+// dependent loads (4 us with 200 slices, 8 us with 92000, 12 us for 64 workers, 22 without the split of their steps).
+// Written by the host and sent, 4 bytes per slice and worker, the table made a bind 1.4 to 4 times as long as one
+// with tiles alone, and the call after it up to 5 %: us, bind and first call with tiles, with the host's table, now:
+// 8 workers 16 MiB 182 + 70, 313 + 68, 188 + 64; 16 workers 16 MiB 256 + 103, 496 + 107, 268 + 103; 2 workers 90 MiB
+// 113 + 82, 453 + 76, 116 + 71; 200 odd tensors of 15 MB apart 217 + 70, 351 + 68, 229 + 63.
+constexpr uint32_t kTableBlock = 256, kTableSteps = 16;
+
+__global__ void __launch_bounds__(kTableBlock)
+k_slice_table(SliceTable t, const SlicePiece* __restrict__ pieces, const uint64_t* __restrict__ rows,
+              uint32_t* __restrict__ places, uint32_t* __restrict__ lengths) {
+  __shared__ uint32_t odd[kTableBlock];
+  const uint32_t per_block = kTableBlock / t.vecs;  // wavefronts of the job
+  const uint32_t mine = threadIdx.x / t.vecs, u = threadIdx.x % t.vecs, wave = blockIdx.x * per_block + mine;
+  const uint32_t k0 = blockIdx.y * kTableSteps, k1 = min(k0 + kTableSteps, t.world);
+  const bool in = mine < per_block && wave < t.waves();
+  uint32_t* const out = lengths + size_t(wave) * (t.vecs + 1);
+  odd[threadIdx.x] = 0;
+  __syncthreads();
+  if (in) {
+    const uint32_t len = place_slice(t, pieces, rows, wave, u, k0, k1, places + size_t(wave) * t.world * t.vecs + u);
+    if (blockIdx.y == 0) out[u] = (len + 3) & ~3u;
+    if (len & 3u) atomicOr(&odd[mine], 1u << u);
+  }
+  __syncthreads();
+  if (in && u == 0 && blockIdx.y == 0) out[t.vecs] = odd[mine];
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 16) places[t.at_words() - 16 + threadIdx.x] = 0;
+}
+
 template <int W, int U>
 hipError_t launch_w(const ReduceArgs& a, dim3 grid, float inv_w, hipStream_t s) {
 #define CARAMEL_GO(BF, P, TR) \
@@ -1197,6 +1228,15 @@ hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t s) {
     if (a.policy != kPlain) CARAMEL_TREE(false, kStream); else CARAMEL_TREE(false, kPlain);
   }
 #undef CARAMEL_TREE
+  return hipGetLastError();
+}
+
+hipError_t launch_slice_table(const SliceTable& t, const SlicePiece* pieces, const uint64_t* rows, uint32_t* at,
+                              uint32_t* bytes, hipStream_t s) {
+  if (t.vecs == 0 || t.vecs > kTableBlock || t.groups == 0) return hipErrorInvalidValue;
+  const uint32_t per_block = kTableBlock / t.vecs;
+  hipLaunchKernelGGL(k_slice_table, dim3((t.waves() + per_block - 1) / per_block, (t.world + kTableSteps - 1) / kTableSteps),
+                     dim3(kTableBlock), 0, s, t, pieces, rows, at, bytes);
   return hipGetLastError();
 }
 

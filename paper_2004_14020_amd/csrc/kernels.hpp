@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "slices.hpp"
 #include "tiles.hpp"
 
 namespace caramel {
@@ -58,6 +59,10 @@ struct CopyArgs {
 hipError_t launch_ring_reduce(const ReduceArgs& a, hipStream_t stream);
 // The same for a job that was cut into slices.
 hipError_t launch_slices(const SliceArgs& a, hipStream_t stream);
+// Writes the tables `at` and `bytes` (SliceTable) from the pieces and the (n_tensors + 1) x W base addresses; all in
+// device memory.
+hipError_t launch_slice_table(const SliceTable& t, const SlicePiece* pieces, const uint64_t* rows, uint32_t* at,
+                              uint32_t* bytes, hipStream_t stream);
 // Segmented gather (pack) or scatter (unpack) driven by the copy-tile table.
 hipError_t launch_copy(const CopyArgs& a, hipStream_t stream);
 

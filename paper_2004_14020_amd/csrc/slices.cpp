@@ -5,37 +5,34 @@
 namespace caramel {
 namespace {
 
-// A piece of a row inside one ring segment.
-struct Piece {
-  uint32_t row, first;  // `first`: worker that is added first
-  uint64_t at, end;     // bytes from the start of the row
-  uint64_t phase;       // position of the row's start inside an aligned block of kSliceBytes: the same in
-                        // every replica, or that of most
-  uint64_t slices() const { return (end + phase + kSliceBytes - 1) / kSliceBytes - (at + phase) / kSliceBytes; }
-};
+// Position of a row's start inside an aligned block of kSliceBytes: the same in every replica, or that of most.
+uint64_t common_phase(const uint64_t* row_addr, uint32_t row, uint32_t W) {
+  const uint64_t* a = row_addr + size_t(row) * W;
+  uint64_t phase = 0;
+  uint32_t best = 0;
+  for (uint32_t w = 0; w < W && 2 * best < W; ++w) {
+    const uint64_t mine = a[w] % kSliceBytes;
+    uint32_t n = 0;
+    for (uint32_t x = 0; x < W; ++x) n += a[x] % kSliceBytes == mine;
+    if (n > best) best = n, phase = mine;
+  }
+  return phase;
+}
 
-// Calls f(piece) for every piece of every unit, in unit order.
-template <typename F>
-void for_each_piece(const HostPlan& p, const uint64_t* row_addr, F&& f) {
+}  // namespace
+
+uint64_t slice_pieces(const HostPlan& p, const uint64_t* row_addr, std::vector<SlicePiece>& out) {
+  out.clear();
   const uint32_t W = p.cfg.world;
   const uint64_t es = p.elem_size();
+  uint64_t n = 0, phase = 0;
   uint32_t phase_row = ~0u;
-  uint64_t phase = 0;
-  auto common_phase = [&](uint32_t row) {
-    if (row == phase_row) return phase;
-    const uint64_t* a = row_addr + size_t(row) * W;
-    uint32_t best = 0;
-    for (uint32_t w = 0; w < W && 2 * best < W; ++w) {
-      const uint64_t mine = a[w] % kSliceBytes;
-      uint32_t n = 0;
-      for (uint32_t x = 0; x < W; ++x) n += a[x] % kSliceBytes == mine;
-      if (n > best) best = n, phase = mine;
-    }
-    phase_row = row;
-    return phase;
-  };
-  auto cut = [&](uint32_t row, uint64_t row_elem, uint64_t n, uint32_t first) {
-    f(Piece{row, first, row_elem * es, (row_elem + n) * es, common_phase(row)});
+  // `elems` of `row` from element `row_elem` on, added from worker `first` on
+  auto cut = [&](uint32_t row, uint64_t row_elem, uint64_t elems, uint32_t first) {
+    if (row != phase_row) phase = common_phase(row_addr, row, W), phase_row = row;
+    const uint64_t at = row_elem * es, end = at + elems * es;
+    out.push_back(SlicePiece{uint32_t(n), row, uint32_t(at / 16), uint32_t(end - at), uint16_t(phase), uint16_t(first)});
+    n += (end + phase + kSliceBytes - 1) / kSliceBytes - (at + phase) / kSliceBytes;
   };
   for (uint32_t ui = 0; ui < p.units.size(); ++ui) {
     const caramel_unit& u = p.units[ui];
@@ -57,9 +54,8 @@ void for_each_piece(const HostPlan& p, const uint64_t* row_addr, F&& f) {
         add(ent[k].tensor, ent[k].tensor_off, ent[k].unit_off, ent[k].unit_off + ent[k].elems);
     }
   }
+  return n;
 }
-
-}  // namespace
 
 // Up to 32 MiB per replica slices are the better cut but for the shapes that choose_slices leaves out.  Few workers
 // have them longer: their walks over long tiles are short, and a tile that is left over at the end, or at a segment
@@ -72,12 +68,6 @@ bool may_have_slices(const HostPlan& p) {
   const bool tree = p.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
   const uint64_t mib = W == 2 ? 112 : (W > 2 && W <= (tree ? 4u : 6u) ? 48 : (!tree && (W == 7 || W == 8) ? 36 : 32));
   return p.replica_elems * p.elem_size() < mib << 20;
-}
-
-uint64_t count_slices(const HostPlan& p, const uint64_t* row_addr) {
-  uint64_t n = 0;
-  for_each_piece(p, row_addr, [&](const Piece& c) { n += c.slices(); });
-  return n;
 }
 
 // Measured on MI355X, microseconds, tiles / slices, data not in the last-level cache where they fit no more.
@@ -144,42 +134,28 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n) {
   return s;
 }
 
-void build_slices(const HostPlan& p, const SliceShape& shape, const uint64_t* row_addr, SliceTable& out) {
-  out = SliceTable{};
-  if (!shape.vecs) return;
-  const uint32_t W = p.cfg.world, V = shape.vecs, waves = shape.lanes / 64;
-  const uint64_t n = count_slices(p, row_addr);
+SliceTable slice_table(const HostPlan& p, const SliceShape& shape, uint64_t n_slices, uint64_t n_pieces,
+                       const uint64_t* row_addr) {
+  SliceTable t;
+  if (!shape.vecs) return t;
+  const uint32_t W = p.cfg.world;
   uint64_t lo = ~uint64_t(0), hi = 0;
-  for (size_t t = 0; t < p.tensor_elems.size(); ++t)
+  for (size_t r = 0; r < p.tensor_elems.size(); ++r)
     for (uint32_t w = 0; w < W; ++w) {
-      const uint64_t a = row_addr[t * W + w];
+      const uint64_t a = row_addr[r * W + w];
       lo = std::min(lo, a);
-      hi = std::max(hi, a + p.tensor_elems[t] * p.elem_size());
+      hi = std::max(hi, a + p.tensor_elems[r] * p.elem_size());
     }
-  if ((hi - lo) >> 36) return;
-  out.base = lo;
-  out.lanes = shape.lanes;
-  out.vecs = V;
-  out.groups = uint32_t((n + shape.share - 1) / shape.share);
-  // (sixteen more: the kernel for one slice per wavefront looks eight workers up at a time)
-  out.at.assign(size_t(out.groups) * waves * V * W + 16, 0);
-  out.bytes.assign(size_t(out.groups) * waves * (V + 1), 0);
-  uint64_t i = 0;
-  std::vector<uint64_t> base(W);
-  for_each_piece(p, row_addr, [&](const Piece& c) {
-    for (uint32_t k = 0; k < W; ++k) base[k] = row_addr[size_t(c.row) * W + (c.first + k) % W] - lo;
-    for (uint64_t at = c.at, len; at < c.end; at += len, ++i) {
-      // slices end on multiples of kSliceBytes in memory
-      len = std::min(kSliceBytes - (c.phase + at) % kSliceBytes, c.end - at);
-      const uint32_t r = uint32_t(i % shape.share), u = r / waves;
-      const size_t wave = size_t(i / shape.share) * waves + r % waves;
-      uint32_t* b = &out.bytes[wave * (V + 1)];
-      b[u] = uint32_t(len + 3) & ~3u;
-      if (len & 3u) b[V] |= 1u << u;
-      uint32_t* a = &out.at[wave * W * V + u];
-      for (uint32_t k = 0; k < W; ++k) a[size_t(k) * V] = uint32_t((base[k] + at) / 16);
-    }
-  });
+  if ((hi - lo) >> 36) return t;
+  t.lanes = shape.lanes;
+  t.vecs = shape.vecs;
+  t.share = shape.share;
+  t.groups = uint32_t((n_slices + shape.share - 1) / shape.share);
+  t.world = W;
+  t.slices = uint32_t(n_slices);
+  t.pieces = uint32_t(n_pieces);
+  t.base = lo;
+  return t;
 }
 
 }  // namespace caramel

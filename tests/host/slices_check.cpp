@@ -2,6 +2,7 @@
 // of every tensor exactly once and nothing else, each stays inside its tensor and inside one aligned block
 // of kSliceBytes in the replicas that share a position, and every element is added in the order of workers that
 // the tile tables (the general path) give it.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -39,10 +40,25 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
   for (const ReduceTile& t : tt.direct)
     for (uint32_t k = 0; k < t.n_elems; ++k) first[t.row][t.vec_off * (16 / es) + k] = uint8_t(t.first);
 
-  SliceTable st;
-  build_slices(p, shape, rows.data(), st);
-  CHECK(st.lanes == shape.lanes && st.vecs == V && shape.share <= waves * V);
-  CHECK(st.at.size() == size_t(st.groups) * waves * V * W + 16 && st.bytes.size() == size_t(st.groups) * waves * (V + 1));
+  std::vector<SlicePiece> pieces;
+  const uint64_t n = slice_pieces(p, rows.data(), pieces);
+  const SliceTable t = slice_table(p, shape, n, pieces.size(), rows.data());
+  CHECK(t.lanes == shape.lanes && t.vecs == V && shape.share <= waves * V);
+  CHECK(t.at_words() == size_t(t.groups) * waves * V * W + 16 && t.bytes_words() == size_t(t.groups) * waves * (V + 1));
+  // as k_slice_table does, a lane per slice and up to 16 steps
+  struct {
+    uint64_t base;
+    uint32_t groups;
+    std::vector<uint32_t> at, bytes;
+  } st{t.base, t.groups, std::vector<uint32_t>(t.at_words()), std::vector<uint32_t>(t.bytes_words())};
+  for (uint32_t wave = 0; wave < t.waves(); ++wave)
+    for (uint32_t u = 0; u < V; ++u) {
+      uint32_t len = 0;
+      for (uint32_t k = 0; k < W; k += 16)
+        len = place_slice(t, pieces.data(), rows.data(), wave, u, k, std::min(k + 16, W), &st.at[size_t(wave) * W * V + u]);
+      st.bytes[size_t(wave) * (V + 1) + u] = (len + 3) & ~3u;
+      if (len & 3u) st.bytes[size_t(wave) * (V + 1) + V] |= 1u << u;
+    }
   std::map<uint64_t, size_t> at;  // worker 0's tensors by address
   for (size_t t = 0; t < first.size(); ++t) at[rows[t * W]] = t;
   uint64_t slices = 0;
@@ -79,7 +95,11 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
       }
     }
   }
-  CHECK(slices == count_slices(p, rows.data()));
+  CHECK(slices == n);
+  // what the host works out and a bind sends: at most two pieces per tensor and segment or chunk, however long
+  uint64_t parts = 0;
+  for (size_t u = 0; u < p.units.size(); ++u) parts += p.units[u].n_entries + W;
+  CHECK(pieces.size() <= parts);
   for (const auto& s : seen)
     for (uint8_t x : s) CHECK(x == 1);
 }
@@ -115,11 +135,12 @@ int main() {
     if (it % 20 == 1 && rows.size() > 2 * cfg.world) {  // out of the table's reach
       std::vector<uint64_t> far = rows;
       far[0] += uint64_t(1) << 37;
-      SliceTable st;
-      build_slices(p, SliceShape{256, 1, 4}, far.data(), st);
-      CHECK(st.groups == 0 && st.at.empty());
+      std::vector<SlicePiece> pieces;
+      const uint64_t n = slice_pieces(p, far.data(), pieces);
+      CHECK(slice_table(p, SliceShape{256, 1, 4}, n, pieces.size(), far.data()).groups == 0);
     }
-    const SliceShape own = choose_slices(p, count_slices(p, rows.data()));
+    std::vector<SlicePiece> pieces;
+    const SliceShape own = choose_slices(p, slice_pieces(p, rows.data(), pieces));
     if (own.vecs) {
       CHECK(own.share && own.share <= own.lanes / 64 * own.vecs);
       ++shapes[std::to_string(own.lanes) + (own.vecs == 1 ? " x 1" : " x n")];
