@@ -90,7 +90,10 @@ bool may_have_slices(const HostPlan& p) {
 //  * Above one round of 256 lanes, fp32 chains: from 16 workers on one round of 512 lanes (24 workers 26 MiB 247 /
 //    238, 32 workers 31 MiB 414 / 375); 8 to 15 workers 1024 lanes in equal shares (8 workers 31 MiB 100 / 90, 12
 //    workers 144 / 136), but where that comes to seven vectors per lane again 512 lanes (12 workers 27 MiB
-//    122.5 / 125.4, with 512 lanes 122).  Up to 7 workers, and with bf16 but for 9 to 24 workers from 20 MiB on, one
+//    122.5 / 125.4, with 512 lanes 122), and rings one vector per lane where a sixth row of slices would be nearly
+//    empty, over 9 workers also where it is not full (tiles / 1024 lanes / one vector: 20 MiB 8 workers 62.7 / 62.9 /
+//    60.4, 9 68.9 / 70.8 / 67.4, 12 92.0 / 93.3 / 92.0; 23 MiB 9 workers 77.9 / 78.3 / 77.0; shuffle over 12 and more
+//    of 20 MiB 1024 lanes 1 to 5 % faster).  Up to 7 workers, and with bf16 but for 9 to 24 workers from 20 MiB on, one
 //    vector per lane in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; 8 workers bf16
 //    98 / 92, 1024 lanes 96; 12 workers bf16 143 / 139, one vector 142.5), and so for trees (8 workers 25 MiB 79.9 /
 //    75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 / 13.0), and so have
@@ -121,6 +124,8 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n) {
   if (W == 1 || (tree && W == 64 && !bf16) || (bf16 && W > 8 && W < 16 && n > 24576 && n <= 28672)) return {};
   s.through = true;
   if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
+  const bool ring = p.cfg.pattern == CARAMEL_PATTERN_RING;
+  if (!bf16 && ring && W >= 8 && W < 16 && n <= (W == 9 ? 24576u : 82u * kComputeUnits)) return s;
   if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
     s.lanes = 512;
     s.vecs = std::clamp(up((n + 1549) / 1550, 2), 14u, most);

@@ -104,7 +104,32 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
     for (uint8_t x : s) CHECK(x == 1);
 }
 
+// The shape of a job of n slices (all of them full), as "lanes x vecs", "tiles" if it has none.
+static std::string shape_of(uint32_t world, uint32_t dtype, uint32_t pattern, uint64_t n) {
+  HostPlan p;
+  p.cfg.world = world;
+  p.cfg.dtype = dtype;
+  p.cfg.pattern = pattern;
+  p.replica_elems = n * kSliceBytes / p.elem_size();
+  const SliceShape s = choose_slices(p, n);
+  return s.vecs ? std::to_string(s.lanes) + " x " + std::to_string(s.vecs) : "tiles";
+}
+
+// Lines at which sweeps have found the other side to be slower.
+static void lines() {
+  const uint32_t ring = CARAMEL_PATTERN_RING, shuffle = CARAMEL_PATTERN_SHUFFLE, f32 = CARAMEL_F32;
+  for (uint32_t pattern : {ring, shuffle})
+    for (uint32_t W = 8; W < 16; ++W) {
+      CHECK(shape_of(W, f32, pattern, 20480) == "256 x 20");
+      for (uint64_t n : {20481, 20992}) CHECK(shape_of(W, f32, pattern, n) == (pattern == ring ? "256 x 1" : "1024 x 6"));
+      for (uint64_t n : {20993, 24576})
+        CHECK(shape_of(W, f32, pattern, n) == (pattern == ring && W == 9 ? "256 x 1" : "1024 x 6"));
+      CHECK(shape_of(W, f32, pattern, 24577) == "512 x 16");
+    }
+}
+
 int main() {
+  lines();
   std::mt19937_64 rng(11);
   auto pick = [&](std::initializer_list<uint64_t> xs) { return *(xs.begin() + rng() % xs.size()); };
   for (int it = 0; it < 260; ++it) {
