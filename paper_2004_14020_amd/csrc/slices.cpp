@@ -97,8 +97,9 @@ bool may_have_slices(const HostPlan& p) {
 //    vector per lane in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; 8 workers bf16
 //    98 / 92, 1024 lanes 96; 12 workers bf16 143 / 139, one vector 142.5), and so for trees (8 workers 25 MiB 79.9 /
 //    75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 / 13.0), and so have
-//    halving-doubling over 64 in fp32 (16 MiB 440 / 447) and 9 to 15 workers in bf16 where a second round of 1024 lanes
-//    would be nearly empty (12 workers 24 MiB 108 / 111).
+//    halving-doubling over 32 and 64 (one large tensor 2 to 5 % slower, 32 workers 31 MiB 411.8 / 422.5, 64 in bf16 15 MiB
+//    418 / 435; many tensors even to 2 % faster) and 9 to 15 workers in bf16 where a second round of 1024 lanes would be
+//    nearly empty (12 workers 24 MiB 108 / 111).
 SliceShape choose_slices(const HostPlan& p, uint64_t n) {
   const uint32_t W = p.cfg.world;
   const uint64_t replica_bytes = p.replica_elems * p.elem_size();
@@ -121,7 +122,7 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n) {
     s.share = 4 * s.vecs;
     return s;
   }
-  if (W == 1 || (tree && W == 64 && !bf16) || (bf16 && W > 8 && W < 16 && n > 24576 && n <= 28672)) return {};
+  if (W == 1 || (tree && W >= 32) || (bf16 && W > 8 && W < 16 && n > 24576 && n <= 28672)) return {};
   s.through = true;
   if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
   const bool ring = p.cfg.pattern == CARAMEL_PATTERN_RING;

@@ -126,6 +126,14 @@ static void lines() {
         CHECK(shape_of(W, f32, pattern, n) == (pattern == ring && W == 9 ? "256 x 1" : "1024 x 6"));
       CHECK(shape_of(W, f32, pattern, 24577) == "512 x 16");
     }
+  // vectors per lane of one round of a tree over 32 and 64 workers, and what lies beyond
+  const uint32_t hd = CARAMEL_PATTERN_HALVING_DOUBLING, most[2][2] = {{14, 12}, {8, 8}};
+  for (uint32_t dtype : {uint32_t(CARAMEL_F32), uint32_t(CARAMEL_BF16)})
+    for (uint32_t W : {32u, 64u}) {
+      const uint32_t v = most[dtype == CARAMEL_BF16][W == 64];
+      CHECK(shape_of(W, dtype, hd, v * 1024) == "256 x " + std::to_string(v));
+      for (uint64_t n : {uint64_t(v * 1024 + 1), uint64_t(32767)}) CHECK(shape_of(W, dtype, hd, n) == "tiles");
+    }
 }
 
 int main() {
