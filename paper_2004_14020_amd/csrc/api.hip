@@ -865,7 +865,7 @@ int upload_tables(caramel_plan* p, bool staged) {
   if (p->opt.tiles_left_to_library() && may_have_slices(h)) {
     std::vector<SlicePiece> pieces;
     const uint64_t n = slice_pieces(h, bd.rows.data(), pieces);
-    const SliceShape shape = choose_slices(h, n);
+    const SliceShape shape = choose_slices(h, n, pieces.size());
     const SliceTable t = slice_table(h, shape, n, pieces.size(), bd.rows.data());
     if (t.groups) {
       p->slices = SliceArgs{nullptr, nullptr, t.base, t.groups, t.lanes, t.vecs, h.cfg.world, h.cfg.dtype == CARAMEL_BF16,

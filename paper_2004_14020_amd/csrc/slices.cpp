@@ -59,15 +59,30 @@ uint64_t slice_pieces(const HostPlan& p, const uint64_t* row_addr, std::vector<S
 
 // Up to 32 MiB per replica slices are the better cut but for the shapes that choose_slices leaves out.  Few workers
 // have them longer: their walks over long tiles are short, and a tile that is left over at the end, or at a segment
-// boundary, weighs as much as elsewhere (us, tiles / slices, fp32 ring unless said otherwise: 2 workers 90 MiB 69.5 / 61.0,
-// 110 MiB 80.2 / 75.0, bf16 75.0 / 73.8, but 190 MiB 125.4 / 126.6; 4 workers 42 MiB 61.3 / 59.5, bf16 56 MiB 81.0 / 83.4; 6
-// workers 48 MiB 106.2 / 101.5, 65 MiB 137.6 / 141.0; 8 workers 33 MiB 109 / 103, 37 MiB 118.5 / 112.1, but 12 large
-// tensors of 38 MiB 116.8 / 119.8, shuffle 108.9 / 116.3; 12 workers 37 MiB 166.5 / 167.6; halving-doubling over 4 42 MiB 63.1 / 60.4, over 8 33 MiB 96.4 / 98.9).
+// boundary, weighs as much as elsewhere (us, tiles / slices, fp32 ring unless said otherwise: 2 workers 90 MiB 69.5 /
+// 61.0, 110 MiB 80.2 / 75.0, bf16 75.0 / 73.8, but 190 MiB 125.4 / 126.6; 4 workers 42 MiB 61.3 / 59.5, bf16 56 MiB
+// 81.0 / 83.4; 6 workers 48 MiB 106.2 / 101.5, 65 MiB 137.6 / 141.0; 8 workers 33 MiB 109 / 103, 37 MiB 118.5 / 112.1,
+// but shuffle 38 MiB 108.9 / 116.3; 12 workers 37 MiB 166.5 / 167.6; halving-doubling over 4 42 MiB 63.1 / 60.4, over
+// 8 33 MiB 96.4 / 98.9).
 bool may_have_slices(const HostPlan& p) {
   const uint32_t W = p.cfg.world;
   const bool tree = p.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING;
   const uint64_t mib = W == 2 ? 112 : (W > 2 && W <= (tree ? 4u : 6u) ? 48 : (!tree && (W == 7 || W == 8) ? 36 : 32));
   return p.replica_elems * p.elem_size() < mib << 20;
+}
+
+// Longest mean length of the pieces with which a job above 32 MiB per replica has slices: what they save are tiles that
+// are left over at the ends of pieces.  Tiles = 1, three placements of the replicas each: shuffle over 8 workers, 33 to 35.5
+// MiB: pieces of 170 KiB (200 tensors) 0.93 to 0.97, 450 KiB (60 tensors) 0.97 to 1.06, 3 to 4.5 MiB (four tensors and one)
+// 0.99 to 1.09; rings over 8, which have eight times the pieces: 90 KiB 0.90 to 0.93, 430 KiB 0.94 to 1.00, 540 KiB (one
+// tensor) 0.92 to 1.03, 568 KiB 0.99 to 1.05.  7 workers: 3 MiB 0.95 to 1.03, 4.3 MiB 1.00 to 1.03.  2 workers in bf16 from 90
+// MiB on: 1 MiB 0.90 to 0.97, 4 MiB 0.98 to 1.01, 6 to 8 MiB 0.97 to 1.03, 11 to 14 MiB 1.00 to 1.04; in fp32 at most 1.00.
+// 3 to 6 workers: 4 to 6 MiB 0.96 to 1.02.
+static uint64_t longest_mean_piece(const HostPlan& p) {
+  const uint32_t W = p.cfg.world;
+  if (W == 8) return (p.cfg.pattern == CARAMEL_PATTERN_RING ? 560 : 448) << 10;
+  if (W == 7) return 4 << 20;
+  return W == 2 && p.cfg.dtype == CARAMEL_BF16 ? 5 << 20 : ~uint64_t(0);
 }
 
 // Measured on MI355X, microseconds, tiles / slices, data not in the last-level cache where they fit no more.
@@ -100,11 +115,12 @@ bool may_have_slices(const HostPlan& p) {
 //    halving-doubling over 32 and 64 (one large tensor 2 to 5 % slower, 32 workers 31 MiB 411.8 / 422.5, 64 in bf16 15 MiB
 //    418 / 435; many tensors even to 2 % faster) and 9 to 15 workers in bf16 where a second round of 1024 lanes would be
 //    nearly empty (12 workers 24 MiB 108 / 111).
-SliceShape choose_slices(const HostPlan& p, uint64_t n) {
+SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
   const uint32_t W = p.cfg.world;
   const uint64_t replica_bytes = p.replica_elems * p.elem_size();
   // (the table of a job of very many tiny tensors would outgrow them)
   if (!may_have_slices(p) || n == 0 || n * W > (1u << 23)) return {};
+  if (replica_bytes >= (uint64_t(32) << 20) && replica_bytes / n_pieces > longest_mean_piece(p)) return {};
   const bool bf16 = p.cfg.dtype == CARAMEL_BF16;
   const bool tree = p.cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && W > 1;
   // vectors per lane that fit the registers: two buffers and the sum, or four buffers and a sum for every level

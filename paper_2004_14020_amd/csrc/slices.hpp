@@ -87,7 +87,7 @@ bool may_have_slices(const HostPlan& p);
 // The pieces of the plan's units, batches in place; `row_addr`: (n_tensors + 1) x W base addresses.  Returns how many
 // slices they come to.
 uint64_t slice_pieces(const HostPlan& p, const uint64_t* row_addr, std::vector<SlicePiece>& out);
-SliceShape choose_slices(const HostPlan& p, uint64_t n_slices);
+SliceShape choose_slices(const HostPlan& p, uint64_t n_slices, uint64_t n_pieces);
 // No workgroups if some tensors lie too far apart (64 GiB) for the table.
 SliceTable slice_table(const HostPlan& p, const SliceShape& shape, uint64_t n_slices, uint64_t n_pieces,
                        const uint64_t* row_addr);

@@ -105,19 +105,19 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
 }
 
 // The shape of a job of n slices (all of them full), as "lanes x vecs", "tiles" if it has none.
-static std::string shape_of(uint32_t world, uint32_t dtype, uint32_t pattern, uint64_t n) {
+static std::string shape_of(uint32_t world, uint32_t dtype, uint32_t pattern, uint64_t n, uint64_t pieces = 1000) {
   HostPlan p;
   p.cfg.world = world;
   p.cfg.dtype = dtype;
   p.cfg.pattern = pattern;
   p.replica_elems = n * kSliceBytes / p.elem_size();
-  const SliceShape s = choose_slices(p, n);
+  const SliceShape s = choose_slices(p, n, pieces);
   return s.vecs ? std::to_string(s.lanes) + " x " + std::to_string(s.vecs) : "tiles";
 }
 
 // Lines at which sweeps have found the other side to be slower.
 static void lines() {
-  const uint32_t ring = CARAMEL_PATTERN_RING, shuffle = CARAMEL_PATTERN_SHUFFLE, f32 = CARAMEL_F32;
+  const uint32_t ring = CARAMEL_PATTERN_RING, shuffle = CARAMEL_PATTERN_SHUFFLE, f32 = CARAMEL_F32, bf16 = CARAMEL_BF16;
   for (uint32_t pattern : {ring, shuffle})
     for (uint32_t W = 8; W < 16; ++W) {
       CHECK(shape_of(W, f32, pattern, 20480) == "256 x 20");
@@ -128,12 +128,26 @@ static void lines() {
     }
   // vectors per lane of one round of a tree over 32 and 64 workers, and what lies beyond
   const uint32_t hd = CARAMEL_PATTERN_HALVING_DOUBLING, most[2][2] = {{14, 12}, {8, 8}};
-  for (uint32_t dtype : {uint32_t(CARAMEL_F32), uint32_t(CARAMEL_BF16)})
+  for (uint32_t dtype : {f32, bf16})
     for (uint32_t W : {32u, 64u}) {
-      const uint32_t v = most[dtype == CARAMEL_BF16][W == 64];
+      const uint32_t v = most[dtype == bf16][W == 64];
       CHECK(shape_of(W, dtype, hd, v * 1024) == "256 x " + std::to_string(v));
       for (uint64_t n : {uint64_t(v * 1024 + 1), uint64_t(32767)}) CHECK(shape_of(W, dtype, hd, n) == "tiles");
     }
+  // from 32 MiB on, long pieces
+  const struct {
+    uint32_t world, dtype, pattern, mib, most_kib;
+  } long_jobs[] = {{8, f32, shuffle, 35, 448},   {8, bf16, shuffle, 35, 448},  {8, f32, ring, 35, 560},
+                   {8, bf16, ring, 35, 560},     {7, f32, shuffle, 35, 4096},  {7, bf16, ring, 35, 4096},
+                   {2, bf16, shuffle, 105, 5120}, {2, bf16, ring, 105, 5120},  {2, bf16, hd, 105, 5120}};
+  for (const auto& j : long_jobs) {
+    const uint64_t n = uint64_t(j.mib) << 10, line = n / j.most_kib;
+    CHECK(shape_of(j.world, j.dtype, j.pattern, n, line + 1) == "256 x 1");
+    CHECK(shape_of(j.world, j.dtype, j.pattern, n, line - 1) == "tiles");
+    CHECK(shape_of(j.world, j.dtype, j.pattern, 32767, 1) != "tiles");
+  }
+  for (uint32_t W = 3; W <= 6; ++W) CHECK(shape_of(W, f32, shuffle, 47 << 10, 1) == "256 x 1");
+  CHECK(shape_of(2, f32, shuffle, 111 << 10, 1) == "256 x 1");
 }
 
 int main() {
@@ -173,7 +187,8 @@ int main() {
       CHECK(slice_table(p, SliceShape{256, 1, 4}, n, pieces.size(), far.data()).groups == 0);
     }
     std::vector<SlicePiece> pieces;
-    const SliceShape own = choose_slices(p, slice_pieces(p, rows.data(), pieces));
+    const uint64_t n = slice_pieces(p, rows.data(), pieces);
+    const SliceShape own = choose_slices(p, n, pieces.size());
     if (own.vecs) {
       CHECK(own.share && own.share <= own.lanes / 64 * own.vecs);
       ++shapes[std::to_string(own.lanes) + (own.vecs == 1 ? " x 1" : " x n")];
