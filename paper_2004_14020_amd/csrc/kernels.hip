@@ -1243,68 +1243,32 @@ hipError_t launch_slice_table(const SliceTable& t, const SlicePiece* pieces, con
 hipError_t launch_slices(const SliceArgs& a, hipStream_t s) {
   const float inv_w = 1.0f / float(a.world);
   const dim3 grid(a.groups), lanes(a.lanes);
-#define CARAMEL_SLICES(BF, P, N, L) \
-  if (a.bf16 == BF && a.policy == P && a.vecs == N && a.lanes == L) { \
-    hipLaunchKernelGGL((k_slices<BF, P, N, L>), grid, lanes, 0, s, a.at, a.bytes, a.base, a.world, inv_w); \
+  const bool through = a.policy == kThrough, one = a.vecs == 1 && a.lanes == 256;
+#define CARAMEL_ROUND(BF, TH, N, L) \
+  if (!a.tree && a.bf16 == BF && through == TH && a.vecs == N && a.lanes == L) { \
+    hipLaunchKernelGGL((k_slices<BF, TH ? kThrough : kStream, N, L>), grid, lanes, 0, s, a.at, a.bytes, a.base, a.world, inv_w); \
     return hipGetLastError(); \
   }
-#define CARAMEL_ROUND(BF, N) CARAMEL_SLICES(BF, kStream, N, 256) CARAMEL_SLICES(BF, kThrough, N, 256)
-#define CARAMEL_SLICE2(P, CW) \
-  if (a.bf16) hipLaunchKernelGGL((k_slice<true, P, CW>), grid, lanes, 0, s, a.at, a.bytes, a.base, a.world, inv_w); \
-  else hipLaunchKernelGGL((k_slice<false, P, CW>), grid, lanes, 0, s, a.at, a.bytes, a.base, a.world, inv_w)
-#define CARAMEL_SLICE(CW) \
-  if (a.vecs == 1 && a.lanes == 256 && (CW == 0 || a.world == CW)) { \
-    if (a.policy == kThrough) CARAMEL_SLICE2(kThrough, CW); else CARAMEL_SLICE2(kStream, CW); \
+#define CARAMEL_ONE(BF, TH, CW) \
+  if (!a.tree && one && a.bf16 == BF && through == TH && (CW == 0 || a.world == CW)) { \
+    hipLaunchKernelGGL((k_slice<BF, TH ? kThrough : kStream, CW>), grid, lanes, 0, s, a.at, a.bytes, a.base, a.world, inv_w); \
     return hipGetLastError(); \
   }
 #define CARAMEL_TREE_ROUND(W, BF, N) \
-  if (a.tree && a.world == W && a.bf16 == BF && a.vecs == N && a.lanes == 256 && a.policy == kStream) { \
+  if (a.tree && a.world == W && a.bf16 == BF && !through && a.vecs == N && a.lanes == 256) { \
     hipLaunchKernelGGL((k_tree_slices<BF, kStream, W, N>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w); \
     return hipGetLastError(); \
   }
-#define CARAMEL_TREE_SLICE2(W, P) \
-  if (a.bf16) hipLaunchKernelGGL((k_tree_slice<true, P, W>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w); \
-  else hipLaunchKernelGGL((k_tree_slice<false, P, W>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w)
-#define CARAMEL_TREE_SLICE(W) \
-  if (a.tree && a.world == W && a.vecs == 1 && a.lanes == 256) { \
-    if (a.policy == kThrough) CARAMEL_TREE_SLICE2(W, kThrough); else CARAMEL_TREE_SLICE2(W, kStream); \
+#define CARAMEL_TREE_ONE(W, BF, TH) \
+  if (a.tree && one && a.world == W && a.bf16 == BF && through == TH) { \
+    hipLaunchKernelGGL((k_tree_slice<BF, TH ? kThrough : kStream, W>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w); \
     return hipGetLastError(); \
   }
-#define CARAMEL_TREE_ROUNDS(W, BF) CARAMEL_TREE_ROUND(W, BF, 2) CARAMEL_TREE_ROUND(W, BF, 4) CARAMEL_TREE_ROUND(W, BF, 6) CARAMEL_TREE_ROUND(W, BF, 8)
-  if (a.tree) {
-    CARAMEL_TREE_SLICE(2) CARAMEL_TREE_SLICE(4) CARAMEL_TREE_SLICE(8) CARAMEL_TREE_SLICE(16) CARAMEL_TREE_SLICE(32)
-    CARAMEL_TREE_SLICE(64)
-    CARAMEL_TREE_ROUNDS(2, false) CARAMEL_TREE_ROUND(2, false, 12) CARAMEL_TREE_ROUND(2, false, 16) CARAMEL_TREE_ROUND(2, false, 20)
-    CARAMEL_TREE_ROUNDS(4, false) CARAMEL_TREE_ROUND(4, false, 12) CARAMEL_TREE_ROUND(4, false, 16) CARAMEL_TREE_ROUND(4, false, 20)
-    CARAMEL_TREE_ROUNDS(8, false) CARAMEL_TREE_ROUND(8, false, 12) CARAMEL_TREE_ROUND(8, false, 16) CARAMEL_TREE_ROUND(8, false, 18)
-    CARAMEL_TREE_ROUNDS(16, false) CARAMEL_TREE_ROUND(16, false, 12) CARAMEL_TREE_ROUND(16, false, 14)
-    CARAMEL_TREE_ROUNDS(32, false) CARAMEL_TREE_ROUND(32, false, 12) CARAMEL_TREE_ROUND(32, false, 14)
-    CARAMEL_TREE_ROUNDS(64, false) CARAMEL_TREE_ROUND(64, false, 12)
-    CARAMEL_TREE_ROUNDS(2, true) CARAMEL_TREE_ROUND(2, true, 12) CARAMEL_TREE_ROUND(2, true, 16)
-    CARAMEL_TREE_ROUNDS(4, true) CARAMEL_TREE_ROUND(4, true, 12) CARAMEL_TREE_ROUND(4, true, 16)
-    CARAMEL_TREE_ROUNDS(8, true) CARAMEL_TREE_ROUND(8, true, 12) CARAMEL_TREE_ROUND(8, true, 14)
-    CARAMEL_TREE_ROUNDS(16, true) CARAMEL_TREE_ROUND(16, true, 10)
-    CARAMEL_TREE_ROUNDS(32, true) CARAMEL_TREE_ROUNDS(64, true)
-    return hipErrorInvalidValue;
-  }
-#undef CARAMEL_TREE_ROUND
-#undef CARAMEL_TREE_ROUNDS
-#undef CARAMEL_TREE_SLICE
-#undef CARAMEL_TREE_SLICE2
-  CARAMEL_SLICE(2) CARAMEL_SLICE(3) CARAMEL_SLICE(4) CARAMEL_SLICE(8) CARAMEL_SLICE(16) CARAMEL_SLICE(0)
-  CARAMEL_ROUND(false, 4) CARAMEL_ROUND(false, 6) CARAMEL_ROUND(false, 8) CARAMEL_ROUND(false, 10) CARAMEL_ROUND(false, 12)
-  CARAMEL_ROUND(false, 14) CARAMEL_ROUND(false, 16) CARAMEL_ROUND(false, 18) CARAMEL_ROUND(false, 20)
-  CARAMEL_ROUND(true, 4) CARAMEL_ROUND(true, 6) CARAMEL_ROUND(true, 8) CARAMEL_ROUND(true, 10) CARAMEL_ROUND(true, 12)
-  CARAMEL_ROUND(true, 14) CARAMEL_ROUND(true, 16)
-  CARAMEL_SLICES(false, kThrough, 14, 512) CARAMEL_SLICES(false, kThrough, 16, 512)
-  CARAMEL_SLICES(false, kThrough, 18, 512) CARAMEL_SLICES(false, kThrough, 20, 512)
-  CARAMEL_SLICES(false, kThrough, 5, 1024) CARAMEL_SLICES(false, kThrough, 6, 1024)
-  CARAMEL_SLICES(false, kThrough, 7, 1024) CARAMEL_SLICES(false, kThrough, 8, 1024)
-  CARAMEL_SLICES(true, kThrough, 4, 1024) CARAMEL_SLICES(true, kThrough, 5, 1024) CARAMEL_SLICES(true, kThrough, 6, 1024)
-#undef CARAMEL_SLICE2
+  CARAMEL_SLICE_KERNELS(CARAMEL_ROUND, CARAMEL_ONE, CARAMEL_TREE_ROUND, CARAMEL_TREE_ONE)
 #undef CARAMEL_ROUND
-#undef CARAMEL_SLICE
-#undef CARAMEL_SLICES
+#undef CARAMEL_ONE
+#undef CARAMEL_TREE_ROUND
+#undef CARAMEL_TREE_ONE
   return hipErrorInvalidValue;
 }
 

@@ -82,6 +82,46 @@ struct SliceShape {
   bool through = true;           // stores are written through the caches
 };
 
+// The kernels there are: choose_slices returns no other shapes, and each of these for some job.
+//   ROUND(bf16, through, vecs, lanes)   chains, several slices per wavefront
+//   ONE(bf16, through, world)           chains, one slice per wavefront; world 0: any other (listed last)
+//   TREE_ROUND(world, bf16, vecs)       halving-doubling in one round of 256 lanes, not through
+//   TREE_ONE(world, bf16, through)      halving-doubling, one slice per wavefront
+#define CARAMEL_ROUNDS_256(ROUND, BF16) \
+  ROUND(BF16, false, 4, 256) ROUND(BF16, false, 6, 256) ROUND(BF16, false, 8, 256) ROUND(BF16, false, 10, 256) \
+  ROUND(BF16, false, 12, 256) ROUND(BF16, false, 14, 256) ROUND(BF16, false, 16, 256) ROUND(BF16, true, 6, 256) \
+  ROUND(BF16, true, 8, 256) ROUND(BF16, true, 10, 256) ROUND(BF16, true, 12, 256) ROUND(BF16, true, 14, 256) \
+  ROUND(BF16, true, 16, 256)
+#define CARAMEL_ONES(ONE, BF16, THROUGH) \
+  ONE(BF16, THROUGH, 2) ONE(BF16, THROUGH, 3) ONE(BF16, THROUGH, 4) ONE(BF16, THROUGH, 8) ONE(BF16, THROUGH, 0)
+#define CARAMEL_TREE_ROUNDS_8(TREE_ROUND, W, BF16) \
+  TREE_ROUND(W, BF16, 2) TREE_ROUND(W, BF16, 4) TREE_ROUND(W, BF16, 6) TREE_ROUND(W, BF16, 8)
+#define CARAMEL_SLICE_KERNELS(ROUND, ONE, TREE_ROUND, TREE_ONE) \
+  ONE(false, false, 16) ONE(true, false, 16) ONE(true, true, 16) \
+  CARAMEL_ONES(ONE, false, false) CARAMEL_ONES(ONE, true, false) CARAMEL_ONES(ONE, false, true) \
+  CARAMEL_ONES(ONE, true, true) \
+  CARAMEL_ROUNDS_256(ROUND, false) ROUND(false, false, 18, 256) ROUND(false, false, 20, 256) \
+  ROUND(false, true, 18, 256) ROUND(false, true, 20, 256) CARAMEL_ROUNDS_256(ROUND, true) \
+  ROUND(false, true, 14, 512) ROUND(false, true, 16, 512) ROUND(false, true, 18, 512) ROUND(false, true, 20, 512) \
+  ROUND(false, true, 5, 1024) ROUND(false, true, 6, 1024) ROUND(false, true, 7, 1024) ROUND(false, true, 8, 1024) \
+  ROUND(true, true, 4, 1024) ROUND(true, true, 5, 1024) ROUND(true, true, 6, 1024) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 2, false) TREE_ROUND(2, false, 12) TREE_ROUND(2, false, 16) TREE_ROUND(2, false, 20) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 4, false) TREE_ROUND(4, false, 12) TREE_ROUND(4, false, 16) TREE_ROUND(4, false, 20) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 8, false) TREE_ROUND(8, false, 12) TREE_ROUND(8, false, 16) TREE_ROUND(8, false, 18) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 16, false) TREE_ROUND(16, false, 12) TREE_ROUND(16, false, 14) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 32, false) TREE_ROUND(32, false, 12) TREE_ROUND(32, false, 14) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 64, false) TREE_ROUND(64, false, 12) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 2, true) TREE_ROUND(2, true, 12) TREE_ROUND(2, true, 16) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 4, true) TREE_ROUND(4, true, 12) TREE_ROUND(4, true, 16) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 8, true) TREE_ROUND(8, true, 12) TREE_ROUND(8, true, 14) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 16, true) TREE_ROUND(16, true, 10) \
+  CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 32, true) CARAMEL_TREE_ROUNDS_8(TREE_ROUND, 64, true) \
+  TREE_ONE(2, false, false) TREE_ONE(4, false, false) TREE_ONE(8, false, false) TREE_ONE(16, false, false) \
+  TREE_ONE(32, false, false) TREE_ONE(64, false, false) TREE_ONE(2, true, false) TREE_ONE(4, true, false) \
+  TREE_ONE(8, true, false) TREE_ONE(16, true, false) TREE_ONE(32, true, false) TREE_ONE(64, true, false) \
+  TREE_ONE(2, false, true) TREE_ONE(4, false, true) TREE_ONE(8, false, true) TREE_ONE(16, false, true) \
+  TREE_ONE(2, true, true) TREE_ONE(4, true, true) TREE_ONE(8, true, true) TREE_ONE(16, true, true)
+
 // Whether choose_slices could ever cut this plan into slices.
 bool may_have_slices(const HostPlan& p);
 // The pieces of the plan's units, batches in place; `row_addr`: (n_tensors + 1) x W base addresses.  Returns how many

@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <map>
 #include <random>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -150,8 +151,56 @@ static void lines() {
   CHECK(shape_of(2, f32, shuffle, 111 << 10, 1) == "256 x 1");
 }
 
+// The kernel that launch_slices takes for a job, and with `all` every one there is.
+static const char* kernel_of(uint32_t world, bool bf16, bool tree, const SliceShape& s, std::set<std::string>* all = nullptr) {
+  const char* found = nullptr;
+  auto match = [&](bool yes, const char* name) {
+    if (all) CHECK(all->insert(name).second);
+    if (yes && !found) found = name;
+  };
+  const bool one = s.vecs == 1 && s.lanes == 256;
+#define ROUND(BF, TH, N, L) \
+  match(!tree && bf16 == BF && s.through == TH && s.vecs == N && s.lanes == L, "slices " #BF " " #TH " " #N " " #L);
+#define ONE(BF, TH, CW) match(!tree && one && bf16 == BF && s.through == TH && (CW == 0 || world == CW), "slice " #BF " " #TH " " #CW);
+#define TREE_ROUND(W, BF, N) \
+  match(tree && world == W && bf16 == BF && !s.through && s.vecs == N && s.lanes == 256, "tree_slices " #W " " #BF " " #N);
+#define TREE_ONE(W, BF, TH) match(tree && one && world == W && bf16 == BF && s.through == TH, "tree_slice " #W " " #BF " " #TH);
+  CARAMEL_SLICE_KERNELS(ROUND, ONE, TREE_ROUND, TREE_ONE)
+  return found;
+}
+
+// Every shape that can be chosen has a kernel and fits what it assumes, and every kernel is chosen for some job.
+static void kernels() {
+  std::set<std::string> all, used;
+  kernel_of(0, false, false, SliceShape{}, &all);
+  for (uint32_t world = 1; world <= CARAMEL_MAX_WORLD; ++world)
+    for (uint32_t dtype : {uint32_t(CARAMEL_F32), uint32_t(CARAMEL_BF16)})
+      for (uint32_t pattern : {CARAMEL_PATTERN_RING, CARAMEL_PATTERN_SHUFFLE, CARAMEL_PATTERN_HALVING_DOUBLING}) {
+        if (pattern == CARAMEL_PATTERN_HALVING_DOUBLING && (world & (world - 1))) continue;
+        const bool tree = pattern == CARAMEL_PATTERN_HALVING_DOUBLING && world > 1;
+        for (uint64_t n = 1; n < 150000; n += n < 70000 ? 61 : 997)
+          for (uint64_t filled : {1024, 700, 200}) {  // bytes of a slice on average
+            HostPlan p;
+            p.cfg.world = world;
+            p.cfg.dtype = dtype;
+            p.cfg.pattern = pattern;
+            p.replica_elems = n * filled / p.elem_size();
+            const SliceShape s = choose_slices(p, n, 1 + n / 64);
+            if (!s.vecs) continue;
+            const char* k = kernel_of(world, dtype == CARAMEL_BF16, tree, s);
+            CHECK(k);
+            CHECK(s.share && s.share <= s.lanes / 64 * s.vecs && s.vecs <= 32);
+            used.insert(k);
+          }
+      }
+  for (const std::string& k : all)
+    if (!used.count(k)) std::printf("never chosen: %s\n", k.c_str());
+  CHECK(used == all);
+}
+
 int main() {
   lines();
+  kernels();
   std::mt19937_64 rng(11);
   auto pick = [&](std::initializer_list<uint64_t> xs) { return *(xs.begin() + rng() % xs.size()); };
   for (int it = 0; it < 260; ++it) {
