@@ -58,11 +58,11 @@ def parse_args():
     return ap.parse_args()
 
 
-def reduce_kernel(pattern: str, world: int, bf16: bool, long_tiles: bool, slices: bool = False) -> str:
-    """The kernel that a reduction over long or small tiles runs, by the library's default rules; `slices`: the
-    job was cut into slices (one per wavefront, k_slice, for the smallest; else k_slices)."""
+def reduce_kernel(pattern: str, world: int, bf16: bool, long_tiles: bool, slices=None) -> str:
+    """The kernel that a reduction over long or small tiles runs, by the library's default rules; `slices`: what
+    Plan.slices() says, (workgroups, lanes, slices per wavefront) if the job is cut into slices."""
     if slices:
-        return "k_tree_slice(s)" if pattern == "hd" and world > 1 else "k_slice(s)"
+        return ("k_tree_slice" if pattern == "hd" and world > 1 else "k_slice") + ("s" if slices[2] > 1 else "")
     if pattern == "hd" and world > 1:
         if long_tiles and not (bf16 and world >= 32):
             return "k_tree_walk"
@@ -242,10 +242,7 @@ def main() -> int:
         v is None for v in (args.launch_mode, args.batch_path, args.tile_vecs, args.max_grid, args.nontemporal, args.unroll,
                             args.block, args.launch_min_bytes, args.align_tiles, args.long_run_bytes))
     as_profiled = args.pattern == "ring" and as_default
-    # with the default options small jobs, and those of few workers that have no long tiles, are cut into slices,
-    # which count as small tiles
-    dom_name = reduce_kernel(args.pattern, wl.world, wl.dtype == cm.BF16, dom is lng,
-                             as_default and dom is sml and (sum(wl.elems()) * es < (32 << 20) or wl.world <= 8))
+    dom_name = reduce_kernel(args.pattern, wl.world, wl.dtype == cm.BF16, dom is lng, plan.slices())
     dom_line = kernel_line(dom) or {}
     span_ms = seq["span_ms"] / max(1, seq["calls"])
     roofline = {"bound": "hbm", "kernel": dom_name, "achieved": dom_line.get("achieved"), "peak": HBM_PEAK_GBS,

@@ -245,7 +245,8 @@ int caramel_plan_serialize(const caramel_plan* plan, void* buf, size_t* len);
  *   fused_ws  DEVICE workspace of world * fused_elems elements (replica w's fused buffer starts
  *             at element w * fused_elems); may be NULL when fused_elems == 0, or when only
  *             caramel_allreduce in its default (direct) mode is going to be used.
- * The library uploads its descriptor tables (synchronously) and creates its internal stream.
+ * The library uploads or builds its descriptor tables (synchronously, on the default stream) and creates
+ * its internal stream.
  * May be called again to re-bind, with the same device current: the plan's tables, stream and
  * events live on the device that is current at the first bind, and `stream` of the calls below
  * must belong to it.  EINVAL: NULL/misaligned pointer, overlapping buffers (checked before any
@@ -403,6 +404,11 @@ enum { CARAMEL_BATCH_STAGED = 0, CARAMEL_BATCH_DIRECT = 1 };
  * there); the others at the next launch.
  * EINVAL for an unknown option or a value out of range. */
 int caramel_plan_set_option(caramel_plan* plan, uint32_t option, uint64_t value);
+
+/* Whether caramel_allreduce, with the options as they are, runs the bound plan over slices (above): `workgroups` of
+ * `lanes` lanes each, `per_wavefront` slices in each wavefront, in one launch; all 0 if it runs over tiles.  Pointers
+ * may be NULL.  ESTATE: plan not bound. */
+int caramel_plan_slices(const caramel_plan* plan, uint32_t* workgroups, uint32_t* lanes, uint32_t* per_wavefront);
 
 enum {
   CARAMEL_K_PACK = 0,

@@ -69,6 +69,10 @@ def caramel_plan_set_option(plan: Plan, option: int, value: int) -> None:
     plan.set_option(option, value)
 
 
+def caramel_plan_slices(plan: Plan):
+    return plan.slices()
+
+
 def caramel_bind(plan: Plan, grad_ptrs, fused_ws) -> None:
     plan.bind(grad_ptrs, fused_ws)
 

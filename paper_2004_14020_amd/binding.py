@@ -32,7 +32,7 @@ EXPORTS = (
     "caramel_threshold_estimate", "caramel_schedule_transfers", "caramel_plan_windows", "caramel_plan_destroy", "caramel_plan_counts", "caramel_plan_units",
     "caramel_plan_entries", "caramel_plan_segments", "caramel_plan_serialize", "caramel_bind",
     "caramel_pack", "caramel_ring_reduce", "caramel_unpack", "caramel_allreduce", "caramel_allreduce_static",
-    "caramel_plan_set_option", "caramel_profile", "caramel_profile_read", "caramel_last_error",
+    "caramel_plan_set_option", "caramel_plan_slices", "caramel_profile", "caramel_profile_read", "caramel_last_error",
     "caramel_version", "caramel_stream_probe", "caramel_allreduce_loop",
 )
 
@@ -114,6 +114,7 @@ def lib() -> C.CDLL:
         getattr(L, name).argtypes = [P, P]
     L.caramel_allreduce_static.argtypes = [P, C.POINTER(P), P]
     L.caramel_plan_set_option.argtypes = [P, C.c_uint32, C.c_uint64]
+    L.caramel_plan_slices.argtypes = [P, C.POINTER(C.c_uint32), C.POINTER(C.c_uint32), C.POINTER(C.c_uint32)]
     L.caramel_profile.argtypes = [P, C.c_int]
     L.caramel_profile_read.argtypes = [P, C.POINTER(KernelStat)]
     L.caramel_last_error.restype = C.c_char_p
@@ -247,6 +248,12 @@ class Plan:
             raise ValueError("grad_ptrs must be world x n_tensors")
         flat = (C.c_void_p * (W * n))(*[int(grad_ptrs[w][t]) for w in range(W) for t in range(n)])
         _check(lib().caramel_allreduce_static(self._h, flat, C.c_void_p(stream)))
+
+    def slices(self):
+        """(workgroups, lanes, slices per wavefront) of allreduce on the bound plan; None if it runs over tiles."""
+        g, n, v = C.c_uint32(), C.c_uint32(), C.c_uint32()
+        _check(lib().caramel_plan_slices(self._h, C.byref(g), C.byref(n), C.byref(v)))
+        return (g.value, n.value, v.value) if g.value else None
 
     def allreduce_loop(self, n_calls: int, stream: int = 0):
         """(host microseconds to issue one call, microseconds one call takes on the stream)."""

@@ -302,6 +302,11 @@ int run_reduce(caramel_plan* p, const Binding& bd, const DeviceTables& dt, bool 
   return CARAMEL_OK;
 }
 
+// Whether caramel_allreduce reduces batch units where their members lie.
+bool reduces_in_place(const caramel_plan* p) {
+  return p->opt.batch_path == CARAMEL_BATCH_DIRECT || p->host.fused_elems == 0;
+}
+
 // Reduction in place of a job that was cut into slices at bind: one launch on the caller's stream.  An
 // option that asks for tiles, or for the pipeline, takes the tiles instead.
 bool use_slices(const caramel_plan* p, bool direct, bool pipelined) {
@@ -776,6 +781,16 @@ int caramel_plan_set_option(caramel_plan* p, uint32_t option, uint64_t value) {
   }
 }
 
+int caramel_plan_slices(const caramel_plan* p, uint32_t* workgroups, uint32_t* lanes, uint32_t* per_wavefront) {
+  if (!p) return fail(CARAMEL_EINVAL, "plan is NULL");
+  if (!p->bound) return fail(CARAMEL_ESTATE, "plan is not bound to device memory");
+  const SliceArgs a = use_slices(p, reduces_in_place(p), use_pipeline(p)) ? p->slices : SliceArgs{};
+  if (workgroups) *workgroups = a.groups;
+  if (lanes) *lanes = a.lanes;
+  if (per_wavefront) *per_wavefront = a.vecs;
+  return CARAMEL_OK;
+}
+
 namespace {
 int bind_plan(caramel_plan* p, void* const* grads, void* fused_ws);
 }
@@ -921,6 +936,9 @@ int bind_plan(caramel_plan* p, void* const* grads, void* fused_ws) {
     std::fprintf(stderr, "caramel: bind  %zu units, long tiles of %u vectors, small of %u, runs of %llu bytes or more are long\n",
                  h.units.size(), p->bind.shape.long_vecs, p->bind.shape.small_vecs,
                  (unsigned long long)p->bind.shape.long_run_bytes);
+    if (p->slices.groups)
+      std::fprintf(stderr, "caramel: bind  in place over slices: %u workgroups of %u lanes, %u slices per wavefront\n",
+                   p->slices.groups, p->slices.lanes, p->slices.vecs);
     for (size_t u = 0; u < h.units.size(); ++u) {
       const UnitTiles& ut = p->bind.tt.direct_unit[u];
       std::fprintf(stderr, "caramel: unit %zu %s stream %u %llu bytes per replica: %u long + %u small tiles\n", u,
@@ -962,7 +980,7 @@ int caramel_ring_reduce(caramel_plan* p, void* stream) {
 
 int caramel_allreduce(caramel_plan* p, void* stream) {
   return guarded([&]() -> int {
-    const bool direct = p && (p->opt.batch_path == CARAMEL_BATCH_DIRECT || p->host.fused_elems == 0);
+    const bool direct = p && reduces_in_place(p);
     if (int rc = need_bound(p, !direct)) return rc;
     return pipeline(p, hipStream_t(stream), true, direct);
   });
@@ -1046,7 +1064,7 @@ int caramel_allreduce_loop(caramel_plan* p, void* stream, uint32_t n_calls, doub
                            double* stream_us_per_call) {
   return guarded([&]() -> int {
     if (!host_us_per_call || !stream_us_per_call || n_calls == 0) return fail(CARAMEL_EINVAL, "NULL argument or no calls");
-    const bool direct = p && (p->opt.batch_path == CARAMEL_BATCH_DIRECT || p->host.fused_elems == 0);
+    const bool direct = p && reduces_in_place(p);
     if (int rc = need_bound(p, !direct)) return rc;
     hipStream_t s = hipStream_t(stream);
     hipEvent_t e0 = nullptr, e1 = nullptr;

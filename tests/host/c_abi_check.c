@@ -53,6 +53,8 @@ int main(void) {
   CHECK(caramel_plan_serialize(plan, image, &len) == CARAMEL_OK && memcmp(image, "CARAMEL1", 8) == 0);
   /* device calls on an unbound plan are refused before anything touches a GPU */
   CHECK(caramel_allreduce(plan, NULL) == CARAMEL_ESTATE);
+  CHECK(caramel_plan_slices(plan, NULL, NULL, NULL) == CARAMEL_ESTATE);
+  CHECK(caramel_plan_slices(NULL, NULL, NULL, NULL) == CARAMEL_EINVAL);
   CHECK(strlen(caramel_last_error()) > 0);
   caramel_plan_destroy(plan);
   caramel_plan_destroy(NULL);

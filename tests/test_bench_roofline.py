@@ -14,6 +14,14 @@ def test_name_of_the_reduce_kernel(pattern, world, bf16, long_tiles, name):
     assert bench.reduce_kernel(pattern, world, bf16, long_tiles) == name
 
 
+@pytest.mark.parametrize("pattern,world,slices,name", [
+    ("ring", 4, (263, 256, 1), "k_slice"), ("shuffle", 16, (256, 256, 12), "k_slices"), ("ring", 12, (256, 1024, 5), "k_slices"),
+    ("hd", 1, (9, 256, 1), "k_slice"), ("hd", 8, (30, 256, 1), "k_tree_slice"), ("hd", 64, (200, 256, 8), "k_tree_slices"),
+    ("ring", 8, None, "k_ring_reduce")])
+def test_name_of_the_kernel_over_slices(pattern, world, slices, name):
+    assert bench.reduce_kernel(pattern, world, False, False, slices) == name
+
+
 def test_traffic_comes_from_a_profile_of_the_same_kernel(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     (tmp_path / "profiles").mkdir()
