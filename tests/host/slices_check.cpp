@@ -215,9 +215,15 @@ int main() {
     cfg.num_streams = uint32_t(pick({1, 2}));
     cfg.pattern = uint32_t(pick({CARAMEL_PATTERN_RING, CARAMEL_PATTERN_RING, CARAMEL_PATTERN_SHUFFLE, CARAMEL_PATTERN_HALVING_DOUBLING}));
     if (cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING && (cfg.world & (cfg.world - 1))) cfg.world = 16;
-    const bool large = it % 13 == 0;  // enough slices for every shape
+    const bool wide = it % 20 == 3, large = it % 13 == 0;  // one round of 256 lanes; more than that, fp32 chains
     std::vector<uint64_t> elems(1 + rng() % (large ? 3 : 40));
     for (uint64_t& e : elems) e = large ? 700001 + rng() % 2000000 : pick({1, 2, 3, 17, 100, 257, 1000, 4099, 16384, 70001});
+    if (wide) {
+      cfg.world = uint32_t(pick({10, 12, 16, 24}));
+      cfg.dtype = CARAMEL_F32;
+      if (cfg.pattern == CARAMEL_PATTERN_HALVING_DOUBLING) cfg.pattern = CARAMEL_PATTERN_RING;
+      elems.assign({5600001 + rng() % 1000000, 17, 1 + rng() % 1000000});  // 21 to 30 MiB
+    }
     HostPlan p;
     std::string why;
     CHECK(build_host_plan(cfg, elems.data(), uint32_t(elems.size()), nullptr, 0.0, 0.0, p, why) == CARAMEL_OK);
@@ -226,7 +232,7 @@ int main() {
     for (size_t t = 0; t < elems.size(); ++t) {
       const uint64_t common = rng() % 4096;
       for (uint32_t w = 0; w < cfg.world; ++w)
-        rows[t * cfg.world + w] = (uint64_t(1) << 46) + (uint64_t(w) << 29) + (uint64_t(t) << (large ? 24 : 21)) + (alike ? common : rng() % 4096) * cfg.align_bytes;
+        rows[t * cfg.world + w] = (uint64_t(1) << 46) + (uint64_t(w) << 29) + (uint64_t(t) << (wide ? 25 : (large ? 24 : 21))) + (alike ? common : rng() % 4096) * cfg.align_bytes;
     }
     if (it % 20 == 1 && rows.size() > 2 * cfg.world) {  // out of the table's reach
       std::vector<uint64_t> far = rows;
@@ -246,7 +252,7 @@ int main() {
     const uint32_t lanes = uint32_t(pick({256, 512, 1024})), vecs = uint32_t(pick({1, 4, 5, 20}));
     check(p, SliceShape{lanes, vecs, uint32_t(1 + rng() % (lanes / 64 * vecs))}, rows, alike);
   }
-  CHECK(shapes["256 x 1"] && shapes["256 x n"]);
+  CHECK(shapes["256 x 1"] && shapes["256 x n"] && shapes["512 x n"] && shapes["1024 x n"]);
   std::printf("slices_check ok\n");
   return 0;
 }

@@ -72,3 +72,35 @@ def test_random_configurations(chunk):
         plan.allreduce()
         assert_same_bits(dev.download(), ref, f"chunk {chunk} case {case}")
         plan.close()
+
+
+def draw_small(rng: random.Random):
+    """A job that the library cuts as it likes: no option that shapes tiles, every replica elsewhere."""
+    cfg, elems, _, place = draw(rng)
+    elems += [rng.choice([400001, 999999, 1500000, 3000001]) for _ in range(rng.randint(0, 2) if cfg.world <= 16 else 0)]
+    opts = {cm.OPT_LAUNCH_MIN_BYTES: rng.choice([0, 65536, 4 << 20]), cm.OPT_MERGE_SMALL_BYTES: rng.choice([0, 1 << 20])}
+    place.pop("arena_phase")
+    place["arena_phases"] = [256 * rng.randrange(256) for _ in range(cfg.world)]
+    if rng.random() < 0.3:
+        place["arena_phases"] = [place["arena_phases"][0]] * cfg.world
+    return cfg, elems, opts, place
+
+
+@pytest.mark.parametrize("chunk", range(6))
+def test_random_small_jobs(chunk):
+    rng = random.Random(4140220 + chunk)
+    over_slices = 0
+    for case in range(20):
+        cfg, elems, opts, place = draw_small(rng)
+        print(f"case: random small chunk {chunk} case {case}: {cfg} elems={elems} opts={opts} place={place}", flush=True)
+        grads = make_inputs(cfg, elems, seed=5000 + 1000 * chunk + case)
+        ref = oracle_result(cfg, elems, grads)
+        plan = lib_plan(cfg, elems, opts)
+        dev = Replicas(plan, elems, **place)
+        over_slices += plan.slices() is not None
+        dev.upload(grads)
+        dev.fill_fused(0xA5)
+        plan.allreduce()
+        assert_same_bits(dev.download(), ref, f"chunk {chunk} case {case}")
+        plan.close()
+    assert over_slices >= 18
