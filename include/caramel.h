@@ -308,8 +308,10 @@ int caramel_allreduce_static(caramel_plan* plan, void* const* grads, void* strea
  * While the options below that shape tiles and their kernels have their defaults (2 to 6, 9 to 12, 14, 16, 17) and
  * the launch mode is AUTO without the pipeline, small jobs that are reduced in place are cut into 1 KiB slices
  * instead and go out in one launch: less than 32 MiB per replica, 112 with 2 workers, 48 with 3 to 6, 36 with 7
- * and 8 (halving-doubling: 112 with 2, 48 with 4), but for a few shapes for which tiles are faster.  Their
- * table is built at caramel_bind; an option that asks for tiles takes effect all the same. */
+ * and 8 (halving-doubling: 112 with 2, 48 with 4), but for some shapes for which tiles are faster
+ * (caramel_plan_slices says what a plan got).  Their table is built at caramel_bind.  One of those options at
+ * another value than its default gives tiles at the next call, also after the bind; set to its default it does
+ * not, and a plan that was bound without slices has tiles until it is bound again. */
 enum {
   /* How units map to kernel launches.  PER_UNIT: consecutive units of a plan stream share a
    * launch until it covers CARAMEL_OPT_LAUNCH_MIN_BYTES / CARAMEL_OPT_LONG_LAUNCH_MIN_BYTES

@@ -74,8 +74,8 @@ __device__ __forceinline__ f32x4 bits_to_f32(u32x4 v) { return __builtin_bit_cas
 __device__ __forceinline__ u32x4 f32_to_bits(f32x4 v) { return __builtin_bit_cast(u32x4, v); }
 
 // fp32 -> bf16, round to nearest, ties to even; NaN stays a (quiet) NaN.  Two values to a conversion
-// instruction (it equals the integer arithmetic  (b + 0x7FFF + (b >> 16 & 1)) >> 16,  NaN: b >> 16 | 0x40,
-// on all 2^32 bit patterns, in both halves), where that arithmetic takes six instructions a value.
+// instruction (it equals the integer arithmetic  (b + 0x7FFF + (b >> 16 & 1)) >> 16,  NaN: b >> 16 | 0x40;
+// tests/test_gpu_rounding.py), where that arithmetic takes six instructions a value.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
@@ -949,7 +949,9 @@ k_slice(const uint32_t* places, const uint32_t* lengths, uint64_t base, uint32_t
 // (as in k_tree_walk).  One round of 256-lane workgroups, like k_slices: one wavefront per SIMD, so 512 registers
 // hold four buffers and the open partial sums of every level.  The next pair of workers is on its way while a pair is
 // added.  Eight workers to a turn of the loop; the sums of the turns are merged by its number's trailing ones.
-// Bound: HBM, and the latencies of W / 2 pairs.
+// Bound: HBM, and the latencies of W / 2 pairs.  No vector register is spilled, but scalar ones are, to lanes of vector
+// registers (N places and as many buffer descriptors of four words): 8 workers none, 2 and 4 workers up to 134, at the
+// widest, 16 to 64 workers 6 to 12 with N = 4, 54 to 82 with 6, up to 249 with 14.
 template <bool BF16, int P, int W, int N>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 k_tree_slices(const uint32_t* places, const uint32_t* lengths, uint64_t base, float inv_w) {
