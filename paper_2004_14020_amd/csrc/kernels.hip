@@ -1245,28 +1245,40 @@ hipError_t launch_slice_table(const SliceTable& t, const SlicePiece* pieces, con
 hipError_t launch_slices(const SliceArgs& a, hipStream_t s) {
   const float inv_w = 1.0f / float(a.world);
   const dim3 grid(a.groups), lanes(a.lanes);
-  const bool through = a.policy == kThrough, one = a.vecs == 1 && a.lanes == 256;
+  const bool through = a.policy == kThrough;
+#define CARAMEL_SKIP(...)
 #define CARAMEL_ROUND(BF, TH, N, L) \
-  if (!a.tree && a.bf16 == BF && through == TH && a.vecs == N && a.lanes == L) { \
+  if (a.vecs == N && a.bf16 == BF && through == TH && a.lanes == L) { \
     hipLaunchKernelGGL((k_slices<BF, TH ? kThrough : kStream, N, L>), grid, lanes, 0, s, a.at, a.bytes, a.base, a.world, inv_w); \
     return hipGetLastError(); \
   }
 #define CARAMEL_ONE(BF, TH, CW) \
-  if (!a.tree && one && a.bf16 == BF && through == TH && (CW == 0 || a.world == CW)) { \
+  if ((CW == 0 || a.world == CW) && a.bf16 == BF && through == TH) { \
     hipLaunchKernelGGL((k_slice<BF, TH ? kThrough : kStream, CW>), grid, lanes, 0, s, a.at, a.bytes, a.base, a.world, inv_w); \
     return hipGetLastError(); \
   }
 #define CARAMEL_TREE_ROUND(W, BF, N) \
-  if (a.tree && a.world == W && a.bf16 == BF && !through && a.vecs == N && a.lanes == 256) { \
+  if (a.vecs == N && a.world == W && a.bf16 == BF && !through && a.lanes == 256) { \
     hipLaunchKernelGGL((k_tree_slices<BF, kStream, W, N>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w); \
     return hipGetLastError(); \
   }
 #define CARAMEL_TREE_ONE(W, BF, TH) \
-  if (a.tree && one && a.world == W && a.bf16 == BF && through == TH) { \
+  if (a.world == W && a.bf16 == BF && through == TH) { \
     hipLaunchKernelGGL((k_tree_slice<BF, TH ? kThrough : kStream, W>), grid, lanes, 0, s, a.at, a.bytes, a.base, inv_w); \
     return hipGetLastError(); \
   }
-  CARAMEL_SLICE_KERNELS(CARAMEL_ROUND, CARAMEL_ONE, CARAMEL_TREE_ROUND, CARAMEL_TREE_ONE)
+  if (a.vecs == 1 && a.lanes == 256) {
+    if (a.tree) {
+      CARAMEL_SLICE_KERNELS(CARAMEL_SKIP, CARAMEL_SKIP, CARAMEL_SKIP, CARAMEL_TREE_ONE)
+    } else {
+      CARAMEL_SLICE_KERNELS(CARAMEL_SKIP, CARAMEL_ONE, CARAMEL_SKIP, CARAMEL_SKIP)
+    }
+  } else if (a.tree) {
+    CARAMEL_SLICE_KERNELS(CARAMEL_SKIP, CARAMEL_SKIP, CARAMEL_TREE_ROUND, CARAMEL_SKIP)
+  } else {
+    CARAMEL_SLICE_KERNELS(CARAMEL_ROUND, CARAMEL_SKIP, CARAMEL_SKIP, CARAMEL_SKIP)
+  }
+#undef CARAMEL_SKIP
 #undef CARAMEL_ROUND
 #undef CARAMEL_ONE
 #undef CARAMEL_TREE_ROUND
