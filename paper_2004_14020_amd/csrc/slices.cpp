@@ -101,7 +101,9 @@ static uint64_t longest_mean_piece(const HostPlan& p) {
 //  * Stores: what one round writes is left to the last-level cache, where it fits (8 workers 4 MiB 12.6 written
 //    through, 11.6; 2 workers 12 MiB 9.2 / 8.8; called one at a time 8 x 15 MB 56.0 / 53.0; 32 workers 12 MiB, 384
 //    MiB in all, 142 / 144).  Longer jobs write while others read, and are better off through (4 workers 30
-//    MiB 43.8 / 44.9, 8 workers 87.4 / 90.1).
+//    MiB 43.8 / 44.9, 8 workers 87.4 / 90.1), but for up to 64 MiB in all: where those are still in the caches, writing
+//    through made them slower than tiles (2 workers bf16 17 MiB, called over and over on the same memory 11.4 tiles /
+//    13.6 through / 11.8, with others in between 14.6 / 13.6 / 14.3; 31 MiB 21.7 / 22.6 / 21.4 and 23.5 / 22.3 / 22.9).
 //  * Above one round of 256 lanes, fp32 chains: from 16 workers on one round of 512 lanes (24 workers 26 MiB 247 /
 //    238, 32 workers 31 MiB 414 / 375); 8 to 15 workers 1024 lanes in equal shares (8 workers 31 MiB 100 / 90, 12
 //    workers 144 / 136), but where that comes to seven vectors per lane again 512 lanes (12 workers 27 MiB
@@ -139,17 +141,19 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
     return s;
   }
   if (W == 1 || (tree && W >= 32) || (bf16 && W > 8 && W < 16 && n > 24576 && n <= 28672)) return {};
-  s.through = true;
+  s.through = W * replica_bytes > (uint64_t(64) << 20);
   if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
   const bool ring = p.cfg.pattern == CARAMEL_PATTERN_RING;
   if (!bf16 && ring && W >= 8 && W < 16 && n <= (W == 9 ? 24576u : 82u * kComputeUnits)) return s;
   if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
     s.lanes = 512;
+    s.through = true;
     s.vecs = std::clamp(up((n + 1549) / 1550, 2), 14u, most);
     s.share = 8 * s.vecs;
   } else if (bf16 ? W > 8 && W <= 24 && n > 20480 : W >= 8) {
     const uint64_t full = 16 * (bf16 ? 6 : 8) * kComputeUnits, rounds = (n + full - 1) / full;
     s.lanes = 1024;
+    s.through = true;
     s.share = uint32_t((n + rounds * kComputeUnits - 1) / (rounds * kComputeUnits));
     s.vecs = std::max<uint32_t>(bf16 ? 4 : 5, (s.share + 15) / 16);
   }

@@ -116,6 +116,15 @@ static std::string shape_of(uint32_t world, uint32_t dtype, uint32_t pattern, ui
   return s.vecs ? std::to_string(s.lanes) + " x " + std::to_string(s.vecs) : "tiles";
 }
 
+static bool through(uint32_t world, uint32_t dtype, uint32_t pattern, uint64_t n) {
+  HostPlan p;
+  p.cfg.world = world;
+  p.cfg.dtype = dtype;
+  p.cfg.pattern = pattern;
+  p.replica_elems = n * kSliceBytes / p.elem_size();
+  return choose_slices(p, n, 1000).through;
+}
+
 // Lines at which sweeps have found the other side to be slower.
 static void lines() {
   const uint32_t ring = CARAMEL_PATTERN_RING, shuffle = CARAMEL_PATTERN_SHUFFLE, f32 = CARAMEL_F32, bf16 = CARAMEL_BF16;
@@ -148,6 +157,11 @@ static void lines() {
     CHECK(shape_of(j.world, j.dtype, j.pattern, 32767, 1) != "tiles");
   }
   for (uint32_t W = 3; W <= 6; ++W) CHECK(shape_of(W, f32, shuffle, 47 << 10, 1) == "256 x 1");
+  // many rounds: written through from 64 MiB in all on
+  for (uint32_t pattern : {ring, shuffle, hd})
+    for (uint32_t dtype : {f32, bf16})
+      for (uint64_t n : {uint64_t(20481), uint64_t(32768)}) CHECK(!through(2, dtype, pattern, n) && through(2, dtype, pattern, 32769));
+  CHECK(!through(3, bf16, ring, 21845) && through(3, bf16, ring, 21846) && through(5, f32, ring, 20481));
   CHECK(shape_of(2, f32, shuffle, 111 << 10, 1) == "256 x 1");
 }
 
