@@ -32,7 +32,7 @@ uint64_t slice_pieces(const HostPlan& p, const uint64_t* row_addr, std::vector<S
     if (row != phase_row) phase = common_phase(row_addr, row, W), phase_row = row;
     const uint64_t at = row_elem * es, end = at + elems * es;
     out.push_back(SlicePiece{uint32_t(n), row, uint32_t(at / 16), uint32_t(end - at), uint16_t(phase), uint16_t(first)});
-    n += (end + phase + kSliceBytes - 1) / kSliceBytes - (at + phase) / kSliceBytes;
+    n += slices_of(out.back());
   };
   for (uint32_t ui = 0; ui < p.units.size(); ++ui) {
     const caramel_unit& u = p.units[ui];

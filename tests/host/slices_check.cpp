@@ -46,6 +46,8 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
   const SliceTable t = slice_table(p, shape, n, pieces.size(), rows.data());
   CHECK(t.lanes == shape.lanes && t.vecs == V && shape.share <= waves * V);
   CHECK(t.at_words() == size_t(t.groups) * waves * V * W + 16 && t.bytes_words() == size_t(t.groups) * waves * (V + 1));
+  std::map<std::pair<size_t, uint64_t>, uint64_t> piece_bytes;  // by tensor and place
+  for (const SlicePiece& c : pieces) piece_bytes[{c.row, uint64_t(c.at) * 16}] = c.bytes;
   // as k_slice_table does, a lane per slice and up to 16 steps
   struct {
     uint64_t base;
@@ -89,7 +91,11 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
       CHECK(step < W && off % 16 == 0 && off + whole <= p.tensor_elems[tensor] * es);
       const uint32_t f = (W - step) % W;
       for (uint32_t k = 0; k < W; ++k) CHECK(address(k) == rows[tensor * W + (f + k) % W] + off);
-      if (alike) CHECK(address(0) / kSliceBytes == (address(0) + whole - 1) / kSliceBytes);
+      // inside one aligned block, or a whole piece
+      if (alike && address(0) / kSliceBytes != (address(0) + whole - 1) / kSliceBytes) {
+        const auto c = piece_bytes.find(std::make_pair(tensor, off));
+        CHECK(c != piece_bytes.end() && c->second == whole);
+      }
       for (uint64_t e = off / es; e < (off + whole) / es; ++e) {
         CHECK(!seen[tensor][e] && first[tensor][e] == f);
         seen[tensor][e] = 1;
