@@ -98,6 +98,12 @@ static uint64_t longest_mean_piece(const HostPlan& p) {
 //    over sooner (8 workers 1.2 MiB 6.0, two vectors 6.1, four 6.6; 2.1 MiB 8.2, four 7.5).  Up to 4 workers there
 //    are fewer steps to wait for (4 workers 2.2 MiB 5.2, four vectors 5.3; 2.7 MiB 5.5 / 5.3).  Trees, which take
 //    the workers by pairs, have two vectors from 1000 slices on (16 workers 1.5 MiB 11.4, two vectors 9.7).
+//  * Many tensors of a few hundred bytes: slices are short, and what counts is how many of them are on their way.  One
+//    per wavefront where otherwise four would take turns (ring, tiles / four / one: 16 workers 2500 tensors of 64 bytes
+//    6.45 / 8.54 / 5.91, 3000 of 256 7.7 / 8.9 / 7.1, 8 workers 5.3 / 5.4 / 4.2; 6000, eight vectors: 8 workers 8.2 / 6.5,
+//    16 12.6 / 11.4), and beyond one round, with up to 15 fp32 workers up to 700 bytes a slice (8 workers 15000 of
+//    1200 bytes 60.8 / 1024 lanes 61.9 / 56.9, 16 workers 60000 of 64 86.4 / 512 lanes 84.4 / 67.3; trees over 32 and 64
+//    with tensors of 600 bytes 0.87 of the time of tiles).
 //  * Stores: what one round writes is left to the last-level cache, where it fits (8 workers 4 MiB 12.6 written
 //    through, 11.6; 2 workers 12 MiB 9.2 / 8.8; called one at a time 8 x 15 MB 56.0 / 53.0; 32 workers 12 MiB, 384
 //    MiB in all, 142 / 144).  Longer jobs write while others read, and are better off through (4 workers 30
@@ -132,7 +138,14 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
   auto up = [](uint64_t v, uint32_t step) { return uint32_t((v + step - 1) / step * step); };
   SliceShape s{256, 1, 4, W * replica_bytes > (uint64_t(256) << 20)};
   if (n <= (tree ? 1024u : (W <= 4 ? 2560u : 2048u))) return s;
-  if (n <= uint64_t(4) * most * kComputeUnits) {
+  const uint64_t whole = uint64_t(4) * most * kComputeUnits;  // slices of one round of 256 lanes
+  const bool one_round = n <= whole, large = W * replica_bytes > (uint64_t(64) << 20);
+  const uint32_t shortest = one_round ? (n <= 4096 ? 320 : 0) : ((!bf16 && W >= 8 && W < 16) || (tree && W >= 32) ? 700 : 320);
+  if (replica_bytes < n * shortest) {
+    s.through = large && !(tree && W >= 32);
+    return s;
+  }
+  if (one_round) {
     const uint64_t each = n <= 8192 ? 4 * kComputeUnits : 850;
     s.vecs = std::min(most, up((n + each - 1) / each, tree && n > 8192 ? 4 : 2));
     if (!tree) s.vecs = std::max(s.vecs, 4u);
@@ -141,7 +154,7 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
     return s;
   }
   if (W == 1 || (tree && W >= 32) || (bf16 && W > 8 && W < 16 && n > 24576 && n <= 28672)) return {};
-  s.through = W * replica_bytes > (uint64_t(64) << 20);
+  s.through = large;
   if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
   const bool ring = p.cfg.pattern == CARAMEL_PATTERN_RING;
   if (!bf16 && ring && W >= 8 && W < 16 && n <= (W == 9 ? 24576u : 82u * kComputeUnits)) return s;

@@ -111,13 +111,14 @@ static void check(const HostPlan& p, const SliceShape& shape, const std::vector<
     for (uint8_t x : s) CHECK(x == 1);
 }
 
-// The shape of a job of n slices (all of them full), as "lanes x vecs", "tiles" if it has none.
-static std::string shape_of(uint32_t world, uint32_t dtype, uint32_t pattern, uint64_t n, uint64_t pieces = 1000) {
+// The shape of a job of n slices of so many bytes on average, as "lanes x vecs", "tiles" if it has none.
+static std::string shape_of(uint32_t world, uint32_t dtype, uint32_t pattern, uint64_t n, uint64_t pieces = 1000,
+                            uint64_t slice_bytes = kSliceBytes) {
   HostPlan p;
   p.cfg.world = world;
   p.cfg.dtype = dtype;
   p.cfg.pattern = pattern;
-  p.replica_elems = n * kSliceBytes / p.elem_size();
+  p.replica_elems = n * slice_bytes / p.elem_size();
   const SliceShape s = choose_slices(p, n, pieces);
   return s.vecs ? std::to_string(s.lanes) + " x " + std::to_string(s.vecs) : "tiles";
 }
@@ -163,6 +164,16 @@ static void lines() {
     CHECK(shape_of(j.world, j.dtype, j.pattern, 32767, 1) != "tiles");
   }
   for (uint32_t W = 3; W <= 6; ++W) CHECK(shape_of(W, f32, shuffle, 47 << 10, 1) == "256 x 1");
+  // many short slices
+  for (uint32_t dtype : {f32, bf16})
+    for (uint32_t pattern : {ring, shuffle, hd}) {
+      CHECK(shape_of(16, dtype, pattern, 4096, 4096, 319) == "256 x 1" && shape_of(16, dtype, pattern, 4096, 4096, 320) == "256 x 4");
+      CHECK(shape_of(16, dtype, pattern, 4097, 4097, 64) == "256 x 6");
+      CHECK(shape_of(16, dtype, pattern, 30000, 30000, 319) == "256 x 1");
+    }
+  CHECK(shape_of(16, f32, ring, 30000, 30000, 320) == "512 x 20" && shape_of(8, f32, shuffle, 30000, 30000, 699) == "256 x 1");
+  CHECK(shape_of(8, f32, shuffle, 30000, 30000, 700) == "1024 x 8" && shape_of(32, bf16, hd, 30000, 30000, 699) == "256 x 1");
+  CHECK(shape_of(32, bf16, hd, 30000, 30000, 700) == "tiles");
   // many rounds: written through from 64 MiB in all on
   for (uint32_t pattern : {ring, shuffle, hd})
     for (uint32_t dtype : {f32, bf16})
@@ -199,7 +210,7 @@ static void kernels() {
         if (pattern == CARAMEL_PATTERN_HALVING_DOUBLING && (world & (world - 1))) continue;
         const bool tree = pattern == CARAMEL_PATTERN_HALVING_DOUBLING && world > 1;
         for (uint64_t n = 1; n < 150000; n += n < 70000 ? 61 : 997)
-          for (uint64_t filled : {1024, 700, 200}) {  // bytes of a slice on average
+          for (uint64_t filled : {1024, 701, 400, 200}) {  // bytes of a slice on average
             HostPlan p;
             p.cfg.world = world;
             p.cfg.dtype = dtype;
