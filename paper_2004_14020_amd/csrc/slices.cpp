@@ -113,16 +113,17 @@ static uint64_t longest_mean_piece(const HostPlan& p) {
 //  * Above one round of 256 lanes, fp32 chains: from 16 workers on one round of 512 lanes (24 workers 26 MiB 247 /
 //    238, 32 workers 31 MiB 414 / 375); 8 to 15 workers 1024 lanes in equal shares (8 workers 31 MiB 100 / 90, 12
 //    workers 144 / 136), but where that comes to seven vectors per lane again 512 lanes (12 workers 27 MiB
-//    122.5 / 125.4, with 512 lanes 122), and rings one vector per lane where a sixth row of slices would be nearly
-//    empty, over 9 workers also where it is not full (tiles / 1024 lanes / one vector: 20 MiB 8 workers 62.7 / 62.9 /
-//    60.4, 9 68.9 / 70.8 / 67.4, 12 92.0 / 93.3 / 92.0; 23 MiB 9 workers 77.9 / 78.3 / 77.0; shuffle over 12 and more
-//    of 20 MiB 1024 lanes 1 to 5 % faster).  Up to 7 workers, and with bf16 but for 9 to 24 workers from 20 MiB on, one
-//    vector per lane in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; 8 workers bf16
-//    98 / 92, 1024 lanes 96; 12 workers bf16 143 / 139, one vector 142.5), and so for trees (8 workers 25 MiB 79.9 /
-//    75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 / 13.0), and so have
-//    halving-doubling over 32 and 64 (one large tensor 2 to 5 % slower, 32 workers 31 MiB 411.8 / 422.5, 64 in bf16 15 MiB
-//    418 / 435; many tensors even to 2 % faster) and 9 to 15 workers in bf16 where a second round of 1024 lanes would be
-//    nearly empty (12 workers 24 MiB 108 / 111).
+//    122.5 / 125.4, with 512 lanes 122), and rings one vector per lane where the last row of slices would be nearly
+//    empty, over 9 workers also where the sixth is not full (tiles / 1024 lanes / one vector: 20 MiB 8 workers 62.7 / 62.9
+//    / 60.4, 9 68.9 / 70.8 / 67.4, 12 92.0 / 93.3 / 92.0; 23 MiB 9 workers 77.9 / 78.3 / 77.0; 27.7 MiB 14 workers 148.7 /
+//    154.4 / 147.5; shuffle over 12 and more of 20 MiB 1024 lanes 1 to 5 % faster).  bf16 chains over 12 to 24 workers from
+//    20 MiB on likewise (12 workers 143 / 139, one vector 142.5).  Up to 7 workers, and with bf16 otherwise, one vector per
+//    lane in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; bf16: 8 workers 98 / 92, 1024
+//    lanes 96; 9 workers 31.5 MiB 107.9 / 103.6, 107.3; 10 118.4 / 117.0, 127.9; 11 20.3 MiB 85.4 / 84.2, 85.4), and so for
+//    trees (8 workers 25 MiB 79.9 / 75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 /
+//    13.0), and so have halving-doubling over 32 and 64 (one large tensor 2 to 5 % slower, 32 workers 31 MiB 411.8 / 422.5,
+//    64 in bf16 15 MiB 418 / 435; many tensors even to 2 % faster) and 12 to 15 workers in bf16 where a second round of
+//    1024 lanes would be nearly empty (12 workers 24 MiB 108 / 111).
 SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
   const uint32_t W = p.cfg.world;
   const uint64_t replica_bytes = p.replica_elems * p.elem_size();
@@ -153,21 +154,21 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
     s.share = 4 * s.vecs;
     return s;
   }
-  if (W == 1 || (tree && W >= 32) || (bf16 && W > 8 && W < 16 && n > 24576 && n <= 28672)) return {};
+  if (W == 1 || (tree && W >= 32) || (bf16 && W >= 12 && W < 16 && n > 24576 && n <= 28672)) return {};
   s.through = large;
   if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
-  const bool ring = p.cfg.pattern == CARAMEL_PATTERN_RING;
-  if (!bf16 && ring && W >= 8 && W < 16 && n <= (W == 9 ? 24576u : 82u * kComputeUnits)) return s;
   if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
     s.lanes = 512;
     s.through = true;
     s.vecs = std::clamp(up((n + 1549) / 1550, 2), 14u, most);
     s.share = 8 * s.vecs;
-  } else if (bf16 ? W > 8 && W <= 24 && n > 20480 : W >= 8) {
+  } else if (bf16 ? W >= 12 && W <= 24 && n > 20480 : W >= 8) {
     const uint64_t full = 16 * (bf16 ? 6 : 8) * kComputeUnits, rounds = (n + full - 1) / full;
+    const uint32_t share = uint32_t((n + rounds * kComputeUnits - 1) / (rounds * kComputeUnits));
+    if (p.cfg.pattern == CARAMEL_PATTERN_RING && ((share - 1) % 16 < 2 || (W == 9 && n <= 24576))) return s;
     s.lanes = 1024;
     s.through = true;
-    s.share = uint32_t((n + rounds * kComputeUnits - 1) / (rounds * kComputeUnits));
+    s.share = share;
     s.vecs = std::max<uint32_t>(bf16 ? 4 : 5, (s.share + 15) / 16);
   }
   return s;

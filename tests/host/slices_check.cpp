@@ -142,7 +142,15 @@ static void lines() {
       for (uint64_t n : {20993, 24576})
         CHECK(shape_of(W, f32, pattern, n) == (pattern == ring && W == 9 ? "256 x 1" : "1024 x 6"));
       CHECK(shape_of(W, f32, pattern, 24577) == "512 x 16");
+      for (uint64_t n : {28673, 29184}) CHECK(shape_of(W, f32, pattern, n) == (pattern == ring ? "256 x 1" : "1024 x 8"));
+      CHECK(shape_of(W, f32, pattern, 29185) == "1024 x 8");
     }
+  for (uint32_t W = 9; W < 16; ++W) {
+    for (uint64_t n : {20481, 24577, 32767}) CHECK((shape_of(W, bf16, shuffle, n) == "256 x 1") == (W < 12));
+    CHECK((shape_of(W, bf16, ring, 26000) == "tiles") == (W >= 12));
+  }
+  CHECK(shape_of(12, bf16, ring, 20992) == "256 x 1" && shape_of(12, bf16, ring, 20993) == "1024 x 6");
+  CHECK(shape_of(24, bf16, ring, 33000, 1000, 900) == "256 x 1" && shape_of(24, bf16, shuffle, 33000, 1000, 900) == "1024 x 5");
   // vectors per lane of one round of a tree over 32 and 64 workers, and what lies beyond
   const uint32_t hd = CARAMEL_PATTERN_HALVING_DOUBLING, most[2][2] = {{14, 12}, {8, 8}};
   for (uint32_t dtype : {f32, bf16})

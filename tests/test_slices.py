@@ -90,13 +90,13 @@ def rounds(*vecs):
 
 # shapes (lanes, slices per wavefront) that these sizes come to, and the sizes that have tiles
 FP32, BF16 = rounds(4, 6, 8, 10, 12, 14, 16, 18, 20), rounds(4, 6, 8, 10, 12, 14, 16)
-WIDE_8 = {(1024, 5), (1024, 6), (1024, 8), (512, 16), (512, 18)}
-WIDE_BF16 = {(1024, 4), (1024, 5), (1024, 6)}
+WIDE_8 = {(1024, 6), (1024, 8), (512, 16), (512, 18)}
+WIDE_BF16 = {(1024, 4), (1024, 6)}
 ABOVE = {2: (113 << 10,), 3: (49 << 10,), 4: (49 << 10,), 6: (49 << 10,), 7: (37 << 10,), 8: (37 << 10,)}
 JOBS = ([("ring", 1, 0, FP32, CHAIN_SIZES[13:]), ("ring", 1, 1, BF16, CHAIN_SIZES[12:])] +
         [("ring", W, d, BF16 if d else FP32, ABOVE[W]) for W in (2, 3, 4, 6, 7) for d in (0, 1)] +
         [("ring", 8, 0, FP32 | WIDE_8, ABOVE[8]), ("ring", 8, 1, BF16, ABOVE[8]),
-         ("shuffle", 8, 0, FP32 | WIDE_8, (35 << 10, 37 << 10)), ("ring", 9, 0, FP32 | WIDE_8 - {(1024, 6)}, ()),
+         ("shuffle", 8, 0, FP32 | WIDE_8 | {(1024, 5)}, (35 << 10, 37 << 10)), ("ring", 9, 0, FP32 | WIDE_8 - {(1024, 6)}, ()),
          ("ring", 12, 0, FP32 | WIDE_8 - {(512, 16)}, ()), ("ring", 12, 1, BF16 | WIDE_BF16, (24577, 26000)),
          ("ring", 16, 0, FP32 | {(512, 14), (512, 16), (512, 18), (512, 20)}, ()), ("ring", 16, 1, BF16 | WIDE_BF16, ()),
          ("ring", 64, 0, rounds(4, 6, 8, 12, 14), ()), ("ring", 64, 1, rounds(4, 6, 8, 12, 14), ()),
