@@ -102,8 +102,7 @@ static uint64_t longest_mean_piece(const HostPlan& p) {
 //    per wavefront where otherwise four would take turns (ring, tiles / four / one: 16 workers 2500 tensors of 64 bytes
 //    6.45 / 8.54 / 5.91, 3000 of 256 7.7 / 8.9 / 7.1, 8 workers 5.3 / 5.4 / 4.2; 6000, eight vectors: 8 workers 8.2 / 6.5,
 //    16 12.6 / 11.4), and beyond one round, with up to 15 fp32 workers up to 700 bytes a slice (8 workers 15000 of
-//    1200 bytes 60.8 / 1024 lanes 61.9 / 56.9, 16 workers 60000 of 64 86.4 / 512 lanes 84.4 / 67.3; trees over 32 and 64
-//    with tensors of 600 bytes 0.87 of the time of tiles).
+//    1200 bytes 60.8 / 1024 lanes 61.9 / 56.9, 16 workers 60000 of 64 86.4 / 512 lanes 84.4 / 67.3).
 //  * Stores: what one round writes is left to the last-level cache, where it fits (8 workers 4 MiB 12.6 written
 //    through, 11.6; 2 workers 12 MiB 9.2 / 8.8; called one at a time 8 x 15 MB 56.0 / 53.0; 32 workers 12 MiB, 384
 //    MiB in all, 142 / 144).  Longer jobs write while others read, and are better off through (4 workers 30
@@ -121,9 +120,10 @@ static uint64_t longest_mean_piece(const HostPlan& p) {
 //    lane in many rounds (5 workers 31 MiB 59 / 58, 1024 lanes 56 but 49.8 / 46.9 at 26; bf16: 8 workers 98 / 92, 1024
 //    lanes 96; 9 workers 31.5 MiB 107.9 / 103.6, 107.3; 10 118.4 / 117.0, 127.9; 11 20.3 MiB 85.4 / 84.2, 85.4), and so for
 //    trees (8 workers 25 MiB 79.9 / 75.3, 16 workers 170 / 158, bf16 165 / 153).  One worker has tiles there (26 MiB 11.5 /
-//    13.0), and so have halving-doubling over 32 and 64 (one large tensor 2 to 5 % slower, 32 workers 31 MiB 411.8 / 422.5,
-//    64 in bf16 15 MiB 418 / 435; many tensors even to 2 % faster) and 12 to 15 workers in bf16 where a second round of
-//    1024 lanes would be nearly empty (12 workers 24 MiB 108 / 111).
+//    13.0), and so have 12 to 15 workers in bf16 where a second round of 1024 lanes would be nearly empty (12 workers 24 MiB
+//    108 / 111), halving-doubling over 64 in fp32 (16 MiB 440 / 447), and over 32 and 64 if pieces are long (one large
+//    tensor 2 to 5 % slower: 32 workers 31 MiB 411.8 / 422.5, 64 in bf16 15 MiB 418 / 435; 60 tensors 3 % faster to 1 % slower,
+//    200 and more, pieces of 150 KiB and less, 0 to 4 % faster, 20000 11 %).
 SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
   const uint32_t W = p.cfg.world;
   const uint64_t replica_bytes = p.replica_elems * p.elem_size();
@@ -141,7 +141,7 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
   if (n <= (tree ? 1024u : (W <= 4 ? 2560u : 2048u))) return s;
   const uint64_t whole = uint64_t(4) * most * kComputeUnits;  // slices of one round of 256 lanes
   const bool one_round = n <= whole, large = W * replica_bytes > (uint64_t(64) << 20);
-  const uint32_t shortest = one_round ? (n <= 4096 ? 320 : 0) : ((!bf16 && W >= 8 && W < 16) || (tree && W >= 32) ? 700 : 320);
+  const uint32_t shortest = one_round ? (n <= 4096 ? 320 : 0) : (!bf16 && W >= 8 && W < 16 ? 700 : 320);
   if (replica_bytes < n * shortest) {
     s.through = large && !(tree && W >= 32);
     return s;
@@ -154,8 +154,9 @@ SliceShape choose_slices(const HostPlan& p, uint64_t n, uint64_t n_pieces) {
     s.share = 4 * s.vecs;
     return s;
   }
-  if (W == 1 || (tree && W >= 32) || (bf16 && W >= 12 && W < 16 && n > 24576 && n <= 28672)) return {};
-  s.through = large;
+  const bool long_pieces = replica_bytes / n_pieces > (192 << 10) || (W == 64 && !bf16);
+  if (W == 1 || (tree && W >= 32 && long_pieces) || (bf16 && W >= 12 && W < 16 && n > 24576 && n <= 28672)) return {};
+  s.through = large && !(tree && W >= 32);
   if (tree || replica_bytes >= (uint64_t(32) << 20)) return s;
   if (!bf16 && (W >= 16 || (W >= 8 && (n + 4095) / 4096 == 7)) && n <= uint64_t(8) * most * kComputeUnits) {
     s.lanes = 512;

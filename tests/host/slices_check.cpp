@@ -157,7 +157,10 @@ static void lines() {
     for (uint32_t W : {32u, 64u}) {
       const uint32_t v = most[dtype == bf16][W == 64];
       CHECK(shape_of(W, dtype, hd, v * 1024) == "256 x " + std::to_string(v));
-      for (uint64_t n : {uint64_t(v * 1024 + 1), uint64_t(32767)}) CHECK(shape_of(W, dtype, hd, n) == "tiles");
+      for (uint64_t n : {uint64_t(v * 1024 + 1), uint64_t(32767)}) {
+        CHECK(shape_of(W, dtype, hd, n, n / 200) == "tiles");
+        CHECK(shape_of(W, dtype, hd, n, n / 180) == (W == 64 && dtype == f32 ? "tiles" : "256 x 1"));
+      }
     }
   // from 32 MiB on, long pieces
   const struct {
@@ -180,8 +183,7 @@ static void lines() {
       CHECK(shape_of(16, dtype, pattern, 30000, 30000, 319) == "256 x 1");
     }
   CHECK(shape_of(16, f32, ring, 30000, 30000, 320) == "512 x 20" && shape_of(8, f32, shuffle, 30000, 30000, 699) == "256 x 1");
-  CHECK(shape_of(8, f32, shuffle, 30000, 30000, 700) == "1024 x 8" && shape_of(32, bf16, hd, 30000, 30000, 699) == "256 x 1");
-  CHECK(shape_of(32, bf16, hd, 30000, 30000, 700) == "tiles");
+  CHECK(shape_of(8, f32, shuffle, 30000, 30000, 700) == "1024 x 8");
   // many rounds: written through from 64 MiB in all on
   for (uint32_t pattern : {ring, shuffle, hd})
     for (uint32_t dtype : {f32, bf16})
